@@ -1549,6 +1549,7 @@ __global__ __launch_bounds__(256) void k_scatter(EngineArgs a) {
 constexpr int NREC = 64;                // distinct children per round in a wavefront's hash
 constexpr int WHASH = 128;              // hash slots per wavefront (load <= 0.5)
 constexpr int POST_QUEUE = 1024;        // new determinants whose H_DD is still to be computed
+constexpr int POST_FLUSH = 256;         // queued new determinants that are computed at once
 constexpr int POST_MAX_SYS = 256;       // systems whose status k_post snapshots in LDS
 constexpr int POST_WIN = 32;            // chunks per window of bucket metadata in LDS
 // the window's POST_WIN BPC + 1 record offsets are loaded by one thread each
@@ -1717,7 +1718,14 @@ __device__ __forceinline__ int wl_claim_limited(det_t D, WaveLds &W, int *ncl, i
 // order of a single sum.
 __device__ __forceinline__ int pair_row(int p, int n) { return p * (2 * n - p - 3) / 2 - 1; }
 
-__device__ __forceinline__ void hdiag_lds2(double e_core, det_t da, det_t db,
+// The table loads of four partners q are issued before their four dependent adds, so a
+// sum waits once per four loads instead of once per load (nel: electrons, uniform).
+__device__ __forceinline__ int take_low(det_t &m) {
+    const int q = dctz(m);
+    m &= m - 1ull;
+    return q;
+}
+__device__ __forceinline__ void hdiag_lds2(double e_core, det_t da, det_t db, int nel,
                                            const double *hpp, const double *jk, int n,
                                            double &ra, double &rb) {
     double xa = e_core, xb = e_core;
@@ -1725,13 +1733,27 @@ __device__ __forceinline__ void hdiag_lds2(double e_core, det_t da, det_t db,
         xa = xa + hpp[dctz(ma)];
         xb = xb + hpp[dctz(mb)];
     }
-    for (det_t m1a = da, m1b = db; m1a; m1a &= m1a - 1ull, m1b &= m1b - 1ull) {
-        const int ba = pair_row(dctz(m1a), n);
-        const int bb = pair_row(dctz(m1b), n);
-        for (det_t m2a = m1a & (m1a - 1ull), m2b = m1b & (m1b - 1ull); m2a;
-             m2a &= m2a - 1ull, m2b &= m2b - 1ull) {
-            xa = xa + jk[ba + dctz(m2a)];
-            xb = xb + jk[bb + dctz(m2b)];
+    det_t m1a = da, m1b = db;
+    for (int left = nel - 1; left > 0; --left) {
+        const int ba = pair_row(take_low(m1a), n), bb = pair_row(take_low(m1b), n);
+        det_t m2a = m1a, m2b = m1b;
+        int r = left;
+        for (; r >= 4; r -= 4) {
+            double va[4], vb[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                va[u] = jk[ba + take_low(m2a)];
+                vb[u] = jk[bb + take_low(m2b)];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                xa = xa + va[u];
+                xb = xb + vb[u];
+            }
+        }
+        for (; r > 0; --r) {
+            xa = xa + jk[ba + take_low(m2a)];
+            xb = xb + jk[bb + take_low(m2b)];
         }
     }
     ra = xa;
@@ -1777,10 +1799,10 @@ __device__ __forceinline__ void flush_new_dets(const SysDesc &d, const uint32_t 
         double h0, h1;
         const det_t k0 = ldk(keys_of(d) + i0), k1 = ldk(keys_of(d) + i1);
 #if FQ_DET_WORDS == 1
-        hdiag_lds2(d.e_core, k0, k1, hpp, jk, d.n_so, h0, h1);
+        hdiag_lds2(d.e_core, k0, k1, d.N, hpp, jk, d.n_so, h0, h1);
 #else
         if (jk)
-            hdiag_lds2(d.e_core, k0, k1, hpp, jk, d.n_so, h0, h1);
+            hdiag_lds2(d.e_core, k0, k1, d.N, hpp, jk, d.n_so, h0, h1);
         else
             hdiag_glb2(d.e_core, k0, k1, hpp, d.jk, h0, h1);
 #endif
@@ -1875,17 +1897,19 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
     const int gwin = per_wg >= POST_WIN ? POST_WIN : per_wg > 0 ? (int)per_wg : 1;
     for (;;) {
         __syncthreads();   // the previous window is done
-        if (s_qn > 0) {    // (uniform)
-            flush();
-            if (t == 0) {
-                s_qn = 0;
-                s_qsys = -1;
-            }
-        }
         if (t == 0) s_win = (int64_t)atomicAdd(&a.work[1], 1u) * gwin;
         __syncthreads();
         const int64_t c0 = s_win;
         if (c0 >= nch) break;
+        // The queue is kept over windows of one system (small launches bring few new
+        // determinants per window, and a flush is a latency of its own): it is emptied when
+        // it holds one per thread or the window begins with another system.
+        if (s_qn >= POST_FLUSH || (s_qn > 0 && a.chunk_sys[c0] != s_qsys)) {   // (uniform)
+            flush();
+            if (t == 0) s_qn = 0;
+        }
+        __syncthreads();
+        if (t == 0 && s_qn == 0) s_qsys = -1;
         const int nwin = (int)(nch - c0 < gwin ? nch - c0 : gwin);
         if (t < nwin) {
             const int sc = a.chunk_sys[c0 + t];
