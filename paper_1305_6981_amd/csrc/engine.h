@@ -36,6 +36,7 @@ struct IterRecord {
     int64_t born;      // determinants that entered the main list
     int64_t used;      // entries in the buckets after the iteration (occupied + the reference)
     int64_t n_var, n_prev;
+    int64_t rec_max;   // most spawn records of one bucket
     double num, shift;
     int32_t varying, status;
 };
@@ -92,6 +93,9 @@ struct SysDesc {
     uint64_t cap;                    // nb * BQ
     int64_t nbuckets;                // nb
     int64_t nchunks, gchunk0;        // chunks (nb / BPC) of this system and the first global one
+    // Spawn records: bucket b's go to slots [rec0 + b rec_r, rec0 + (b + 1) rec_r) of the
+    // handle's record buffer.
+    int64_t rec0, rec_r;
     int64_t stop_at;                 // iterate while iter < stop_at
     // Restricted space (FCIQMC_SPACE_* bits; children outside it are null excitations).
     int32_t space, max_ex, max_sen, pad2;
@@ -114,8 +118,8 @@ struct SysDesc {
     int32_t det_words, pad5;
 };
 
-// A spawn record (16 B, written and read with one vector access): child
-// determinant, signed walkers, and a tag word whose meaning depends on the buffer.
+// A spawn record (16 B, written and read with one vector access): child determinant,
+// signed walkers, and a tag word (bit 0: from an initiator; bits 1-3: k_post's marks).
 struct __attribute__((aligned(16))) SpawnRec {
     uint64_t det;
     int32_t w;
@@ -148,21 +152,15 @@ struct EngineArgs {
     uint32_t *tile_chunk;            // [tile_cap] chunk of each spawn tile (k_scan_down); tiles
     int64_t tile_cap;                // beyond the capacity are found by search
     // Spawn records of the iteration (the per-destination blocks of Sec. 4.1, with the
-    // bucket as destination): appended by k_spawn with their rank among the bucket's
-    // records, grouped by bucket by k_scatter.
-    SpawnRec *recs;                  // [rec_cap] tag: global bucket | initiator flag << 31, or
-                                     // the system | REC_UNRANKED for k_fix to place
-    uint32_t *rec_rank;              // [rec_cap] rank among its bucket's records
-    SpawnRec *srt;                   // [rec_cap] the records grouped by bucket; tag: bit 0
-                                     // initiator flag, bits 1-2 k_post's round marks
-    unsigned long long *rec_count;   // records appended this iteration
-    int64_t rec_cap;
-    uint32_t *bhist;                 // [BPC chunk_cap] records per bucket (zeroed by k_bscan_down)
-    uint32_t *boff;                  // [BPC chunk_cap + 1] first sorted record of each bucket,
-                                     // and the end of the last one
+    // bucket as destination): k_spawn writes a record straight into its child's bucket's
+    // slots (SysDesc::rec0, rec_r), at the place the bucket's counter gives it. Writing
+    // them unsorted and grouping them afterwards (a counting sort in five launches) cost
+    // 115 us of a 3.3 ms iteration and 23 us of a 118 us one.
+    SpawnRec *recs;
+    uint32_t *bhist;                 // [BPC chunk_cap] records per bucket (k_post clears them)
+    uint32_t *rec_max;               // [max_sys] most records of one bucket this iteration
     long long *d0acc;                // [max_sys] walkers spawned onto the reference (kept out of
                                      // the records: the reference is the hot spot of Sec. 4.1)
-    unsigned long long *boff_rg;     // [2 SCAN_G] records per range of buckets, their scan
     // New determinants that did not fit their bucket (completed, then re-bucketed by the host).
     uint64_t *sp_det;
     int32_t *sp_pop, *sp_sys;

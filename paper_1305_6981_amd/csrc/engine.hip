@@ -211,8 +211,11 @@ struct SysHost {
     std::vector<double> t3;    // [n_so][64 W][64 W] single-excitation term table
     double *d_t3 = nullptr;
     int64_t growth = 0;        // expected per-iteration increase of the entries
-    int64_t spawn_peak = 0;    // most spawn records of one iteration in the last launch
-    double spawn_rate = 1.0;   // largest ratio of consecutive iterations' records
+    double spawn_rate = 1.0;   // mean growth of the records per iteration in the last launch
+    int64_t rec_r = 0;         // record slots per bucket
+    int64_t rec_peak = 0;      // most records of one bucket in the last launch (0: unknown)
+    double h_max = 0.0;        // scale of the largest off-diagonal elements
+    int64_t pop_max = 0;       // largest |C| of the list as loaded
     int64_t reserve_bytes = 0; // admission accounting (target footprint)
     // mirrored dynamics and statistics
     IterRecord last{};
@@ -252,11 +255,10 @@ struct fciqmc_t {
     void *d_stage = nullptr;                // this device's staging area (not owned)
     // spawn records (see EngineArgs) and the spill list
     void *d_recs = nullptr;
-    int64_t rec_cap = 0;
-    unsigned long long *d_rec_count = nullptr;
-    uint32_t *d_bhist = nullptr, *d_boff = nullptr;
+    int64_t rec_cap = 0;                    // slots allocated
+    int64_t rec_floor = 65536;              // slots a system's buckets share at least
+    uint32_t *d_bhist = nullptr, *d_rec_max = nullptr;
     long long *d_d0acc = nullptr;
-    unsigned long long *d_boff_rg = nullptr;
     void *d_spill = nullptr;
     int64_t sp_cap = 0;
     unsigned long long *d_sp_count = nullptr;
@@ -314,18 +316,10 @@ EngineArgs make_args(fciqmc_t *h) {
     a.work = h->d_work;
     a.tile_chunk = h->d_tile_chunk;
     a.tile_cap = h->tile_cap;
-    char *r = (char *)h->d_recs;
-    const size_t rc = (size_t)h->rec_cap;
-    const size_t rb = 16 * (size_t)h->W;     // bytes per record
-    a.recs = (SpawnRec *)r;
-    a.srt = (SpawnRec *)(r + rb * rc);
-    a.rec_rank = (uint32_t *)(r + 2 * rb * rc);
-    a.rec_count = h->d_rec_count;
-    a.rec_cap = h->rec_cap;
+    a.recs = (SpawnRec *)h->d_recs;
     a.bhist = h->d_bhist;
+    a.rec_max = h->d_rec_max;
     a.d0acc = h->d_d0acc;
-    a.boff = h->d_boff;
-    a.boff_rg = h->d_boff_rg;
     char *q = (char *)h->d_spill;
     const size_t sc = (size_t)h->sp_cap;
     const size_t kb = 8 * (size_t)h->W;      // bytes per determinant
@@ -344,7 +338,7 @@ EngineArgs make_args(fciqmc_t *h) {
     return a;
 }
 
-// The spawn-record buffer for `cap` records (32 W + 4 B each: unsorted, sorted, rank).
+// The spawn-record buffer for `cap` records (16 W B each).
 int ensure_records(fciqmc_t *h, int64_t cap) {
     if (cap <= h->rec_cap) return 0;
     HIP_TRY(hipStreamSynchronize(h->stream));
@@ -352,12 +346,39 @@ int ensure_records(fciqmc_t *h, int64_t cap) {
     h->d_recs = nullptr;
     h->rec_cap = 0;
     drop_graphs(h);
-    if (hipMalloc(&h->d_recs, (size_t)cap * (32 * h->W + 4)) != hipSuccess) {
+    if (hipMalloc(&h->d_recs, (size_t)cap * (16 * h->W)) != hipSuccess) {
         (void)hipGetLastError();
         return set_err(FCIQMC_ENOMEM, "spawn-record buffer of " + std::to_string(cap) +
                                           " records does not fit in device memory");
     }
     h->rec_cap = cap;
+    return 0;
+}
+
+// Slots per bucket are kept at a multiple of 8: a bucket's records then begin on a
+// 128-byte line.
+int64_t round_slots(double x) { return ((int64_t)std::ceil(x) + 7) / 8 * 8; }
+
+// Fewest record slots per bucket worth having: a small list's buckets share rec_floor
+// slots (early iterations multiply a handful of records), a large list's have 24 each.
+int64_t min_slots(const fciqmc_t *h, int64_t nbuckets) {
+    const int64_t share = h->rec_floor / std::max<int64_t>(nbuckets, 1);
+    return round_slots((double)std::max<int64_t>(24, std::min<int64_t>(share, 1024)));
+}
+
+// Lay the active systems' record slots out one after another, each system's at its own
+// count per bucket; the buffer grows when they need more.
+int layout_records(fciqmc_t *h) {
+    int64_t at = 0;
+    for (int s = 0; s < h->max_sys; ++s) {
+        SysHost &S = h->sys[s];
+        if (!S.active) continue;
+        if (S.rec_r <= 0) S.rec_r = min_slots(h, S.cap / BQ);
+        h->hdesc[s].rec0 = at;
+        h->hdesc[s].rec_r = S.rec_r;
+        at += S.cap / BQ * S.rec_r;
+    }
+    if (at > h->rec_cap) return ensure_records(h, std::max<int64_t>(at, h->rec_cap + h->rec_cap / 4));
     return 0;
 }
 
@@ -400,7 +421,6 @@ int relayout(fciqmc_t *h) {
         hipFree(h->d_chunk_toff);
         hipFree(h->d_chunk_stat);
         hipFree(h->d_bhist);
-        hipFree(h->d_boff);
         h->d_chunk_sys = nullptr;
         h->chunk_alloc = 0;
         HIP_TRY(hipMalloc(&h->d_chunk_sys, na * sizeof(int32_t)));
@@ -410,11 +430,10 @@ int relayout(fciqmc_t *h) {
         HIP_TRY(hipMalloc(&h->d_chunk_toff, na * sizeof(unsigned long long)));
         HIP_TRY(hipMalloc(&h->d_chunk_stat, na * POST_WAVES * sizeof(ChunkStat)));
         HIP_TRY(hipMalloc(&h->d_bhist, BPC * na * sizeof(uint32_t)));
-        HIP_TRY(hipMalloc(&h->d_boff, (BPC * na + 1) * sizeof(uint32_t)));
         h->chunk_alloc = na;
         drop_graphs(h);
     }
-    // record counts start at zero (the record scan keeps them so after every iteration)
+    // record counts start at zero (k_post keeps them so after every iteration)
     HIP_TRY(hipMemsetAsync(h->d_bhist, 0, BPC * h->chunk_alloc * sizeof(uint32_t), h->stream));
     std::vector<int32_t> cs(total), cl(total);
     int64_t g = 0;
@@ -446,7 +465,7 @@ int relayout(fciqmc_t *h) {
     HIP_TRY(hipMemcpyAsync(h->d_nchunks, &h->n_chunks, sizeof(int64_t), hipMemcpyHostToDevice,
                            h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
-    return 0;
+    return layout_records(h);
 }
 
 // The tile -> chunk map: room for every chunk's first tile and for twice the
@@ -799,6 +818,18 @@ int admit(fciqmc_t *h, int s, const fciqmc_hamiltonian *ham, const fciqmc_params
                 S.t3[((size_t)p * ns + a) * ns + q] = coul - exch;
             }
         }
+    {
+        double h1m = 0.0, em = 0.0;
+        for (int p = 0; p < S.M; ++p)
+            for (int q = 0; q < p; ++q) h1m = std::max(h1m, std::fabs(S.h1[(size_t)p * S.M + q]));
+        // (pa|qb) with p != a and q != b: the diagonal pairs p = a are the last of each row
+        std::vector<char> diag((size_t)np, 0);
+        for (int p = 0; p < S.M; ++p) diag[(size_t)p * (p + 1) / 2 + p] = 1;
+        for (int64_t i = 0, k = 0; i < np; ++i)
+            for (int64_t j = 0; j <= i; ++j, ++k)
+                if (!diag[i] && !diag[j]) em = std::max(em, std::fabs(S.eri[k]));
+        S.h_max = h1m + 2.0 * em;
+    }
     const int64_t cap = initial_capacity(prm);
     void *blk = nullptr;
     rc = alloc_tables(h, S, cap, &blk);
@@ -933,8 +964,10 @@ int load_list(fciqmc_t *h, int s, const std::vector<hdet_t> &det, const std::vec
     hipFree(dp);
     if (rc) return rc;
     S.growth = std::max<int64_t>(256, n / 8);
-    S.spawn_peak = 0;
     S.spawn_rate = 1.0;
+    S.rec_peak = 0;
+    S.pop_max = 0;
+    for (int32_t p : pop) S.pop_max = std::max<int64_t>(S.pop_max, p < 0 ? -(int64_t)p : p);
     return 0;
 }
 
@@ -1070,23 +1103,19 @@ int capture_or_get(fciqmc_t *h, int L, hipGraphExec_t *out) {
 
 // Before a launch of up to L iterations: re-bucket any main list whose buckets
 // would pass 5/8 full on average during the launch (each iteration adds at most
-// `growth` entries, the largest increase seen, with slack), size the spawn-record
-// buffer for the launch (the largest record count of the last launch growing at
-// the largest rate seen), and return how many iterations that headroom allows.
-// Whatever the estimates miss is caught on the device: an overflowing record
-// buffer abandons the iteration for a re-run, an overflowing bucket spills.
+// `growth` entries, the largest increase seen, with slack), size the record slots per
+// bucket for the launch (the fullest bucket of the last launch growing at the largest
+// rate seen), and return how many iterations that headroom allows. Whatever the
+// estimates miss is caught on the device: overflowing record slots abandon the
+// iteration for a re-run, an overflowing bucket of the main list spills.
 int plan_launch(fciqmc_t *h, int L, int *L_out) {
     int allowed = L;
-    int64_t rec_need = 0;
-    double rate = 1.0;
+    bool relaid = false;
     for (int s = 0; s < h->max_sys; ++s) {
         SysHost &S = h->sys[s];
         if (!S.active || S.fatal) continue;
         const SysDesc &d = h->hdesc[s];
         if (d.iter >= d.stop_at) continue;
-        // records of one iteration: at most one per attempt before anything is known
-        rec_need += S.spawn_peak > 0 ? S.spawn_peak : std::max<int64_t>(S.last.nw, 1);
-        rate = std::max(rate, S.spawn_rate);
         if (!h->planner) continue;   // overflows are left to the redo and spill paths
         const int64_t g = std::max<int64_t>(S.growth, 256);
         int64_t used = std::max<int64_t>(S.last.used, S.last.nd + 1);
@@ -1098,34 +1127,40 @@ int plan_launch(fciqmc_t *h, int L, int *L_out) {
         }
         const int64_t room = (S.cap * 5 / 8 - used) / g;
         allowed = (int)std::max<int64_t>(1, std::min<int64_t>(allowed, room));
-    }
-    if (h->planner && rec_need > 0) {
-        const int lg = std::min(allowed, 8);
-        const double grow = std::pow(rate, (double)lg);
-        const int64_t want = (int64_t)(1.5 * (double)rec_need * grow) + 65536;
-        if (want > h->rec_cap) {
-            const int rc = ensure_records(h, std::max<int64_t>(want, h->rec_cap + h->rec_cap / 2));
-            if (rc) return rc;
+        // Record slots per bucket: the fullest bucket of the last launch with half as much
+        // again, growing at the launch's largest rate. Before anything is known: one per
+        // walker, spread over the buckets, and what the list's largest population sends to
+        // one child, tau |H| |C| (a list that starts on the reference sends thousands to
+        // each of its few neighbours on a lattice; a re-run costs a system the rest of the
+        // launch). Given back when four times too many.
+        const int64_t nb = S.cap / BQ;
+        const double peak = S.rec_peak > 0 ? (double)S.rec_peak
+                                           : (double)std::max<int64_t>(S.last.nw, 1) / (double)nb +
+                                                 S.prm.tau * S.h_max * (double)S.pop_max;
+        const double grow = std::min(std::pow(S.spawn_rate, (double)std::min(allowed, 8)), 4.0);
+        const int64_t want = std::max(min_slots(h, nb), round_slots(1.5 * peak * grow + 16.0));
+        if (want > S.rec_r || 4 * want < S.rec_r) {
+            S.rec_r = want;
+            relaid = true;
         }
-        if (rate > 1.0) {
-            const double fit = std::log((double)h->rec_cap / (1.25 * (double)rec_need)) / std::log(rate);
+        if (S.spawn_rate > 1.0) {
+            const double fit = std::log((double)S.rec_r / (1.25 * peak)) / std::log(S.spawn_rate);
             allowed = (int)std::max<double>(1.0, std::min<double>((double)allowed, std::floor(fit)));
         }
     }
+    if (relaid) {
+        const int rc = layout_records(h);
+        if (rc) return rc;
+    }
     *L_out = allowed;
     return 0;
-}
-
-// Spawn records of iteration `it` of system s (from the host ring of records).
-int64_t rr_spawns(const fciqmc_t *h, int s, int64_t it) {
-    return h->h_rec[(int64_t)s * REC_CAP + it % REC_CAP].spawns;
 }
 
 // Launch L iterations (graph or direct), then read records and statuses. With
 // `sample` the last iteration runs as direct launches bracketed by events, which
 // gives the per-phase device times of one iteration on the graph path too.
 int run_iterations(fciqmc_t *h, int L, bool sample) {
-    bool grow_records = false;
+    std::vector<int> redo;
     std::vector<int> spilled;
     std::vector<int64_t> before(h->max_sys);
     for (int s = 0; s < h->max_sys; ++s) before[s] = h->hdesc[s].iter;
@@ -1193,29 +1228,26 @@ int run_iterations(fciqmc_t *h, int L, bool sample) {
                 }
                 S.last = r;
             }
-            // headroom estimates for the next launch: the largest growth of the entries
-            // and the largest record count of this one, with 25 % slack, and the largest
-            // ratio of consecutive record counts
+            // headroom estimates for the next launch: the largest growth of the entries in
+            // this one, with 25 % slack, its fullest bucket of records and the mean growth
+            // of the record count per iteration
             S.growth = std::max<int64_t>(256, seen + seen / 4);
-            int64_t peak = 0, prev = 0;
-            double rt = 1.0;
-            for (int64_t it = before[s] + 1; it <= d.iter; ++it) {
-                const int64_t sp = rr_spawns(h, s, it);
-                peak = std::max(peak, sp);
-                if (prev > 0) rt = std::max(rt, (double)sp / (double)prev);
-                prev = sp;
-            }
-            S.spawn_peak = peak + peak / 4;
-            S.spawn_rate = std::min(rt, 4.0);
+            S.rec_peak = 1;
+            for (int64_t it = before[s] + 1; it <= d.iter; ++it)
+                S.rec_peak = std::max(S.rec_peak, rr[it % REC_CAP].rec_max);
+            const int64_t sp0 = rr[(before[s] + 1) % REC_CAP].spawns, sp1 = S.last.spawns;
+            S.spawn_rate = 1.0;
+            if (n_new > 1 && sp0 > 0 && sp1 > sp0)
+                S.spawn_rate = std::min(std::pow((double)sp1 / (double)sp0, 1.0 / (double)(n_new - 1)), 4.0);
         }
         uint32_t &st = h->hstatus[s];
         if (st & ST_TABLE_FULL) {
-            // the record buffer overflowed: this iteration was abandoned and runs again
+            // a bucket's record slots overflowed: this iteration was abandoned and runs again
             st &= ~ST_TABLE_FULL;
             S.redos += 1;
             rc = reset_spawns(h, s);
             if (rc) return rc;
-            grow_records = true;
+            redo.push_back(s);
         }
         if (st & ST_SPILLED) {
             st &= ~ST_SPILLED;
@@ -1231,8 +1263,15 @@ int run_iterations(fciqmc_t *h, int L, bool sample) {
                                                        : " (population overflow)"));
         }
     }
-    if (grow_records) {
-        rc = ensure_records(h, 2 * h->rec_cap);
+    for (int s : redo) {
+        // the abandoned iteration counted its dropped records: slots for the fullest bucket
+        uint32_t most = 0;
+        HIP_TRY(hipMemcpyAsync(&most, h->d_rec_max + s, sizeof most, hipMemcpyDeviceToHost, h->stream));
+        HIP_TRY(hipMemsetAsync(h->d_rec_max + s, 0, sizeof most, h->stream));
+        HIP_TRY(hipStreamSynchronize(h->stream));
+        h->sys[s].rec_peak = most;
+        h->sys[s].rec_r = std::max(h->sys[s].rec_r + 8, round_slots(1.5 * (double)most + 16.0));
+        rc = layout_records(h);
         if (rc) return rc;
     }
     if (!spilled.empty()) {
@@ -1345,15 +1384,10 @@ int create_handle(int max_slots, void *stream, int W, fciqmc_t **out) {
     HIP_TRY(hipMalloc(&h->d_fin, sizeof(FinPart) * FIN_BLOCKS * max_slots));
     HIP_TRY(hipMalloc(&h->d_c0, sizeof(int64_t) * max_slots));
     HIP_TRY(hipMalloc(&h->d_err, sizeof(uint32_t)));
-    HIP_TRY(hipMalloc(&h->d_rec_count, sizeof(unsigned long long)));
-    HIP_TRY(hipMalloc(&h->d_boff_rg, 2 * SCAN_G * sizeof(unsigned long long)));
+    HIP_TRY(hipMalloc(&h->d_rec_max, sizeof(uint32_t) * max_slots));
+    HIP_TRY(hipMemsetAsync(h->d_rec_max, 0, sizeof(uint32_t) * max_slots, h->stream));
     HIP_TRY(hipMalloc(&h->d_d0acc, sizeof(long long) * max_slots));
     HIP_TRY(hipMemsetAsync(h->d_d0acc, 0, sizeof(long long) * max_slots, h->stream));
-    HIP_TRY(hipMemsetAsync(h->d_rec_count, 0, sizeof(unsigned long long), h->stream));
-    {
-        const int rc = ensure_records(h, 65536);
-        if (rc) return rc;
-    }
     h->sp_cap = SPILL_CAP;
     HIP_TRY(hipMalloc(&h->d_spill, (size_t)h->sp_cap * (16 + 8 * h->W)));
     HIP_TRY(hipMalloc(&h->d_sp_count, sizeof(unsigned long long)));
@@ -1410,6 +1444,7 @@ int admit_full(fciqmc_t *h, int s, const fciqmc_hamiltonian *ham, const fciqmc_p
     h->sys[s].last.c0 = n0;
     h->sys[s].last.shift = prm->initial_shift;
     if (prm->spawn_capacity > 0) {   // the record buffer is shared by the handle's systems
+        h->rec_floor = std::max(h->rec_floor, prm->spawn_capacity);
         rc = ensure_records(h, prm->spawn_capacity);
         if (rc) return rc;
     }
@@ -1442,10 +1477,8 @@ void release(fciqmc_t *h) {
     hipFree(h->d_chunk_stat);
     hipFree(h->d_tile_chunk);
     hipFree(h->d_recs);
-    hipFree(h->d_rec_count);
+    hipFree(h->d_rec_max);
     hipFree(h->d_bhist);
-    hipFree(h->d_boff);
-    hipFree(h->d_boff_rg);
     hipFree(h->d_d0acc);
     hipFree(h->d_spill);
     hipFree(h->d_sp_count);
@@ -1731,7 +1764,7 @@ struct SysSnapshot {
     std::vector<int32_t> pop;
     SysDesc desc{};
     IterRecord last{};
-    int64_t tot_att = 0, tot_sp = 0, redos = 0, spills = 0, growth = 0, spawn_peak = 0;
+    int64_t tot_att = 0, tot_sp = 0, redos = 0, spills = 0, growth = 0, rec_peak = 0;
     double spawn_rate = 1.0;
     Blocker e_blk, s_blk;
     std::vector<IterRecord> ring;
@@ -1757,7 +1790,7 @@ int take_snapshot(fciqmc_t *h, int s, SysSnapshot &o) {
     o.redos = S.redos;
     o.spills = S.spills;
     o.growth = S.growth;
-    o.spawn_peak = S.spawn_peak;
+    o.rec_peak = S.rec_peak;
     o.spawn_rate = S.spawn_rate;
     o.e_blk = S.e_blk;
     o.s_blk = S.s_blk;
@@ -1783,7 +1816,7 @@ int restore_snapshot(fciqmc_t *h, const SysSnapshot &o) {
     S.redos = o.redos;
     S.spills = o.spills;
     S.growth = o.growth;
-    S.spawn_peak = o.spawn_peak;
+    S.rec_peak = o.rec_peak;
     S.spawn_rate = o.spawn_rate;
     S.e_blk = o.e_blk;
     S.s_blk = o.s_blk;
@@ -1918,7 +1951,13 @@ int fciqmc_set_test_options(fciqmc_t *h, int32_t planner, int64_t tile_map_limit
         hipFree(h->d_recs);
         h->d_recs = nullptr;
         h->rec_cap = 0;
-        const int rc = ensure_records(h, record_capacity);
+        int rc = ensure_records(h, record_capacity);
+        if (rc) return rc;
+        // every bucket of the handle gets its share of them
+        for (SysHost &S : h->sys)
+            if (S.active)
+                S.rec_r = std::max<int64_t>(1, record_capacity / std::max<int64_t>(1, BPC * h->n_chunks));
+        rc = layout_records(h);
         if (rc) return rc;
     }
     if (tile_map_limit != h->tile_map_limit) {

@@ -6,7 +6,7 @@
 // distribution of determinants over processes by a hash (Sec. 4.1), with a
 // wavefront in the role of a process. Four consecutive buckets form a chunk,
 // the unit of attempt mapping. One iteration of every active system is
-// eleven launches (twelve in the first iteration of a launch sequence):
+// six launches (seven in the first iteration of a launch sequence):
 //
 //   k_chunk_sum   sum |C| over each bucket and over fixed contiguous ranges of
 //                 buckets (first iteration of a launch sequence only;
@@ -16,12 +16,8 @@
 //   k_spawn       one spawning attempt per walker (Sec. 2, Eq. pspawn): random
 //                 excitation with its pgen (Sec. 5), Slater-Condon element,
 //                 acceptance; each accepted spawn becomes a record (child,
-//                 signed walkers, initiator flag) addressed to the child's
+//                 signed walkers, initiator flag) in the slots of the child's
 //                 bucket -- the per-destination blocks of Sec. 4.1
-//   k_fix         bucket and rank of records left unranked by k_spawn (rare)
-//   k_bscan_*     exclusive scan of the records per bucket (range totals, their
-//                 scan, then the scan inside each range)
-//   k_scatter     the records grouped by bucket (a counting sort)
 //   k_post        per bucket, by one wavefront: the records merged per child in
 //                 an LDS hash (the sort and compress of Sec. 4.1); death/cloning
 //                 of every entry (Eq. pdeath); annihilation with the initiator
@@ -346,7 +342,6 @@ __device__ __forceinline__ rec_t get_rec(const rec_t *p) {
 #endif
 static_assert(sizeof(rec_t) == 16 * FQ_DET_WORDS, "record size");
 __device__ __forceinline__ rec_t *recs_of(const EngineArgs &a) { return (rec_t *)a.recs; }
-__device__ __forceinline__ rec_t *srt_of(const EngineArgs &a) { return (rec_t *)a.srt; }
 __device__ __forceinline__ det_t *spill_dets(const EngineArgs &a) { return (det_t *)a.sp_det; }
 
 __device__ __forceinline__ double eri_so(const SysDesc &d, int p, int q, int r, int s) {
@@ -1009,44 +1004,21 @@ __global__ __launch_bounds__(256) void k_scan_down(EngineArgs a) {
 // k+1 / next occupied slot.
 // ---------------------------------------------------------------------------
 
-// Spawn records. A record is (child, signed walkers, child's global bucket |
-// initiator flag << 31, rank among that bucket's records), appended to the
-// iteration's record buffer; the rank comes from the bucket's record counter. A
-// record that would land past the buffer's capacity is dropped and the system
-// marked: the iteration is then abandoned and re-run after the buffer grows.
+// A spawn record into its child's bucket's slots, at the place the bucket's counter
+// gives it. A record past the bucket's slots is dropped (still counted) and the system
+// marked: the iteration is then abandoned and re-run with more slots per bucket.
 // Walkers spawned onto the reference go to a per-system sum instead (every
 // iteration sends it many: the reference is the hot spot of Sec. 4.1).
-constexpr uint32_t REC_UNRANKED = 0x40000000u;
-__device__ __forceinline__ void put_record(const EngineArgs &a, const SysDesc &d, int s,
-                                           unsigned long long j, det_t D, int32_t v, bool init,
-                                           uint32_t *status) {
-    if (j >= (unsigned long long)a.rec_cap) {
+__device__ __forceinline__ void put_record(const EngineArgs &a, const SysDesc &d, det_t D,
+                                           int32_t v, bool init, uint32_t *status) {
+    const uint32_t b = bucket_of(D, (uint64_t)d.nbuckets);
+    const uint32_t k = __hip_atomic_fetch_add(&a.bhist[d.gchunk0 * BPC + b], 1u, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT);
+    if (k >= (uint32_t)d.rec_r) {
         atomicOr(status, ST_TABLE_FULL);
         return;
     }
-    const uint32_t gb = (uint32_t)(d.gchunk0 * BPC) + bucket_of(D, (uint64_t)d.nbuckets);
-    a.rec_rank[j] = __hip_atomic_fetch_add(&a.bhist[gb], 1u, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-    put_rec(recs_of(a) + j, D, v, gb | (init ? 0x80000000u : 0u));
-}
-
-// One record per active lane, with one buffer reservation for the wavefront
-// (callable from divergent code). Its bucket and rank are left to k_fix, which
-// keeps this path short in the spawning loop.
-__device__ __forceinline__ void put_record_wave(const EngineArgs &a, int s, det_t D, int32_t v,
-                                                bool init, uint32_t *status) {
-    const uint64_t m = __ballot(1);
-    const int lane = threadIdx.x & 63;
-    const int leader = __builtin_ctzll(m);
-    unsigned long long base = 0;
-    if (lane == leader) base = atomicAdd(a.rec_count, (unsigned long long)__popcll(m));
-    base = __shfl(base, leader, 64);
-    const unsigned long long j = base + (unsigned long long)__popcll(m & ((1ull << lane) - 1ull));
-    if (j >= (unsigned long long)a.rec_cap) {
-        atomicOr(status, ST_TABLE_FULL);
-        return;
-    }
-    put_rec(recs_of(a) + j, D, v, (uint32_t)s | REC_UNRANKED | (init ? 0x80000000u : 0u));
+    put_rec(recs_of(a) + d.rec0 + (int64_t)b * d.rec_r + k, D, v, init ? 1u : 0u);
 }
 
 // Work queued in LDS by the attempt loop and drained by the whole workgroup:
@@ -1093,7 +1065,6 @@ struct SpawnQueues {
     det_t spd[SPW_QUEUE];
     int2 spv[SPW_QUEUE];   // (signed walkers, initiator flag)
     int nsgl, nspw, sys;
-    unsigned long long base;   // first record of a drain
     uint32_t dead;             // the drained system's status, as seen by thread 0
 };
 
@@ -1155,17 +1126,14 @@ __device__ void drain_queues(SpawnQueues &Q, const EngineArgs &a, const SysDesc 
             Q.spd[qq] = Dn;
             Q.spv[qq] = make_int2(v, init ? 1 : 0);
         } else {
-            put_record_wave(a, s, Dn, v, init, status);
+            put_record(a, d, Dn, v, init, status);
         }
     }
     __syncthreads();
-    // the queued records: one buffer reservation for the workgroup
     const int nspw = dead ? 0 : (Q.nspw < SPW_QUEUE ? Q.nspw : SPW_QUEUE);
-    if (t == 0 && nspw > 0) Q.base = atomicAdd(a.rec_count, (unsigned long long)nspw);
-    __syncthreads();
     for (int j = t; j < nspw; j += blockDim.x) {
         const int2 v = Q.spv[j];
-        put_record(a, d, s, Q.base + (unsigned long long)j, Q.spd[j], v.x, v.y != 0, status);
+        put_record(a, d, Q.spd[j], v.x, v.y != 0, status);
     }
     __syncthreads();
     if (t == 0) {
@@ -1397,7 +1365,7 @@ void k_spawn(EngineArgs a, const SysDesc *__restrict__ desc) {
                                 Q.spd[q] = ex.det;
                                 Q.spv[q] = make_int2(v, init ? 1 : 0);
                             } else {
-                                put_record_wave(a, s, ex.det, v, init, status);
+                                put_record(a, d, ex.det, v, init, status);
                             }
                         }
                     }
@@ -1421,116 +1389,7 @@ void k_spawn(EngineArgs a, const SysDesc *__restrict__ desc) {
 }
 
 // ---------------------------------------------------------------------------
-// K4a: bucket and rank of the records the spawning loop left unranked (those
-// written while its queue was full; usually none).
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_fix(EngineArgs a, const SysDesc *__restrict__ desc) {
-    const unsigned long long cnt = *a.rec_count;
-    const int64_t n = cnt < (unsigned long long)a.rec_cap ? (int64_t)cnt : a.rec_cap;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const uint32_t gf = recs_of(a)[i].tag;
-        if (!(gf & REC_UNRANKED)) continue;
-        const SysDesc &d = desc[gf & 0x3FFFFFFFu];
-        const uint32_t gb = (uint32_t)(d.gchunk0 * BPC) + bucket_of(recs_of(a)[i].det, (uint64_t)d.nbuckets);
-        a.rec_rank[i] = __hip_atomic_fetch_add(&a.bhist[gb], 1u, __ATOMIC_RELAXED,
-                                               __HIP_MEMORY_SCOPE_AGENT);
-        recs_of(a)[i].tag = gb | (gf & 0x80000000u);
-    }
-}
-
-// ---------------------------------------------------------------------------
-// K4b: exclusive scan of the records per bucket (one workgroup; each thread
-// takes a contiguous range of buckets).
-// ---------------------------------------------------------------------------
-// Bucket b's range of the record scan: SCAN_G ranges of ceil(buckets / SCAN_G).
-__device__ __forceinline__ void bscan_range(int64_t nch, int g, int64_t &lo, int64_t &hi) {
-    const int64_t per = (nch + SCAN_G - 1) / SCAN_G;
-    lo = (int64_t)g * per;
-    hi = lo + per < nch ? lo + per : nch;
-    if (lo > nch) lo = nch;
-}
-
-// Records per range of buckets (coalesced: the workgroup reads its range in
-// consecutive blocks of 256).
-__global__ __launch_bounds__(256) void k_bscan_up(EngineArgs a) {
-    __shared__ unsigned long long ws[4];
-    int64_t lo, hi;
-    bscan_range(*a.nchunks * BPC, blockIdx.x, lo, hi);
-    unsigned long long v = 0;
-    for (int64_t i = lo + threadIdx.x; i < hi; i += 256) v += a.bhist[i];
-    v = wave_sum(v);
-    if ((threadIdx.x & 63) == 0) ws[threadIdx.x >> 6] = v;
-    __syncthreads();
-    if (threadIdx.x == 0) a.boff_rg[blockIdx.x] = ws[0] + ws[1] + ws[2] + ws[3];
-}
-
-// Exclusive scan of the SCAN_G range totals (one workgroup, two per thread).
-__global__ __launch_bounds__(1024) void k_bscan_top(EngineArgs a) {
-    __shared__ unsigned long long part[1024];
-    const int t = threadIdx.x;
-    const unsigned long long s0 = a.boff_rg[2 * t], s1 = a.boff_rg[2 * t + 1];
-    part[t] = s0 + s1;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        const unsigned long long x = t >= off ? part[t - off] : 0ull;
-        __syncthreads();
-        part[t] += x;
-        __syncthreads();
-    }
-    const unsigned long long run = part[t] - (s0 + s1);
-    a.boff_rg[SCAN_G + 2 * t] = run;
-    a.boff_rg[SCAN_G + 2 * t + 1] = run + s0;
-}
-
-// First sorted record of each bucket: the range's offset plus a scan inside the range.
-__global__ __launch_bounds__(256) void k_bscan_down(EngineArgs a) {
-    __shared__ unsigned long long ws[4];
-    int64_t lo, hi;
-    bscan_range(*a.nchunks * BPC, blockIdx.x, lo, hi);
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    unsigned long long base = a.boff_rg[SCAN_G + blockIdx.x];
-    for (int64_t c = lo; c < hi; c += 256) {
-        const int64_t i = c + t;
-        const unsigned long long v = i < hi ? a.bhist[i] : 0ull;
-        unsigned long long x = v;
-        for (int o = 1; o < 64; o <<= 1) {
-            const unsigned long long y = __shfl_up(x, o, 64);
-            if (lane >= o) x += y;
-        }
-        if (lane == 63) ws[w] = x;
-        __syncthreads();
-        unsigned long long pre = 0;
-        for (int k = 0; k < w; ++k) pre += ws[k];
-        if (i < hi) {
-            a.boff[i] = (uint32_t)(base + pre + x - v);
-            a.bhist[i] = 0u;   // counted afresh next iteration
-        }
-        base += ws[0] + ws[1] + ws[2] + ws[3];
-        __syncthreads();
-    }
-    // the end of the last bucket's records
-    if (threadIdx.x == 0 && hi == *a.nchunks * BPC && lo < hi) a.boff[hi] = (uint32_t)base;
-}
-
-// ---------------------------------------------------------------------------
-// K4c: the records grouped by bucket (order inside a bucket is immaterial:
-// every merge is an integer sum).
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_scatter(EngineArgs a) {
-    const unsigned long long cnt = *a.rec_count;
-    const int64_t n = cnt < (unsigned long long)a.rec_cap ? (int64_t)cnt : a.rec_cap;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const rec_t r = get_rec(recs_of(a) + i);
-        const uint32_t gb = r.tag & 0x7FFFFFFFu;
-        const uint32_t pos = a.boff[gb] + a.rec_rank[i];
-        put_rec(srt_of(a) + pos, r.det, r.w, r.tag >> 31);
-    }
-}
-
-// ---------------------------------------------------------------------------
-// K4d: annihilation. A workgroup takes windows of consecutive chunks from a shared
+// K4: annihilation. A workgroup takes windows of consecutive chunks from a shared
 // counter and, in each chunk, every wavefront one bucket, with no workgroup barrier
 // inside a bucket:
 //   - the bucket's records are merged per child in the wavefront's LDS hash
@@ -1542,9 +1401,9 @@ __global__ __launch_bounds__(256) void k_scatter(EngineArgs a) {
 //     (emptied positions first); the other children are discarded;
 //   - the bucket is re-packed; the estimator partials and the next iteration's
 //     sum of |C| are written.
-// A bucket with more than NREC records (rare at the planned sizes) merges them in
-// rounds of at most NREC distinct children, staging its new determinants in the
-// unsorted record buffer, which k_scatter has consumed by then.
+// A bucket with more than NREC records merges them in rounds of at most NREC distinct
+// children, staging each merged child outside the bucket in the slot of the record that
+// entered it into the hash.
 // ---------------------------------------------------------------------------
 constexpr int NREC = 64;                // distinct children per round in a wavefront's hash
 constexpr int WHASH = 128;              // hash slots per wavefront (load <= 0.5)
@@ -1552,12 +1411,14 @@ constexpr int POST_QUEUE = 1024;        // new determinants whose H_DD is still 
 constexpr int POST_FLUSH = 256;         // queued new determinants that are computed at once
 constexpr int POST_MAX_SYS = 256;       // systems whose status k_post snapshots in LDS
 constexpr int POST_WIN = 32;            // chunks per window of bucket metadata in LDS
-// the window's POST_WIN BPC + 1 record offsets are loaded by one thread each
-static_assert(POST_WIN * BPC + 1 <= 256, "one k_post thread per record offset of a window");
+// the window's POST_WIN BPC record counts are loaded by one thread each
+static_assert(POST_WIN * BPC <= 256, "one k_post thread per record count of a window");
 constexpr uint32_t F_INIT = 1u;         // from an initiator parent (records and hash slots)
 constexpr uint32_t F_MATCHED = 2u;      // hash slot: the child is an entry of the bucket
 constexpr uint32_t F_MAYBE = 2u;        // record: found the hash full in this round,
 constexpr uint32_t F_DEFER = 4u;        // record: left for a later round
+constexpr uint32_t F_STAGED = 8u;       // record: holds a merged child outside the bucket
+constexpr int OWN_SHIFT = 2;            // hash slot: the record that entered the child
 
 // Orders the LDS accesses of a wavefront's lanes around it (LDS operations of one
 // wavefront complete in issue order, so no wait is needed, only no code motion).
@@ -1582,7 +1443,7 @@ __device__ __forceinline__ uint32_t wh_home(det_t D) {
 struct WaveLds {
     det_t key[WHASH];          // child (one word: 0 when empty)
     long long acc[WHASH];      // walkers arrived for it
-    uint32_t flg[WHASH];       // F_INIT | F_MATCHED
+    uint32_t flg[WHASH];       // F_INIT | F_MATCHED, slow path: record << OWN_SHIFT
 #if FQ_DET_WORDS == 2
     uint32_t own[WHASH];       // 0: empty; else the lane that entered the child, + 1
 #endif
@@ -1624,8 +1485,9 @@ __device__ __forceinline__ int wh_claim(uint64_t D, uint64_t *hk, bool *own) {
 // As wh_claim, with at most NREC claims per round: *ncl counts claims made and
 // claims in flight. -1 when D is absent and no claim is left (D may have been
 // entered meanwhile by another lane, which a lookup afterwards settles).
-__device__ __forceinline__ int wh_claim_limited(uint64_t D, uint64_t *hk, int *ncl) {
+__device__ __forceinline__ int wh_claim_limited(uint64_t D, uint64_t *hk, int *ncl, bool *own) {
     uint32_t h = wh_home(D);
+    *own = false;
     for (int k = 0; k < WHASH; ++k) {
         const uint64_t x = hk[h];
         if (x == D) return (int)h;
@@ -1636,6 +1498,7 @@ __device__ __forceinline__ int wh_claim_limited(uint64_t D, uint64_t *hk, int *n
             }
             const unsigned long long old =
                 atomicCAS((unsigned long long *)&hk[h], 0ull, (unsigned long long)D);
+            *own = old == 0ull;
             if (old == 0ull) return (int)h;
             atomicSub(ncl, 1);   // the slot went to another lane's claim
             if (old == D) return (int)h;
@@ -1649,8 +1512,8 @@ __device__ __forceinline__ int wl_find(det_t D, const WaveLds &W) { return wh_fi
 __device__ __forceinline__ int wl_claim(det_t D, WaveLds &W, bool *own, int) {
     return wh_claim(D, W.key, own);
 }
-__device__ __forceinline__ int wl_claim_limited(det_t D, WaveLds &W, int *ncl, int) {
-    return wh_claim_limited(D, W.key, ncl);
+__device__ __forceinline__ int wl_claim_limited(det_t D, WaveLds &W, int *ncl, bool *own, int) {
+    return wh_claim_limited(D, W.key, ncl, own);
 }
 __device__ __forceinline__ bool wl_used(const WaveLds &W, int h) { return W.key[h] != 0ull; }
 __device__ __forceinline__ void wl_clear(WaveLds &W, int h) { W.key[h] = 0ull; }
@@ -1686,8 +1549,10 @@ __device__ __forceinline__ int wl_claim(det_t D, WaveLds &W, bool *own, int lane
         h = (h + 1u) & (uint32_t)(WHASH - 1);
     }
 }
-__device__ __forceinline__ int wl_claim_limited(det_t D, WaveLds &W, int *ncl, int lane) {
+__device__ __forceinline__ int wl_claim_limited(det_t D, WaveLds &W, int *ncl, bool *own,
+                                                int lane) {
     uint32_t h = wh_home(D);
+    *own = false;
     for (int k = 0; k < WHASH; ++k) {
         bool won = false, full = false;
         if (W.own[h] == 0u) {
@@ -1701,6 +1566,7 @@ __device__ __forceinline__ int wl_claim_limited(det_t D, WaveLds &W, int *ncl, i
         }
         if (won) W.key[h] = D;
         wave_sync();
+        *own = won;
         if (won) return (int)h;
         if (full) return -1;
         if (W.key[h] == D) return (int)h;
@@ -1846,7 +1712,7 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
     __shared__ int s_cloc[POST_WIN];                 // chunk index inside its system's table
     __shared__ uint8_t s_cnext[POST_WIN];            // its walkers spawn next iteration
     __shared__ int16_t s_bn[POST_WIN * BPC];         // entries per bucket
-    __shared__ uint32_t s_boff[POST_WIN * BPC + 1];  // first sorted record per bucket, and the end
+    __shared__ uint32_t s_nr[POST_WIN * BPC];        // records per bucket
     __shared__ unsigned long long s_cnws[POST_WIN];  // the chunk's sum of |C| after the iteration
     __shared__ int s_cdone[POST_WIN];                // wavefronts done with the chunk
     __shared__ int s_qn, s_qsys;
@@ -1856,7 +1722,6 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
     const int64_t nch = *a.nchunks;
     const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
     WaveLds &W = L.w[wid];
-    if (blockIdx.x == 0 && t == 0) *a.rec_count = 0ull;   // k_scatter has consumed the records
     unsigned long long *const nws_next = sums(a, cur_half(a) ^ 1u);
     unsigned long long *const rg_next = ranges(a, cur_half(a) ^ 1u);
     const int64_t per_range = (nch + SCAN_G - 1) / SCAN_G;
@@ -1925,7 +1790,16 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
             s_cnws[t] = 0ull;
             s_cdone[t] = 0;
         }
-        if (t <= nwin * BPC) s_boff[t] = a.boff[c0 * BPC + t];
+        uint32_t nrec = 0;
+        if (t < nwin * BPC) {
+            nrec = a.bhist[c0 * BPC + t];
+            if (nrec) a.bhist[c0 * BPC + t] = 0u;   // counted afresh next iteration
+            s_nr[t] = nrec;
+            // the fullest bucket, from which the host plans the slots (of an abandoned
+            // iteration too: its dropped records were counted)
+            const int sr = nrec ? a.chunk_sys[c0 + t / BPC] : -1;
+            if (sr >= 0 && nrec > a.rec_max[sr]) atomicMax(&a.rec_max[sr], nrec);
+        }
         __syncthreads();
         if (t < nwin * BPC) {
             const int sc = s_csys[t / BPC];
@@ -1952,8 +1826,8 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                 const int64_t lb = (int64_t)s_cloc[ci] * BPC + wid;
                 const int64_t base = lb * BQ;
                 const int n = s_bn[ci * BPC + wid];
-                const uint32_t r0 = s_boff[ci * BPC + wid];
-                const uint32_t nr = s_boff[ci * BPC + wid + 1] - r0;
+                const uint32_t nr = s_nr[ci * BPC + wid];
+                rec_t *const seg = recs_of(a) + d.rec0 + lb * d.rec_r;   // the bucket's records
                 // the H_DD queue serves one system at a time: the first to use it in a window
                 if (lane == 0 && s_qsys < 0) atomicCAS(&s_qsys, -1, s);
                 // entry u * 64 + lane is this lane's u-th; R rounds cover the n entries
@@ -1976,7 +1850,7 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                 int rh = 0;
                 bool rown = false;
                 if ((uint32_t)lane < nr && nr <= (uint32_t)NREC) {
-                    const rec_t r = get_rec(srt_of(a) + r0 + lane);
+                    const rec_t r = get_rec(seg + lane);
                     rd = r.det;
                     rw = r.w;
                     rf = r.tag;
@@ -2013,7 +1887,6 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                 wave_sync();
                 long long spv[4] = {0ll, 0ll, 0ll, 0ll};   // walkers arrived per entry
                 uint32_t flv = 0u;                         // bit u: an initiator sent some
-                int kc = 0;                                // slow path: staged children (uniform)
                 if (nr <= (uint32_t)NREC) {
                     // Fast path: at most NREC records, so at most NREC distinct children.
                     if ((uint32_t)lane < nr) {
@@ -2038,8 +1911,8 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                 } else {
                     // Slow path: rounds of at most NREC distinct children. A child whose
                     // records found the hash full is left whole for a later round; the
-                    // children outside the bucket are staged, merged, in the bucket's range
-                    // of the unsorted record buffer.
+                    // children outside the bucket are staged, merged, in the slots of the
+                    // records that entered them.
                     for (int round = 0;; ++round) {
                         if (round > 0) {
                             wl_clear(W, lane);
@@ -2053,38 +1926,36 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                         wave_sync();
                         bool maybe = false;
                         for (uint32_t j = lane; j < nr; j += 64) {   // (a record stays with its lane)
-                            rec_t *const srt = srt_of(a);
-                            const uint32_t f = srt[r0 + j].tag;
-                            if (round > 0 && !(f & F_DEFER)) continue;
-                            const det_t D = srt[r0 + j].det;
-                            const int h = wl_claim_limited(D, W, &s_ncl[wid], lane);
+                            const rec_t r = get_rec(seg + j);
+                            if (round > 0 && !(r.tag & F_DEFER)) continue;
+                            bool own;
+                            const int h = wl_claim_limited(r.det, W, &s_ncl[wid], &own, lane);
                             if (h < 0) {
-                                srt[r0 + j].tag = (f & F_INIT) | F_MAYBE;
+                                seg[j].tag = (r.tag & F_INIT) | F_MAYBE;
                                 maybe = true;
                                 continue;
                             }
-                            if (f & F_DEFER) srt[r0 + j].tag = f & F_INIT;
-                            atomicAdd((unsigned long long *)&W.acc[h],
-                                      (unsigned long long)(long long)srt[r0 + j].w);
-                            if (f & F_INIT) atomicOr(&W.flg[h], F_INIT);
+                            if (r.tag & F_DEFER) seg[j].tag = r.tag & F_INIT;
+                            atomicAdd((unsigned long long *)&W.acc[h], (unsigned long long)(long long)r.w);
+                            const uint32_t f = (r.tag & F_INIT) | (own ? j << OWN_SHIFT : 0u);
+                            if (f) atomicOr(&W.flg[h], f);
                         }
                         wave_sync();
                         bool defer = false;
                         if (__ballot(maybe)) {
                             for (uint32_t j = lane; j < nr; j += 64) {
-                                rec_t *const srt = srt_of(a);
-                                const uint32_t f = srt[r0 + j].tag;
-                                if (!(f & F_MAYBE)) continue;
-                                const int h = wl_find(srt[r0 + j].det, W);
+                                const rec_t r = get_rec(seg + j);
+                                if (!(r.tag & F_MAYBE)) continue;
+                                const int h = wl_find(r.det, W);
                                 if (h < 0) {
-                                    srt[r0 + j].tag = (f & F_INIT) | F_DEFER;
+                                    seg[j].tag = (r.tag & F_INIT) | F_DEFER;
                                     defer = true;
                                     continue;
                                 }
-                                srt[r0 + j].tag = f & F_INIT;
+                                seg[j].tag = r.tag & F_INIT;
                                 atomicAdd((unsigned long long *)&W.acc[h],
-                                          (unsigned long long)(long long)srt[r0 + j].w);
-                                if (f & F_INIT) atomicOr(&W.flg[h], F_INIT);
+                                          (unsigned long long)(long long)r.w);
+                                if (r.tag & F_INIT) atomicOr(&W.flg[h], F_INIT);
                             }
                             wave_sync();
                         }
@@ -2101,19 +1972,14 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                         wave_sync();
                         // stage this round's children outside the bucket (one per slot)
                         for (int h = lane; h < WHASH; h += 64) {
-                            const det_t D = W.key[h];
-                            const bool cand = wl_used(W, h) && !(W.flg[h] & F_MATCHED);
-                            const uint64_t m = __ballot(cand);
-                            if (cand) {
-                                const uint32_t j = r0 + (uint32_t)kc + (uint32_t)__popcll(m & lanes_below(lane));
-                                long long sp = W.acc[h];
-                                if (sp > 2147483647ll || sp < -2147483647ll) {
-                                    atomicOr(status, ST_POP_OVERFLOW);
-                                    sp = 0;
-                                }
-                                put_rec(recs_of(a) + j, D, (int32_t)sp, W.flg[h] & F_INIT);
+                            const uint32_t f = W.flg[h];
+                            if (!wl_used(W, h) || (f & F_MATCHED)) continue;
+                            long long sp = W.acc[h];
+                            if (sp > 2147483647ll || sp < -2147483647ll) {
+                                atomicOr(status, ST_POP_OVERFLOW);
+                                sp = 0;
                             }
-                            kc += __popcll(m);
+                            put_rec(seg + (f >> OWN_SHIFT), W.key[h], (int32_t)sp, (f & F_INIT) | F_STAGED);
                         }
                         wave_sync();
                         if (!__ballot(defer)) break;
@@ -2231,12 +2097,11 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                         place(cand ? rd : det_t(0ull), rsp, (f & F_INIT) != 0u);
                     }
                 } else {
-                    for (int i0 = 0; i0 < kc; i0 += 64) {
-                        const int i = i0 + lane;
-                        const bool in = i < kc;
-                        const rec_t *const st = recs_of(a);
-                        place(in ? st[r0 + i].det : det_t(0ull), in ? (long long)st[r0 + i].w : 0ll,
-                              in && (st[r0 + i].tag & F_INIT));
+                    for (uint32_t i0 = 0; i0 < nr; i0 += 64) {
+                        const uint32_t i = i0 + lane;
+                        const bool in = i < nr && (seg[i].tag & F_STAGED);
+                        place(in ? seg[i].det : det_t(0ull), in ? (long long)seg[i].w : 0ll,
+                              in && (seg[i].tag & F_INIT));
                     }
                 }
                 // Re-pack: n' = (kept entries) + (new determinants); when fewer new
@@ -2278,12 +2143,10 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                 if (nr <= (uint32_t)NREC) {
                     if (nearn & 1u) num = num + ref_hel(d, rd) * (double)rsp;
                 } else {
-                    for (int i = lane; i < kc; i += 64) {
-                        const rec_t *const st = recs_of(a);
-                        const det_t D = st[r0 + i].det;
-                        const int32_t sp = st[r0 + i].w;
-                        if (sp != 0 && (st[r0 + i].tag & F_INIT) && near_ref(d, D))
-                            num = num + ref_hel(d, D) * (double)sp;
+                    for (uint32_t i = lane; i < nr; i += 64) {
+                        const rec_t r = get_rec(seg + i);
+                        if ((r.tag & F_STAGED) && r.w != 0 && (r.tag & F_INIT) && near_ref(d, r.det))
+                            num = num + ref_hel(d, r.det) * (double)r.w;
                     }
                 }
             }
@@ -2420,6 +2283,8 @@ __global__ __launch_bounds__(64) void k_finalize(EngineArgs a) {
         r.used = used;
         r.n_var = d.n_var;
         r.n_prev = d.n_prev;
+        r.rec_max = (int64_t)a.rec_max[s];
+        a.rec_max[s] = 0u;
         r.num = num;
         r.shift = d.shift;
         r.varying = d.varying;
@@ -2456,12 +2321,6 @@ void launch_iteration(const EngineArgs &a, int post_grid, int spawn_grid, bool f
         hipLaunchKernelGGL(k_spawn<false>, dim3((unsigned)spawn_grid), dim3(256), 0, s, a,
                            (const SysDesc *)a.desc);
     if (ev) (void)hipEventRecord(ev[3], s);
-    hipLaunchKernelGGL(k_fix, dim3((unsigned)spawn_grid), dim3(256), 0, s, a,
-                       (const SysDesc *)a.desc);
-    hipLaunchKernelGGL(k_bscan_up, dim3(SCAN_G), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_bscan_top, dim3(1), dim3(1024), 0, s, a);
-    hipLaunchKernelGGL(k_bscan_down, dim3(SCAN_G), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(k_scatter, dim3((unsigned)spawn_grid), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_post, dim3((unsigned)post_grid), dim3(256), 0, s, a,
                        (const SysDesc *)a.desc);
     if (ev) (void)hipEventRecord(ev[4], s);
