@@ -14,8 +14,21 @@ constexpr int BUCKET_FILL = 128;     // planned mean entries per bucket (half fu
 constexpr int NCLASS = 16;           // symmetry classes: 2 spins x up to 8 abelian irreps
 constexpr int REC_CAP = 256;         // per-system ring of per-iteration records
 constexpr int MAX_GRAPH_ITERS = 64;  // iterations captured in one graph launch
-constexpr int SCAN_G = 2048;         // workgroups of the chunk-sum and scan-down kernels; each
-                                     // takes one contiguous range of chunks
+// Lists of work (spawn tiles, windows of chunks) with a counter each, and where the
+// counters lie: each on a 128-byte line of its own. Tiles: three sets of lists (even and
+// odd steps, a launch's first), and per set the buckets whose tiles were not listed.
+constexpr int NLIST = 32;
+constexpr int CTR_STRIDE = 32;                                    // unsigned ints
+constexpr int CTR_SPAWN(int l) { return l * CTR_STRIDE; }
+constexpr int CTR_POST(int l) { return (NLIST + l) * CTR_STRIDE; }
+constexpr int CTR_FALLBACK = 2 * NLIST * CTR_STRIDE;
+constexpr int N_WORK = CTR_FALLBACK + CTR_STRIDE;
+constexpr int CTR_TILES(int h, int l) { return (h * NLIST + l) * (CTR_STRIDE / 2); }
+constexpr int CTR_UNLISTED(int h) { return (3 * NLIST + h) * (CTR_STRIDE / 2); }
+constexpr int N_TOTAL = CTR_UNLISTED(3);
+constexpr int TILE_MAX_SH(int W) { return W == 1 ? 9 : 8; }   // log2 of a wavefront's largest
+                                     // spawn tile (W words per determinant)
+constexpr int SPAWN_SLOTS = 16;      // shares of a system's spawning-event counter
 constexpr int FIN_BLOCKS = 64;       // workgroups per system reducing the chunk statistics
 
 // Status bits set on the device.
@@ -57,7 +70,7 @@ constexpr uint64_t CNT_FIELD = (1ull << 21) - 1;
 
 // One workgroup's share of a system's iteration statistics.
 struct FinPart {
-    int64_t nw, nd, merged, aborted, used, attempts, born;
+    int64_t nw, nd, merged, aborted, used, born;
     double num;
 };
 
@@ -83,6 +96,17 @@ struct SysDesc {
     const double *h1, *eri;
     const double *jk;                // [n_so][64]: (pp|qq) - (pq|qp) for p < q, spin orbitals
     const double *t3;                // [n_so][64][64]: (pa|qq) - d(s_p,s_q)(pq|qa), same-spin p, a
+    // Rejection bounds of the spawning kernel, over spatial orbital pairs [32 W][32 W] in
+    // half precision, rounded up, relative to their largest. With mostly double
+    // excitations (p_double >= 1/2): s with |(pa|qb)| <= s_pa s_qb. Otherwise: the largest
+    // |<D'|H|D>| of a single excitation p -> a.
+    const uint16_t *bound;
+    // A double with type word w0 is rejected when (float)w0 > bound x bound_f[pgen index]
+    // (no point group) or (float)w0 pgen > bound x bound_ft; a single of nt choices when
+    // (float)w0 sg_mul - sg_sub (its uniform, rounded down) > bound x nt x bound_ft.
+    float bound_f[4], bound_ft, sg_mul, sg_sub;
+    uint32_t dbl_thr;                // w0 <= dbl_thr: a double excitation (U < P_double)
+    int32_t has_double, defer;       // P_double > 0; single excitations are rare (>= 1/2)
     // Main list: nb buckets of BQ entries (structure of arrays); a determinant lives
     // in bucket floor(mix64(D) nb / 2^64), the entries of bucket b are the first
     // bcnt[b] of [b BQ, (b+1) BQ), every one occupied (the reference may sit at 0).
@@ -108,6 +132,7 @@ struct SysDesc {
     double shift;
     int32_t varying, pad3;
     int64_t n_prev, n_var;
+    int64_t nw;                      // walkers, i.e. the next iteration's attempts
     // --- set by the host: determinants of more than 64 spin orbitals (two words,
     // Sec. 3): the high words of d0, valid, cmask, frz_occ and frz_emp, and the irreps
     // of spatial orbitals 32-63 (4 bits each); det_words = 1 or 2 selects the width.
@@ -129,28 +154,22 @@ struct __attribute__((aligned(16))) SpawnRec {
 struct EngineArgs {
     SysDesc *desc;
     int32_t max_sys;
-    int32_t tile;                    // attempts per spawn-kernel tile
-    unsigned int *work;              // [0] next spawn tile, [1] next post chunk (reset per iteration)
+    int32_t wsh;                     // log2 of a spawn tile's attempts
+    unsigned int *work;              // [N_WORK] shares taken of each list (reset per iteration)
     uint32_t *status;                // per system: ST_* bits (kept apart from the read-only
-    unsigned long long *spawns;      // descriptors) and spawning events of the iteration
+    unsigned long long *spawns;      // descriptors); [SPAWN_SLOTS] spawning events each
     const int32_t *chunk_sys;        // system of each global chunk (-1: unused)
     const int32_t *chunk_local;      // chunk index inside its system's table
-    unsigned long long *chunk_nw;    // [2][chunk_cap] sum |C| per chunk: this iteration's
-                                     // attempts in half (step & 1), the next one's in the other
-    int64_t chunk_cap;
-    unsigned long long *step;        // iterations run by this handle (selects the halves)
-    unsigned long long *chunk_off;   // exclusive scan of chunk_nw
-    unsigned long long *chunk_toff;  // exclusive scan of the spawn tiles of each chunk
+    unsigned long long *step;        // iterations run by this handle (its parity selects total)
     ChunkStat *chunk_stat;           // [chunks][POST_WAVES]
-    unsigned long long *blk;         // [2][4][SCAN_G]: per chunk range sum |C|, tiles, and
-                                     // their exclusive scans, halves selected like chunk_nw
     FinPart *fin_part;               // [max_sys][FIN_BLOCKS]
     int64_t *c0;                     // [max_sys] population on the reference after the iteration
-    unsigned long long *total;       // [0] total attempts, [1] total spawn tiles
+    unsigned long long *total;       // [N_TOTAL] lengths of the lists of spawn tiles
     const int64_t *nchunks;          // global chunks in use
     IterRecord *rec;                 // [max_sys][REC_CAP]
-    uint32_t *tile_chunk;            // [tile_cap] chunk of each spawn tile (k_scan_down); tiles
-    int64_t tile_cap;                // beyond the capacity are found by search
+    int32_t *tiles;                  // [NLIST][list_cap][4] the spawn tiles (see put_tile)
+    int64_t list_cap;
+    uint32_t *unlisted;              // [BPC chunk_cap] buckets whose tiles did not fit a list
     // Spawn records of the iteration (the per-destination blocks of Sec. 4.1, with the
     // bucket as destination): k_spawn writes a record straight into its child's bucket's
     // slots (SysDesc::rec0, rec_r), at the place the bucket's counter gives it. Writing
@@ -188,8 +207,8 @@ constexpr size_t NOALLOC_BYTES = NOALLOC_FLAGS_OFF + 4 * (size_t)NOALLOC_MAX_DET
 constexpr int NKERN = 5;   // profiled kernel groups: chunk sums, scans, spawn, annihilation
                            // (record sort + death/annihilation pass), statistics/shift
 #define FQ_WIDTH_LAUNCHERS                                                                     \
-    /* first: the chunk sums are taken from the tables (the first iteration of a launch,     \
-       after any host-side change); later iterations use the sums the previous iteration's   \
+    /* first: the spawn tiles are listed from the tables (the first iteration of a launch,    \
+       after any host-side change); later iterations use the list the previous iteration's    \
        k_post wrote. */                                                                       \
     void launch_iteration(const EngineArgs &a, int post_grid, int spawn_grid, bool first,      \
                           hipStream_t s, hipEvent_t *ev /* NKERN + 1 events or nullptr */);     \
@@ -221,7 +240,7 @@ hipError_t launch_stage_compact(const uint64_t *key, const int32_t *pop, const i
 hipError_t launch_stage_sort(void *stage, int64_t n, hipStream_t s);
 // Initiator flag of each of the n sorted entries: |pop| > n_a, or the reference.
 hipError_t launch_stage_flags(void *stage, int64_t n, int32_t n_a, uint64_t d0, hipStream_t s);
-int spawn_grid_size();
+int spawn_grid_size(int W);
 int post_grid_size();
 
 }  // namespace fq

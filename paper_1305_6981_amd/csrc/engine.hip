@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -210,6 +211,8 @@ struct SysHost {
     std::vector<double> jk;    // [n_so][64 W] pair table
     std::vector<double> t3;    // [n_so][64 W][64 W] single-excitation term table
     double *d_t3 = nullptr;
+    std::vector<uint16_t> bound;   // [32 W][32 W] rejection bounds (SysDesc::bound)
+    uint16_t *d_bound = nullptr;
     int64_t growth = 0;        // expected per-iteration increase of the entries
     double spawn_rate = 1.0;   // mean growth of the records per iteration in the last launch
     int64_t rec_r = 0;         // record slots per bucket
@@ -247,10 +250,10 @@ struct fciqmc_t {
     // global chunk layout
     int64_t chunk_alloc = 0, n_chunks = 0;
     int32_t *d_chunk_sys = nullptr, *d_chunk_local = nullptr;
-    unsigned long long *d_chunk_nw = nullptr, *d_chunk_off = nullptr, *d_total = nullptr;
-    unsigned long long *d_chunk_toff = nullptr;
+    unsigned long long *d_total = nullptr;  // lengths of the tile lists
+    uint32_t *d_unlisted = nullptr;         // buckets whose tiles did not fit
     ChunkStat *d_chunk_stat = nullptr;
-    uint32_t *d_tile_chunk = nullptr;       // chunk of each spawn tile
+    int32_t *d_tiles = nullptr;             // the spawn tiles, 16 B each
     bool tile_map_off = false;              // its allocation failed once: search instead
     void *d_stage = nullptr;                // this device's staging area (not owned)
     // spawn records (see EngineArgs) and the spill list
@@ -264,8 +267,7 @@ struct fciqmc_t {
     unsigned long long *d_sp_count = nullptr;
     uint32_t *d_spilled = nullptr;
     int64_t tile_cap = 0;
-    unsigned long long *d_blk = nullptr;    // [2][4][SCAN_G] range sums and scans
-    unsigned long long *d_step = nullptr;   // iterations run (selects the halves of the sums)
+    unsigned long long *d_step = nullptr;   // iterations run (its parity selects d_total)
     FinPart *d_fin = nullptr;               // [max_sys][FIN_BLOCKS]
     int64_t *d_c0 = nullptr;                // [max_sys]
     int64_t *d_nchunks = nullptr;
@@ -273,7 +275,8 @@ struct fciqmc_t {
     int spawn_grid = 2048;
     int post_grid = 1024;
     int tile = 2048;
-    std::map<int, hipGraphExec_t> graphs;   // by 2 L + plain (L iterations, kernel variant)
+    bool shape_set = false;                 // the launch shape was set or tuned: used as it is
+    std::map<std::array<int, 5>, hipGraphExec_t> graphs;   // by iterations, kernel variant, shape
     bool use_graph = true;
     bool profiling = false;
     hipEvent_t ev[NKERN + 1] = {};
@@ -298,24 +301,19 @@ EngineArgs make_args(fciqmc_t *h) {
     a.max_sys = h->max_sys;
     a.chunk_sys = h->d_chunk_sys;
     a.chunk_local = h->d_chunk_local;
-    a.chunk_nw = h->d_chunk_nw;
-    a.chunk_cap = h->chunk_alloc;
     a.step = h->d_step;
-    a.chunk_off = h->d_chunk_off;
-    a.chunk_toff = h->d_chunk_toff;
     a.chunk_stat = h->d_chunk_stat;
-    a.blk = h->d_blk;
     a.fin_part = h->d_fin;
     a.c0 = h->d_c0;
     a.total = h->d_total;
     a.nchunks = h->d_nchunks;
     a.rec = h->d_rec;
-    a.tile = h->tile;
     a.status = h->d_status;
     a.spawns = h->d_spawns;
     a.work = h->d_work;
-    a.tile_chunk = h->d_tile_chunk;
-    a.tile_cap = h->tile_cap;
+    a.tiles = h->d_tiles;
+    a.list_cap = h->tile_cap / NLIST;
+    a.unlisted = h->d_unlisted;
     a.recs = (SpawnRec *)h->d_recs;
     a.bhist = h->d_bhist;
     a.rec_max = h->d_rec_max;
@@ -336,6 +334,31 @@ EngineArgs make_args(fciqmc_t *h) {
         if (h->sys[s].active && (d.n_class != 2 || d.hphf || d.space)) a.plain = 0;
     }
     return a;
+}
+
+// The launch shape of the next iterations: log2 of a wavefront's spawn tile, workgroups
+// of k_spawn and of k_post. A shape set by the caller or tuned is used as it is (a
+// workgroup's tile in four, one part per wavefront, of at most 512 attempts). By default a launch too small to
+// give every wavefront of the chip a tile gets smaller tiles, down to one attempt per
+// lane, and no more workgroups than there are tiles and chunks: a walk of few attempts
+// is all latency (a tile's staging and its lanes' runs of attempts one after another),
+// and idle workgroups still cost their start. Powers of two, so that a growing list
+// meets few shapes (each is captured once).
+struct Shape {
+    int wsh, spawn_grid, post_grid;
+};
+Shape launch_shape(const fciqmc_t *h) {
+    Shape o{std::clamp((int)std::log2((double)h->tile) - 2, 6, TILE_MAX_SH(h->W)), h->spawn_grid, h->post_grid};
+    if (h->shape_set) return o;
+    int64_t walkers = 0;
+    for (int s = 0; s < h->max_sys; ++s)
+        if (h->sys[s].active && !h->sys[s].fatal) walkers += std::max<int64_t>(h->sys[s].last.nw, 0);
+    const int64_t waves = 4 * (int64_t)h->spawn_grid;
+    while (o.wsh > 6 && (walkers >> o.wsh) < waves) --o.wsh;
+    const int64_t tiles = std::min<int64_t>(BPC * h->n_chunks, walkers) + (walkers >> o.wsh);
+    o.spawn_grid = (int)std::min<int64_t>(o.spawn_grid, next_pow2(std::max<int64_t>(1, (tiles + 3) / 4)));
+    o.post_grid = (int)std::min<int64_t>(o.post_grid, next_pow2(std::max<int64_t>(1, h->n_chunks)));
+    return o;
 }
 
 // The spawn-record buffer for `cap` records (16 W B each).
@@ -402,7 +425,8 @@ int download_desc(fciqmc_t *h) {
 // Clear what spawning accumulates for system s outside the records (its event
 // count and its walkers onto the reference): after an abandoned iteration or a load.
 int reset_spawns(fciqmc_t *h, int s) {
-    HIP_TRY(hipMemsetAsync(h->d_spawns + s, 0, sizeof(unsigned long long), h->stream));
+    HIP_TRY(hipMemsetAsync(h->d_spawns + (int64_t)s * SPAWN_SLOTS, 0,
+                           SPAWN_SLOTS * sizeof(unsigned long long), h->stream));
     HIP_TRY(hipMemsetAsync(h->d_d0acc + s, 0, sizeof(long long), h->stream));
     return 0;
 }
@@ -416,18 +440,14 @@ int relayout(fciqmc_t *h) {
         int64_t na = next_pow2(std::max<int64_t>(total, 64));
         hipFree(h->d_chunk_sys);
         hipFree(h->d_chunk_local);
-        hipFree(h->d_chunk_nw);
-        hipFree(h->d_chunk_off);
-        hipFree(h->d_chunk_toff);
+        hipFree(h->d_unlisted);
         hipFree(h->d_chunk_stat);
         hipFree(h->d_bhist);
         h->d_chunk_sys = nullptr;
         h->chunk_alloc = 0;
         HIP_TRY(hipMalloc(&h->d_chunk_sys, na * sizeof(int32_t)));
         HIP_TRY(hipMalloc(&h->d_chunk_local, na * sizeof(int32_t)));
-        HIP_TRY(hipMalloc(&h->d_chunk_nw, 2 * na * sizeof(unsigned long long)));
-        HIP_TRY(hipMalloc(&h->d_chunk_off, na * sizeof(unsigned long long)));
-        HIP_TRY(hipMalloc(&h->d_chunk_toff, na * sizeof(unsigned long long)));
+        HIP_TRY(hipMalloc(&h->d_unlisted, BPC * na * sizeof(uint32_t)));
         HIP_TRY(hipMalloc(&h->d_chunk_stat, na * POST_WAVES * sizeof(ChunkStat)));
         HIP_TRY(hipMalloc(&h->d_bhist, BPC * na * sizeof(uint32_t)));
         h->chunk_alloc = na;
@@ -468,26 +488,27 @@ int relayout(fciqmc_t *h) {
     return layout_records(h);
 }
 
-// The tile -> chunk map: room for every chunk's first tile and for twice the
-// walkers of the last iteration in whole tiles, grown by doubling (a graph holds
-// the pointer, so growing drops the graphs). Tiles beyond it are found by search.
+// The lists of spawn tiles: room in all for two tiles per bucket and for four times the
+// walkers of the last iteration in whole tiles (the lists fill unevenly), grown by
+// doubling (a graph holds the pointer, so growing drops the graphs). Buckets whose tiles
+// do not fit are taken whole from a list of their own.
 int ensure_tile_map(fciqmc_t *h) {
     int64_t walkers = 0;
     for (int s = 0; s < h->max_sys; ++s)
         if (h->sys[s].active) walkers += std::max<int64_t>(h->sys[s].last.nw, 0);
-    int64_t want = h->n_chunks + 2 * walkers / std::max(h->tile, 1) + 65536;
+    int64_t want = 2 * BPC * h->n_chunks + ((4 * walkers) >> launch_shape(h).wsh) + 65536;
     if (h->tile_map_limit >= 0) want = std::min<int64_t>(want, h->tile_map_limit);
     if (want <= h->tile_cap || h->tile_map_off) return 0;
     int64_t cap = std::max<int64_t>(want, 2 * h->tile_cap);
     if (h->tile_map_limit >= 0) cap = std::min<int64_t>(cap, h->tile_map_limit);
     HIP_TRY(hipStreamSynchronize(h->stream));
-    hipFree(h->d_tile_chunk);
-    h->d_tile_chunk = nullptr;
+    hipFree(h->d_tiles);
+    h->d_tiles = nullptr;
     h->tile_cap = 0;
     drop_graphs(h);
-    if (hipMalloc(&h->d_tile_chunk, cap * sizeof(uint32_t)) != hipSuccess) {
-        (void)hipGetLastError();   // no room: every tile grab searches instead
-        h->d_tile_chunk = nullptr;
+    if (hipMalloc(&h->d_tiles, cap * 16) != hipSuccess) {
+        (void)hipGetLastError();   // no room: every tile is found by its bucket instead
+        h->d_tiles = nullptr;
         h->tile_map_off = true;
         return 0;
     }
@@ -503,10 +524,10 @@ int64_t table_bytes(int64_t cap, int W) {
 }
 
 // h1, the packed ERI, the pair table and the single-excitation term table, with
-// rows of 64 W spin orbitals.
+// rows of 64 W spin orbitals, and the rejection bounds (two bytes each).
 int64_t integral_doubles(int M, int W) {
     const int64_t np = (int64_t)M * (M + 1) / 2, ns = 64 * (int64_t)W;
-    return (int64_t)M * M + np * (np + 1) / 2 + ns * ns + (int64_t)2 * M * ns * ns;
+    return (int64_t)M * M + np * (np + 1) / 2 + ns * ns + ns * ns / 16 + (int64_t)2 * M * ns * ns;
 }
 
 int64_t integral_bytes(int M, int W) { return integral_doubles(M, W) * 8 + 256; }
@@ -528,6 +549,8 @@ void carve(SysHost &S, void *blk, int64_t cap) {
     p += (size_t)S.eri.size() * sizeof(double);
     S.d_jk = (double *)p;
     p += (size_t)64 * S.W * 64 * S.W * sizeof(double);
+    S.d_bound = (uint16_t *)p;
+    p += (size_t)32 * S.W * 32 * S.W * sizeof(uint16_t);
     S.d_t3 = (double *)p;
     S.block = blk;
     S.cap = cap;
@@ -555,6 +578,8 @@ int upload_integrals(fciqmc_t *h, SysHost &S) {
     HIP_TRY(hipMemcpyAsync(S.d_h1, S.h1.data(), S.h1.size() * 8, hipMemcpyHostToDevice, h->stream));
     HIP_TRY(hipMemcpyAsync(S.d_eri, S.eri.data(), S.eri.size() * 8, hipMemcpyHostToDevice, h->stream));
     HIP_TRY(hipMemcpyAsync(S.d_jk, S.jk.data(), S.jk.size() * 8, hipMemcpyHostToDevice, h->stream));
+    HIP_TRY(hipMemcpyAsync(S.d_bound, S.bound.data(), S.bound.size() * 2, hipMemcpyHostToDevice,
+                           h->stream));
     HIP_TRY(hipMemcpyAsync(S.d_t3, S.t3.data(), S.t3.size() * 8, hipMemcpyHostToDevice, h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
     return 0;
@@ -571,6 +596,7 @@ void fill_desc_tables(fciqmc_t *h, int s) {
     d.eri = S.d_eri;
     d.jk = S.d_jk;
     d.t3 = S.d_t3;
+    d.bound = S.d_bound;
     d.cap = (uint64_t)S.cap;
     d.nbuckets = S.cap / BQ;
 }
@@ -622,6 +648,96 @@ int rebucket_system(fciqmc_t *h, int s, int64_t new_cap, int64_t n_spill) {
         if (attempt >= 4) return set_err(FCIQMC_ECAPACITY, "re-bucketing the main list failed");
         new_cap *= 2;
     }
+}
+
+// x in [0, 1] (or not finite) as a half-precision number not below it, 0 as 0, and none
+// subnormal (the dot product of the kernel's test may take those as 0).
+uint16_t half_up(double x) {
+    if (x > 0.0 && x < 6.2e-5) x = 6.2e-5;
+    _Float16 h = (_Float16)x;
+    uint16_t b;
+    std::memcpy(&b, &h, 2);
+    if ((double)h < x) ++b;   // (positive: the next bit pattern is the next number)
+    return b;
+}
+
+// Rejection bounds of double excitations: s over pairs of different spatial orbitals with
+// |(pa|qb)| <= s_pa s_qb for every two of them, made small by a few sweeps of s_i =
+// max_j |V_ij| / s_j, each of which keeps every inequality. (A sum over two indices
+// decides most attempts: with integrals that decay as exp(-(|p-a| + |q-b|)/3), such a
+// product follows them, where a single largest element would pass nearly every attempt.)
+// Returns the largest s, to which the table is relative.
+double double_bounds(const SysHost &S, std::vector<uint16_t> &out) {
+    const int M = S.M, nt = 32 * S.W;
+    std::vector<int64_t> pr;           // packed indices of the pairs p > a
+    std::vector<int> pp, pa;
+    for (int p = 0; p < M; ++p)
+        for (int x = 0; x < p; ++x) {
+            pr.push_back((int64_t)p * (p + 1) / 2 + x);
+            pp.push_back(p);
+            pa.push_back(x);
+        }
+    const int64_t n = (int64_t)pr.size();
+    std::vector<double> V((size_t)n * n), s(n, 0.0), inv(n, 0.0);
+    for (int64_t i = 0; i < n; ++i)
+        for (int64_t j = 0; j <= i; ++j) {
+            const double v = std::fabs(S.eri[pr[i] * (pr[i] + 1) / 2 + pr[j]]);
+            V[(size_t)i * n + j] = V[(size_t)j * n + i] = v;
+            s[i] = std::max(s[i], v);
+            s[j] = std::max(s[j], v);
+        }
+    for (int64_t i = 0; i < n; ++i) {
+        s[i] = std::sqrt(s[i]);
+        inv[i] = s[i] > 0.0 ? 1.0 / s[i] : 0.0;
+    }
+    for (int sweep = 0; sweep < 3; ++sweep)
+        for (int64_t i = 0; i < n; ++i) {
+            double m = 0.0;
+            const double own = V[(size_t)i * n + i];
+            V[(size_t)i * n + i] = 0.0;
+            for (int64_t j = 0; j < n; ++j) m = std::max(m, V[(size_t)i * n + j] * inv[j]);
+            V[(size_t)i * n + i] = own;
+            s[i] = std::max(m, std::sqrt(own));
+            inv[i] = s[i] > 0.0 ? 1.0 / s[i] : 0.0;
+        }
+    double top = 0.0;
+    for (int64_t i = 0; i < n; ++i) top = std::max(top, s[i]);
+    out.assign((size_t)nt * nt, 0);
+    for (int64_t i = 0; i < n; ++i) {
+        const uint16_t b = half_up(top > 0.0 ? s[i] / top : 0.0);
+        out[(size_t)pp[i] * nt + pa[i]] = out[(size_t)pa[i] * nt + pp[i]] = b;
+    }
+    return top;
+}
+
+// Rejection bounds of single excitations p -> a: |h_pa| plus the largest N - 1 spectator
+// terms there can be, over both spins. Returns the largest, to which the table is relative.
+double single_bounds(const SysHost &S, std::vector<uint16_t> &out) {
+    const int M = S.M, nt = 32 * S.W, ns = 64 * S.W;
+    std::vector<double> b((size_t)M * M, 0.0);
+    double top = 0.0;
+    for (int p = 0; p < M; ++p)
+        for (int x = 0; x < M; ++x) {
+            if (p == x) continue;
+            double most = 0.0;
+            for (int sp = 0; sp < 2; ++sp) {
+                double sum = 0.0, big = 0.0;
+                const double *row = &S.t3[((size_t)(2 * p + sp) * ns + (2 * x + sp)) * ns];
+                for (int q = 0; q < 2 * M; ++q) {
+                    if (q == 2 * p + sp || q == 2 * x + sp) continue;
+                    sum += std::fabs(row[q]);
+                    big = std::max(big, std::fabs(row[q]));
+                }
+                most = std::max(most, std::min(sum, big * (double)(S.N - 1)));
+            }
+            b[(size_t)p * M + x] = std::fabs(S.h1[(size_t)p * M + x]) + most;
+            top = std::max(top, b[(size_t)p * M + x]);
+        }
+    out.assign((size_t)nt * nt, 0);
+    for (int p = 0; p < M; ++p)
+        for (int x = 0; x < M; ++x)
+            out[(size_t)p * nt + x] = half_up(top > 0.0 ? b[(size_t)p * M + x] / top : 0.0);
+    return top;
 }
 
 hdet_t aufbau(const std::vector<double> &h1, int M, int na, int nb) {
@@ -830,6 +946,8 @@ int admit(fciqmc_t *h, int s, const fciqmc_hamiltonian *ham, const fciqmc_params
                 if (!diag[i] && !diag[j]) em = std::max(em, std::fabs(S.eri[k]));
         S.h_max = h1m + 2.0 * em;
     }
+    const bool defer = S.p_double >= 0.5;
+    const double scale = defer ? double_bounds(S, S.bound) : single_bounds(S, S.bound);
     const int64_t cap = initial_capacity(prm);
     void *blk = nullptr;
     rc = alloc_tables(h, S, cap, &blk);
@@ -874,6 +992,27 @@ int admit(fciqmc_t *h, int s, const fciqmc_hamiltonian *ham, const fciqmc_params
             d.pgen_c1[sp] = ne[sp] >= 2 && S.N >= 2 ? pg(ne[sp] - 1, ne[sp] - 1, ne[sp]) : 0.0;
             d.pgen_c1[2 + sp] =
                 ne[sp] > 0 && ne[1 - sp] > 0 && S.N >= 2 ? pg(ne[1 - sp], ne[sp], nal_u) : 0.0;
+        }
+    }
+    {
+        // The margin covers every rounding of the bound's single-precision arithmetic
+        // (a few 1e-7) and of the exact test's.
+        constexpr double margin = 1.0 + 1e-5;
+        d.defer = defer ? 1 : 0;
+        d.has_double = d.p_double > 0.0 ? 1 : 0;
+        d.dbl_thr = d.has_double ? (uint32_t)((uint64_t)std::ceil(d.p_double * 4294967296.0) - 1ull) : 0u;
+        // w0 / 2^32 / P_double is a double's uniform
+        const double u1 = d.inv_p_double / 4294967296.0;
+        if (defer) {
+            d.bound_ft = (float)(prm->tau * scale * scale / u1 * margin);
+            for (int c = 0; c < 4; ++c)
+                d.bound_f[c] = d.pgen_c1[c] > 0.0
+                                   ? (float)(prm->tau * scale * scale / d.pgen_c1[c] / u1 * margin)
+                                   : INFINITY;
+        } else {
+            d.bound_ft = (float)(prm->tau * scale / d.p_single * margin);
+            d.sg_mul = (float)(d.inv_p_single / 4294967296.0);
+            d.sg_sub = (float)(d.p_double * d.inv_p_single + 1e-5);
         }
     }
     d.target = prm->target_walkers;
@@ -1080,9 +1219,11 @@ int refresh_stats_after_load(fciqmc_t *h, int s, const std::vector<hdet_t> &det,
 int run_iterations(fciqmc_t *h, int L, bool sample);
 
 int capture_or_get(fciqmc_t *h, int L, hipGraphExec_t *out) {
-    // a graph holds the spawning kernel's variant: one graph per length and variant
+    // one graph per length, spawning variant and launch shape
+    const Shape sh = launch_shape(h);
     EngineArgs a = make_args(h);
-    const int key = 2 * L + a.plain;
+    a.wsh = sh.wsh;
+    const std::array<int, 5> key = {L, a.plain, sh.wsh, sh.spawn_grid, sh.post_grid};
     auto it = h->graphs.find(key);
     if (it != h->graphs.end()) {
         *out = it->second;
@@ -1091,7 +1232,7 @@ int capture_or_get(fciqmc_t *h, int L, hipGraphExec_t *out) {
     hipGraph_t g = nullptr;
     HIP_TRY(hipStreamBeginCapture(h->stream, hipStreamCaptureModeRelaxed));
     for (int i = 0; i < L; ++i)
-        FQ_LAUNCH(h->W, launch_iteration, a, h->post_grid, h->spawn_grid, i == 0, h->stream, nullptr);
+        FQ_LAUNCH(h->W, launch_iteration, a, sh.post_grid, sh.spawn_grid, i == 0, h->stream, nullptr);
     HIP_TRY(hipStreamEndCapture(h->stream, &g));
     hipGraphExec_t ex = nullptr;
     HIP_TRY(hipGraphInstantiate(&ex, g, nullptr, nullptr, 0));
@@ -1166,12 +1307,16 @@ int run_iterations(fciqmc_t *h, int L, bool sample) {
     for (int s = 0; s < h->max_sys; ++s) before[s] = h->hdesc[s].iter;
     int rc = ensure_tile_map(h);
     if (rc) return rc;
+    for (int s = 0; s < h->max_sys; ++s)
+        if (h->sys[s].active) h->hdesc[s].nw = h->sys[s].last.nw;
     rc = upload_desc(h);
     if (rc) return rc;
+    const Shape sh = launch_shape(h);
     EngineArgs a = make_args(h);
+    a.wsh = sh.wsh;
     if (h->profiling) {
         for (int i = 0; i < L; ++i) {
-            FQ_LAUNCH(h->W, launch_iteration, a, h->post_grid, h->spawn_grid, i == 0, h->stream, h->ev);
+            FQ_LAUNCH(h->W, launch_iteration, a, sh.post_grid, sh.spawn_grid, i == 0, h->stream, h->ev);
             HIP_TRY(hipEventSynchronize(h->ev[NKERN]));
             for (int k = 0; k < NKERN; ++k) {
                 float ms = 0.f;
@@ -1190,7 +1335,7 @@ int run_iterations(fciqmc_t *h, int L, bool sample) {
             HIP_TRY(hipGraphLaunch(ex, h->stream));
         }
         if (sample) {
-            FQ_LAUNCH(h->W, launch_iteration, a, h->post_grid, h->spawn_grid, true, h->stream, h->ev);
+            FQ_LAUNCH(h->W, launch_iteration, a, sh.post_grid, sh.spawn_grid, true, h->stream, h->ev);
             HIP_TRY(hipGetLastError());
             HIP_TRY(hipEventSynchronize(h->ev[NKERN]));
             for (int k = 0; k < NKERN; ++k) {
@@ -1201,7 +1346,7 @@ int run_iterations(fciqmc_t *h, int L, bool sample) {
         }
     } else {
         for (int i = 0; i < L; ++i)
-        FQ_LAUNCH(h->W, launch_iteration, a, h->post_grid, h->spawn_grid, i == 0, h->stream, nullptr);
+        FQ_LAUNCH(h->W, launch_iteration, a, sh.post_grid, sh.spawn_grid, i == 0, h->stream, nullptr);
         HIP_TRY(hipGetLastError());
     }
     HIP_TRY(hipStreamSynchronize(h->stream));
@@ -1368,17 +1513,18 @@ int create_handle(int max_slots, void *stream, int W, fciqmc_t **out) {
     h->hstatus.assign(max_slots, 0u);
     HIP_TRY(hipMalloc(&h->d_desc, sizeof(SysDesc) * max_slots));
     HIP_TRY(hipMalloc(&h->d_status, sizeof(uint32_t) * max_slots));
-    HIP_TRY(hipMalloc(&h->d_work, sizeof(unsigned int) * 4));
-    HIP_TRY(hipMemsetAsync(h->d_work, 0, sizeof(unsigned int) * 4, h->stream));
-    HIP_TRY(hipMalloc(&h->d_spawns, sizeof(unsigned long long) * max_slots));
-    HIP_TRY(hipMemsetAsync(h->d_spawns, 0, sizeof(unsigned long long) * max_slots, h->stream));
+    HIP_TRY(hipMalloc(&h->d_work, sizeof(unsigned int) * N_WORK));
+    HIP_TRY(hipMemsetAsync(h->d_work, 0, sizeof(unsigned int) * N_WORK, h->stream));
+    HIP_TRY(hipMalloc(&h->d_spawns, sizeof(unsigned long long) * SPAWN_SLOTS * max_slots));
+    HIP_TRY(hipMemsetAsync(h->d_spawns, 0, sizeof(unsigned long long) * SPAWN_SLOTS * max_slots,
+                           h->stream));
     HIP_TRY(hipHostMalloc((void **)&h->h_rec, sizeof(IterRecord) * REC_CAP * max_slots,
                           hipHostMallocDefault));
     std::memset(h->h_rec, 0, sizeof(IterRecord) * REC_CAP * max_slots);
     HIP_TRY(hipHostGetDevicePointer((void **)&h->d_rec, h->h_rec, 0));
-    HIP_TRY(hipMalloc(&h->d_total, 2 * sizeof(unsigned long long)));
+    HIP_TRY(hipMalloc(&h->d_total, N_TOTAL * sizeof(unsigned long long)));
+    HIP_TRY(hipMemsetAsync(h->d_total, 0, N_TOTAL * sizeof(unsigned long long), h->stream));
     HIP_TRY(hipMalloc(&h->d_nchunks, sizeof(int64_t)));
-    HIP_TRY(hipMalloc(&h->d_blk, 2 * 4 * SCAN_G * sizeof(unsigned long long)));
     HIP_TRY(hipMalloc(&h->d_step, sizeof(unsigned long long)));
     HIP_TRY(hipMemsetAsync(h->d_step, 0, sizeof(unsigned long long), h->stream));
     HIP_TRY(hipMalloc(&h->d_fin, sizeof(FinPart) * FIN_BLOCKS * max_slots));
@@ -1395,7 +1541,7 @@ int create_handle(int max_slots, void *stream, int W, fciqmc_t **out) {
     HIP_TRY(hipMalloc(&h->d_spilled, sizeof(uint32_t) * max_slots));
     HIP_TRY(hipMemsetAsync(h->d_spilled, 0, sizeof(uint32_t) * max_slots, h->stream));
     for (int k = 0; k <= NKERN; ++k) HIP_TRY(hipEventCreate(&h->ev[k]));
-    h->spawn_grid = spawn_grid_size();
+    h->spawn_grid = spawn_grid_size(W);
     h->post_grid = post_grid_size();
     int rc = upload_desc(h);
     if (rc) return rc;
@@ -1464,18 +1610,15 @@ void release(fciqmc_t *h) {
     hipFree(h->d_spawns);
     hipFree(h->d_total);
     hipFree(h->d_nchunks);
-    hipFree(h->d_blk);
     hipFree(h->d_step);
     hipFree(h->d_fin);
     hipFree(h->d_c0);
     hipFree(h->d_err);
     hipFree(h->d_chunk_sys);
     hipFree(h->d_chunk_local);
-    hipFree(h->d_chunk_nw);
-    hipFree(h->d_chunk_off);
-    hipFree(h->d_chunk_toff);
+    hipFree(h->d_unlisted);
     hipFree(h->d_chunk_stat);
-    hipFree(h->d_tile_chunk);
+    hipFree(h->d_tiles);
     hipFree(h->d_recs);
     hipFree(h->d_rec_max);
     hipFree(h->d_bhist);
@@ -1744,6 +1887,7 @@ int fciqmc_set_launch(fciqmc_t *h, int32_t spawn_grid, int32_t tile, int32_t pos
     h->spawn_grid = spawn_grid;
     h->post_grid = post_grid;
     h->tile = tile;
+    h->shape_set = true;
     drop_graphs(h);
     return 0;
 }
@@ -1839,6 +1983,7 @@ int fciqmc_autotune(fciqmc_t *h, int32_t iters_per_trial) {
     }
     const bool was = h->profiling;
     h->profiling = true;
+    h->shape_set = true;   // (each trial runs at its own shape)
     auto trial = [&](int sg, int tl, int pg, double &spawn_ns, double &post_ns) -> int {
         h->spawn_grid = sg;
         h->tile = tl;
@@ -1962,8 +2107,8 @@ int fciqmc_set_test_options(fciqmc_t *h, int32_t planner, int64_t tile_map_limit
     }
     if (tile_map_limit != h->tile_map_limit) {
         HIP_TRY(hipStreamSynchronize(h->stream));
-        hipFree(h->d_tile_chunk);
-        h->d_tile_chunk = nullptr;
+        hipFree(h->d_tiles);
+        h->d_tiles = nullptr;
         h->tile_cap = 0;
         h->tile_map_off = false;
         h->tile_map_limit = tile_map_limit;

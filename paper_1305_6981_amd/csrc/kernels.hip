@@ -170,16 +170,11 @@ __device__ __forceinline__ double u01_32(uint32_t w) {
 // floor(w n / 2^32): an index in [0, n).
 __device__ __forceinline__ uint32_t pick(uint32_t w, uint32_t n) { return __umulhi(w, n); }
 
-// Positions of the set bits of each byte value: the k-th (0-based) set bit of
-// byte b sits at bits [3k, 3k + 3) of sel8_entry(b).
-__device__ __forceinline__ uint32_t sel8_entry(uint32_t b) {
-    uint32_t e = 0, n = 0;
-    for (uint32_t i = 0; i < 8; ++i)
-        if (b & (1u << i)) {
-            e |= i << (3 * n);
-            ++n;
-        }
-    return e;
+// Position of the k-th (0-based) set bit of byte b (k below its bit count), the entries
+// [k][b] of the table sel8 (2 KB, staged in LDS).
+__device__ __forceinline__ uint8_t sel8_entry(uint32_t k, uint32_t b) {
+    for (uint32_t i = 0; i < k; ++i) b &= b - 1u;
+    return (uint8_t)(b ? __builtin_ctz(b) : 0);
 }
 
 // j (j - 1) / 2 for j < 2^12 (0 for j = 0): the index of the first pair (i, j).
@@ -188,25 +183,26 @@ __device__ __forceinline__ uint32_t pair_base(uint32_t j) {
 }
 
 // Position of the k-th (0-based) set bit of x (k < popcount(x)): halving with
-// popcounts down to one byte, then that byte's entry of the table sel8 (the
-// sel8_entry values, staged in LDS).
-__device__ __forceinline__ int select_bit(uint64_t x, uint32_t k, const uint32_t *sel8) {
-    int pos = 0;
+// popcounts down to one byte, then the table. (min(k, k - c) is k - c exactly when
+// k >= c.)
+__device__ __forceinline__ int select_bit(uint64_t x, uint32_t k, const uint8_t *sel8) {
     uint32_t c = (uint32_t)__popc((uint32_t)x);
-    if (k >= c) {
-        k -= c;
-        x >>= 32;
-        pos = 32;
-    }
-    uint32_t w = (uint32_t)x;
+    uint32_t w = k >= c ? (uint32_t)(x >> 32) : (uint32_t)x;
+    uint32_t pos = k >= c ? 32u : 0u;
+    k = k - c < k ? k - c : k;
     c = (uint32_t)__popc(w & 0xFFFFu);
-    if (k >= c) { k -= c; w >>= 16; pos += 16; }
+    uint32_t sh = k >= c ? 16u : 0u;
+    k = k - c < k ? k - c : k;
+    w >>= sh;
+    pos += sh;
     c = (uint32_t)__popc(w & 0xFFu);
-    if (k >= c) { k -= c; w >>= 8; pos += 8; }
-    return pos + (int)((sel8[w & 0xFFu] >> (3u * k)) & 7u);
+    sh = k >= c ? 8u : 0u;
+    k = k - c < k ? k - c : k;
+    w >>= sh;
+    return (int)(pos + sh + sel8[(k << 8) | (w & 0xFFu)]);
 }
 #if FQ_DET_WORDS == 2
-__device__ __forceinline__ int select_bit(det_t x, uint32_t k, const uint32_t *sel8) {
+__device__ __forceinline__ int select_bit(det_t x, uint32_t k, const uint8_t *sel8) {
     const uint32_t c = (uint32_t)__popcll(lo64(x));
     return k < c ? select_bit(lo64(x), k, sel8) : 64 + select_bit(hi64(x), k - c, sel8);
 }
@@ -473,6 +469,7 @@ struct Excit {
     double pgen;
     double hel;
     int p, a;
+    uint32_t nt;   // single excitation: movable electrons times targets
 };
 
 
@@ -502,7 +499,7 @@ struct ClassView {
 template <bool C1>
 __device__ __forceinline__ bool excite_single(const SysDesc &d, const ClassView<C1> &cv,
                                               det_t det, uint32_t w1, uint32_t w2,
-                                              const uint32_t *sel8, Excit &ex) {
+                                              const uint8_t *sel8, Excit &ex) {
     const det_t emp = ~det & valid_of(d);
     const int n_class = C1 ? 2 : d.n_class;
     det_t movable = det_t(0ull);
@@ -520,100 +517,172 @@ __device__ __forceinline__ bool excite_single(const SysDesc &d, const ClassView<
     ex.pgen = d.p_single / (double)((int64_t)nal * (int64_t)nmov);
     ex.p = p;
     ex.a = a;
+    ex.nt = nal * nmov;
     return true;
 }
 
-constexpr int EX_NULL = 0, EX_OK = 1, EX_SINGLE_DEFERRED = 2;
-
-// One excitation from the words of one Philox block: w.x (type), w.y
-// (electron or pair), w.z, w.w (holes). recip[k] = 1.0 / k, filled by IEEE
-// division (same bits as dividing in place). With defer_single a single
-// excitation is only recognised (EX_SINGLE_DEFERRED): the caller queues its
-// words and generates it later, so the rare singles do not make whole
-// wavefronts run the single path.
+// pgen of a single excitation from orbital p of det that has a target (Sec. 5.1): the
+// value excite_single gives, from the electron alone.
 template <bool C1>
-__device__ __forceinline__ int excite(const SysDesc &d, const ClassView<C1> &cv, det_t det,
-                                      uint4 w, const double *recip, const uint32_t *sel8,
-                                      bool defer_single, Excit &ex) {
+__device__ __forceinline__ double single_pgen(const SysDesc &d, const ClassView<C1> &cv, det_t det,
+                                              int p) {
     const det_t emp = ~det & valid_of(d);
-    const int N = d.N;
     const int n_class = C1 ? 2 : d.n_class;
-    if (!(u01_32(w.x) < d.p_double)) {
-        if (defer_single) return EX_SINGLE_DEFERRED;
-        if (!excite_single(d, cv, det, w.y, w.z, sel8, ex)) return EX_NULL;
-        ex.hel = hel_single(d, det, ex.p, ex.a);
-        return EX_OK;
+    det_t movable = det_t(0ull);
+    for (int c = 0; c < n_class; ++c) {
+        const det_t cm = C1 ? cv.mask(c) : cmask_of(d, c);
+        if (emp & cm) movable |= det & cm;
     }
-    // Double (Sec. 5.2): a unique pair by inverse triangular indexing.
-    if (N < 2) return EX_NULL;
-    const uint32_t npairs = (uint32_t)(N * (N - 1) / 2);
-    const uint32_t K = pick(w.y, npairs);   // < 2016
+    const uint32_t nal = (uint32_t)dpopc(emp & cv.mask(cv.cls(d, p)));
+    return d.p_single / (double)((int64_t)nal * (int64_t)dpopc(movable));
+}
+
+// What the spawning kernel's attempts need of a system, kept in scalar registers while it
+// works on the system (read from the descriptor at each attempt, these were a dozen
+// dependent scalar loads: most of a short wavefront's time).
+struct SpawnSys {
+    uint64_t seed;
+    det_t valid;
+    uint32_t iterw;          // iteration, as in the Philox counter
+    uint32_t dbl_thr, npairs;
+    uint32_t n0, n1, nl0, nl1, nu;   // empty orbitals per spin; first-hole choices for like
+                                     // spins (0, 1) and unlike spins; 0: none
+    uint64_t mu;             // orbitals that may be the first hole for unlike spins
+    float f0, f1, f2, f3, ft;   // rejection: (float)w0 > bound x f (SysDesc::bound_f)
+    float sg_mul, sg_sub;    // a single's acceptance uniform, rounded down
+    int32_t has_double, defer, c1, coupled;
+};
+// Values made uniform explicitly (the compiler then keeps them in scalar registers).
+__device__ __forceinline__ uint32_t uni(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+}
+__device__ __forceinline__ uint64_t uni(uint64_t x) {
+    return (uint64_t)uni((uint32_t)x) | ((uint64_t)uni((uint32_t)(x >> 32)) << 32);
+}
+__device__ __forceinline__ float uni(float x) { return __uint_as_float(uni(__float_as_uint(x))); }
+__device__ __forceinline__ SpawnSys spawn_sys(const SysDesc &d) {
+    SpawnSys h;
+    h.seed = uni(d.seed);
+    h.valid = make_det(uni(d.valid), uni(d.valid_hi));
+    h.iterw = uni(((uint32_t)((uint64_t)d.iter & 0xFFFFFFu)) << 8);
+    h.dbl_thr = uni(d.dbl_thr);
+    h.npairs = uni((uint32_t)(d.N * (d.N - 1) / 2));
+    h.n0 = uni((uint32_t)d.n_emp[0]);
+    h.n1 = uni((uint32_t)d.n_emp[1]);
+    h.nl0 = h.n0 >= 2u ? h.n0 : 0u;
+    h.nl1 = h.n1 >= 2u ? h.n1 : 0u;
+    h.nu = (h.n1 > 0u ? h.n0 : 0u) + (h.n0 > 0u ? h.n1 : 0u);
+    h.mu = (h.n1 > 0u ? 0x5555555555555555ull : 0ull) | (h.n0 > 0u ? 0xAAAAAAAAAAAAAAAAull : 0ull);
+    h.f0 = uni(d.bound_f[0]);
+    h.f1 = uni(d.bound_f[1]);
+    h.f2 = uni(d.bound_f[2]);
+    h.f3 = uni(d.bound_f[3]);
+    h.ft = uni(d.bound_ft);
+    h.sg_mul = uni(d.sg_mul);
+    h.sg_sub = uni(d.sg_sub);
+    h.has_double = (int32_t)uni(d.has_double && d.N >= 2 ? 1u : 0u);
+    h.defer = (int32_t)uni((uint32_t)d.defer);
+    h.c1 = (int32_t)uni(d.n_class == 2 ? 1u : 0u);
+    h.coupled = (int32_t)uni((uint32_t)d.hphf);
+    return h;
+}
+// c ? a : b of values (a conditional between two members would select an address and keep
+// the whole struct in memory).
+template <typename T>
+__device__ __forceinline__ T pick_if(bool c, T a, T b) {
+    return c ? a : b;
+}
+__device__ __forceinline__ uint4 spawn_words(const SpawnSys &h, det_t det, uint32_t k) {
+    const uint64_t lo = lo64(det), key = h.seed ^ hi64(det);
+    return philox10(make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), k, h.iterw), (uint32_t)key,
+                    (uint32_t)(key >> 32));
+}
+
+// The orbitals of a double excitation (Sec. 5.2) from the words of one Philox block: the
+// electrons p < q from w.y, the holes a and b, in the order drawn, from w.z and w.w.
+// Returns false for a null excitation. pgen: with no point group one of the four
+// per-system values, given as its index pc; else computed here. recip[k] = 1.0 / k,
+// filled by IEEE division (same bits as dividing in place).
+struct DoubleDraw {
+    int p, q, a, b, pc;
+    double pgen;
+};
+// A unique pair of electrons by inverse triangular indexing.
+__device__ __forceinline__ void draw_pair(uint32_t npairs, det_t det, uint32_t w, const uint8_t *sel8,
+                                          DoubleDraw &x) {
+    const uint32_t K = pick(w, npairs);   // < 2016
     // The estimate from the hardware square root is within one of j (the largest
     // j with j (j - 1) / 2 <= K); one exact integer correction each way.
     // (float)(8 K + 1), exact below 2^23, by the mantissa trick
-    const float x = __int_as_float((int)(0x4B000000u | (8u * K + 1u))) - 8388608.0f;
-    uint32_t j = (uint32_t)((1.0f + __builtin_amdgcn_sqrtf(x)) * 0.5f);
+    const float xf = __int_as_float((int)(0x4B000000u | (8u * K + 1u))) - 8388608.0f;
+    uint32_t j = (uint32_t)((1.0f + __builtin_amdgcn_sqrtf(xf)) * 0.5f);
     j -= pair_base(j) > K ? 1u : 0u;
     j += pair_base(j + 1) <= K ? 1u : 0u;
-    const uint32_t i = K - pair_base(j);
-    const int p = select_bit(det, i, sel8), q = select_bit(det, j, sel8);
-    const bool same = ((p ^ q) & 1) == 0;
-    int a, b;
-    if (C1) {
-        // No point group: every determinant has the same number of empty orbitals of
-        // each spin (d.n_emp), so the allowed sets and their sizes follow from the
-        // spins alone, and pgen is one of four per-system values (the general branch
-        // below gives the same sets, counts and pgen).
-        const int sp = p & 1;
-        const det_t e0 = emp & even_bits(), e1 = emp & odd_bits();
-        const uint32_t n0 = (uint32_t)d.n_emp[0], n1 = (uint32_t)d.n_emp[1];
-        det_t allowed;
-        uint32_t nal;
-        if (same) {
-            allowed = sp ? e1 : e0;
-            const uint32_t ne = sp ? n1 : n0;
-            nal = ne >= 2 ? ne : 0;
-        } else {
-            allowed = (n1 > 0 ? e0 : det_t(0ull)) | (n0 > 0 ? e1 : det_t(0ull));
-            nal = (n1 > 0 ? n0 : 0u) + (n0 > 0 ? n1 : 0u);
-        }
-        if (nal == 0) return EX_NULL;
-        a = select_bit(allowed, pick(w.z, nal), sel8);
-        const int sa = a & 1;
-        const det_t bset = same ? (allowed & ~DBIT(a)) : (sa ? e0 : e1);
-        const uint32_t nba = same ? nal - 1 : (sa ? n0 : n1);
-        b = select_bit(bset, pick(w.w, nba), sel8);
-        ex.pgen = same ? (sp ? d.pgen_c1[1] : d.pgen_c1[0]) : (sa ? d.pgen_c1[3] : d.pgen_c1[2]);
-    } else {
-        const det_t A = same ? (emp & ((p & 1) ? odd_bits() : even_bits())) : emp;
-        const int gpq = cv.irrep(d, p >> 1) ^ cv.irrep(d, q >> 1);
-        // a orbitals whose partner class (Eq. sym1 plus spin) has an empty orbital besides a.
-        det_t allowed = det_t(0ull);
-        for (int c = 0; c < n_class; ++c) {
-            const det_t memb = A & cmask_of(d, c);
-            if (!memb) continue;
-            const int sb = same ? (p & 1) : 1 - (c & 1);
-            const int pc = 2 * (gpq ^ (c >> 1)) + sb;
-            const int nb = dpopc(emp & cv.mask(pc)) - (pc == c ? 1 : 0);
-            if (nb > 0) allowed |= memb;
-        }
-        const uint32_t nal = (uint32_t)dpopc(allowed);
-        if (nal == 0) return EX_NULL;
-        a = select_bit(allowed, pick(w.z, nal), sel8);
-        const int ca = cv.cls(d, a);
-        const int pca = 2 * (gpq ^ (ca >> 1)) + (same ? (p & 1) : 1 - (ca & 1));
-        const det_t bset = emp & cv.mask(pca) & ~DBIT(a);
-        const uint32_t nba = (uint32_t)dpopc(bset);
-        b = select_bit(bset, pick(w.w, nba), sel8);
-        const int cb = cv.cls(d, b);
-        const int pcb = 2 * (gpq ^ (cb >> 1)) + (same ? (p & 1) : 1 - (cb & 1));
-        const int nbb = dpopc(emp & cv.mask(pcb)) - (pcb == cb ? 1 : 0);
-        ex.pgen = (2.0 * d.p_double * (recip[nba] + recip[nbb])) /
-                  (double)((int64_t)N * (int64_t)(N - 1) * (int64_t)nal);
+    x.p = select_bit(det, K - pair_base(j), sel8);
+    x.q = select_bit(det, j, sel8);
+}
+// No point group: every determinant has the same number of empty orbitals of each spin, so
+// the allowed sets and their sizes follow from the spins alone, and pgen is one of four
+// per-system values (the general draw below gives the same sets, counts and pgen). Like
+// spins: both holes from the empty orbitals of that spin, the second by its rank without
+// the first. Unlike spins: the first from all empty orbitals that leave the other spin a
+// choice. Free of branches (a null excitation selects from an empty set, harmlessly).
+__device__ __forceinline__ bool draw_double_c1(const SpawnSys &h, det_t det, uint4 w,
+                                               const uint8_t *sel8, DoubleDraw &x) {
+    const det_t emp = ~det & h.valid;
+    draw_pair(h.npairs, det, w.y, sel8, x);
+    const bool same = ((x.p ^ x.q) & 1) == 0, sp = (x.p & 1) != 0;
+    const uint64_t ev = 0x5555555555555555ull, od = 0xAAAAAAAAAAAAAAAAull;
+    const uint64_t ms = sp ? od : ev, ma = pick_if(same, ms, h.mu);
+    const uint32_t nal = pick_if(same, pick_if(sp, h.nl1, h.nl0), h.nu);
+    const uint32_t ka = pick(w.z, nal);
+    x.a = select_bit(emp & make_det(ma, ma), ka, sel8);
+    const bool sa = (x.a & 1) != 0;
+    const uint64_t mb = same ? ms : sa ? ev : od;
+    const uint32_t nb = pick_if(same, nal ? nal - 1u : 0u, pick_if(sa, h.n0, h.n1));
+    uint32_t kb = pick(w.w, nb);
+    kb += same && kb >= ka ? 1u : 0u;
+    x.b = select_bit(emp & make_det(mb, mb), kb, sel8);
+    x.pc = same ? (int)sp : 2 + (int)sa;
+    return nal != 0u;
+}
+__device__ __forceinline__ bool draw_double(const SysDesc &d, const ClassView<false> &cv, det_t det,
+                                            uint4 w, const double *recip, const uint8_t *sel8,
+                                            DoubleDraw &x) {
+    const det_t emp = ~det & valid_of(d);
+    const int N = d.N, n_class = d.n_class;
+    draw_pair((uint32_t)(N * (N - 1) / 2), det, w.y, sel8, x);
+    const int p = x.p;
+    const bool same = ((p ^ x.q) & 1) == 0;
+    const det_t A = same ? (emp & ((p & 1) ? odd_bits() : even_bits())) : emp;
+    const int gpq = cv.irrep(d, p >> 1) ^ cv.irrep(d, x.q >> 1);
+    // a orbitals whose partner class (Eq. sym1 plus spin) has an empty orbital besides a.
+    det_t allowed = det_t(0ull);
+    for (int c = 0; c < n_class; ++c) {
+        const det_t memb = A & cmask_of(d, c);
+        if (!memb) continue;
+        const int sb = same ? (p & 1) : 1 - (c & 1);
+        const int pc = 2 * (gpq ^ (c >> 1)) + sb;
+        const int nb = dpopc(emp & cv.mask(pc)) - (pc == c ? 1 : 0);
+        if (nb > 0) allowed |= memb;
     }
-    ex.det = det ^ DBIT(p) ^ DBIT(q) ^ DBIT(a) ^ DBIT(b);
-    ex.hel = hel_double(d, det, p, q, a, b);
-    return EX_OK;
+    const uint32_t nal = (uint32_t)dpopc(allowed);
+    if (nal == 0) return false;
+    const int a = select_bit(allowed, pick(w.z, nal), sel8);
+    const int ca = cv.cls(d, a);
+    const int pca = 2 * (gpq ^ (ca >> 1)) + (same ? (p & 1) : 1 - (ca & 1));
+    const det_t bset = emp & cv.mask(pca) & ~DBIT(a);
+    const uint32_t nba = (uint32_t)dpopc(bset);
+    const int b = select_bit(bset, pick(w.w, nba), sel8);
+    const int cb = cv.cls(d, b);
+    const int pcb = 2 * (gpq ^ (cb >> 1)) + (same ? (p & 1) : 1 - (cb & 1));
+    const int nbb = dpopc(emp & cv.mask(pcb)) - (pcb == cb ? 1 : 0);
+    x.a = a;
+    x.b = b;
+    x.pc = 0;
+    x.pgen = (2.0 * d.p_double * (recip[nba] + recip[nbb])) /
+             (double)((int64_t)N * (int64_t)(N - 1) * (int64_t)nal);
+    return true;
 }
 
 // ---------------------------------------------------------------------------
@@ -788,6 +857,13 @@ __device__ __forceinline__ T wave_sum(T v) {
     return v;
 }
 
+// Orders the LDS accesses of a wavefront's lanes around it (LDS operations of one
+// wavefront complete in issue order, so no wait is needed, only no code motion).
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Inclusive prefix sum over the 64 lanes of a wavefront by data-parallel primitives
 // (DPP): shifts within rows of 16 lanes, then row broadcasts (no LDS traffic).
 template <int CTRL>
@@ -813,195 +889,245 @@ __device__ __forceinline__ unsigned long long wave_incl_scan(unsigned long long 
     return x;
 }
 
-// Halves of the chunk sums and range sums: this iteration's in (step & 1).
-__device__ __forceinline__ unsigned cur_half(const EngineArgs &a) { return (unsigned)(*a.step & 1ull); }
-__device__ __forceinline__ unsigned long long *sums(const EngineArgs &a, unsigned h) {
-    return a.chunk_nw + (h ? a.chunk_cap : 0);
+// The same for 32-bit sums and maxima (one instruction a step: lanes without a source
+// take the 0 given as the old value).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_0(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
 }
-__device__ __forceinline__ unsigned long long *ranges(const EngineArgs &a, unsigned h) {
-    return a.blk + (h ? 4 * SCAN_G : 0);
+__device__ __forceinline__ uint32_t wave_incl_sum32(uint32_t x) {
+    x += dpp_or_0<0x111, 0xF>(x);
+    x += dpp_or_0<0x112, 0xF>(x);
+    x += dpp_or_0<0x114, 0xF>(x);
+    x += dpp_or_0<0x118, 0xF>(x);
+    x += dpp_or_0<0x142, 0xA>(x);   // row_bcast:15 into rows 1 and 3
+    x += dpp_or_0<0x143, 0xC>(x);   // row_bcast:31 into rows 2 and 3
+    return x;
+}
+__device__ __forceinline__ uint32_t wave_incl_max32(uint32_t x) {
+    auto mx = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
+    x = mx(x, dpp_or_0<0x111, 0xF>(x));
+    x = mx(x, dpp_or_0<0x112, 0xF>(x));
+    x = mx(x, dpp_or_0<0x114, 0xF>(x));
+    x = mx(x, dpp_or_0<0x118, 0xF>(x));
+    x = mx(x, dpp_or_0<0x142, 0xA>(x));
+    x = mx(x, dpp_or_0<0x143, 0xC>(x));
+    return x;
 }
 
 // ---------------------------------------------------------------------------
-// K1: chunk sums of |C| on the current tables. Workgroup g takes the chunks
-// [g per, (g+1) per) (per = ceil(chunks / SCAN_G)), four at a time, writes
-// each chunk's sum and the range's total attempts and spawn tiles.
+// Handing out work. One counter for the whole chip serves about 100 grabs per
+// microsecond, which 6144 wavefronts exceed (a kernel of 100 us spent most of it in 28000
+// grabs of one tile); so work is kept in NLIST lists with a counter each, on lines of
+// their own. A taker begins with a share of its home list fixed by its number (no atomic),
+// goes on by its home list's counter and then takes from lists that still hold work,
+// found by reading all the counters at once. With one share per taker or less there is no
+// atomic at all.
 // ---------------------------------------------------------------------------
+struct Handout {
+    unsigned int *work;          // the lists' counters (CTR_STRIDE apart)
+    const unsigned int *len;     // the lists' lengths, in LDS
+    unsigned int takers;         // per workgroup
+    unsigned int share;
+    int list;                    // list being taken from
+    bool begin;
+};
+// Items of list l that are handed out by number: one share to every taker of the
+// workgroups congruent to l.
+__device__ __forceinline__ unsigned int handout_fixed(const Handout &h, unsigned int l) {
+    const unsigned int g = gridDim.x;
+    return l < g ? h.takers * ((g - l + NLIST - 1) / NLIST) * h.share : 0u;
+}
+// The next share: items [at, at + count) of list h.list. rank: this taker's number among
+// those at home in its list. Returns false when every list is empty. Whole wavefront;
+// uniform results.
+__device__ __forceinline__ bool handout_next(Handout &h, unsigned int rank, unsigned int &at,
+                                             unsigned int &count) {
+    const unsigned int lane = threadIdx.x & 63u;
+    unsigned int n = (unsigned int)__builtin_amdgcn_readfirstlane((int)h.len[h.list]);
+    if (h.begin) {
+        h.begin = false;
+        at = rank * h.share;
+        if (at < n) {
+            count = n - at < h.share ? n - at : h.share;
+            return true;
+        }
+    }
+    for (;;) {
+        const unsigned int f = handout_fixed(h, (unsigned int)h.list);
+        if (f < n) {
+            unsigned int g = 0;
+            if (lane == 0) g = atomicAdd(&h.work[h.list * CTR_STRIDE], h.share);
+            at = f + (unsigned int)__builtin_amdgcn_readfirstlane((int)g);
+            if (at < n) {
+                count = n - at < h.share ? n - at : h.share;
+                return true;
+            }
+        }
+        // another list that still holds work, the nearest after this one
+        const unsigned int nl = h.len[lane & (NLIST - 1)], fl = handout_fixed(h, lane & (NLIST - 1));
+        const bool open = lane < NLIST && fl < nl;
+        if (!__ballot(open)) return false;
+        unsigned int w = 0xFFFFFFFFu;
+        if (open) w = __hip_atomic_load(&h.work[lane * CTR_STRIDE], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const uint64_t m = __ballot(open && w < nl - fl);
+        if (!m) return false;
+        const uint64_t after = m & ~((2ull << h.list) - 1ull);
+        h.list = __builtin_ctzll(after ? after : m);
+        n = (unsigned int)__builtin_amdgcn_readfirstlane((int)h.len[h.list]);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Spawn tiles. A tile is a run of at most 2^wsh consecutive attempts (walkers) of one
+// bucket, the unit of work of a wavefront in k_spawn; the tiles of all buckets form NLIST
+// lists in no particular order (results do not depend on it), written by k_post as it
+// finishes its windows, or by k_tiles before the first iteration of a launch. A tile
+// holds its system, the bucket in the system, its number among the bucket's tiles, and
+// its attempts | the bucket's entries << 20 | whether the bucket holds 2^30 walkers or more.
+// ---------------------------------------------------------------------------
+constexpr int TILE_ENT_SHIFT = 20;
+constexpr uint32_t TILE_BIG = 1u << 31;
+
+__device__ __forceinline__ void put_tile(const EngineArgs &a, int list, unsigned long long at, int s,
+                                         uint32_t lb, uint32_t j, unsigned long long x, int n) {
+    const unsigned long long done = (unsigned long long)j << a.wsh, wt = 1ull << a.wsh;
+    const unsigned long long left = x > done ? x - done : 0ull;
+    const uint32_t n_t = (uint32_t)(left < wt ? left : wt);
+    gstore_i4(a.tiles + 4 * ((int64_t)list * a.list_cap + (int64_t)at), s, (int)lb, (int)j,
+              (int)(n_t | ((uint32_t)n << TILE_ENT_SHIFT) | (x >> 30 ? TILE_BIG : 0u)));
+}
+
+// A bucket whose tiles do not fit their list: k_spawn takes it whole from a list of its
+// own (any of its tiles' places that were reserved get empty tiles).
+__device__ __forceinline__ void put_unlisted(const EngineArgs &a, int h, int64_t gb) {
+    const unsigned long long u = atomicAdd(&a.total[CTR_UNLISTED(h)], 1ull);
+    a.unlisted[u] = (uint32_t)gb;
+}
+
+// Append the tiles of one bucket per lane (x walkers, n entries; x = 0: none; call with
+// the whole wavefront) to the lists of half h: one reservation in the given list for all
+// buckets of at most 64 tiles (callers deal their groups of buckets out to the lists in
+// turn, so that all lists hold much the same of every system); a bucket with more (the reference's can have thousands)
+// is spread over several lists, in runs of at least 64 (in a batch a list of short runs
+// of many systems makes every wavefront change system at nearly every tile).
+__device__ __forceinline__ void emit_tiles(const EngineArgs &a, int h, int list, int64_t gb, int s,
+                                           uint32_t lb, unsigned long long x, int n) {
+    const int lane = threadIdx.x & 63;
+    const unsigned long long cap = (unsigned long long)a.list_cap;
+    const unsigned long long nt = (x + (1ull << a.wsh) - 1ull) >> a.wsh;
+    const bool few = nt <= 64ull;
+    const unsigned long long mine = few ? nt : 0ull, incl = wave_incl_scan(mine);
+    unsigned long long base = 0;
+    if (lane == 63 && incl) base = atomicAdd(&a.total[CTR_TILES(h, list)], incl);
+    base = __shfl(base, 63, 64);
+    const unsigned long long at = base + incl - mine;
+    const bool fits = mine == 0ull || at + mine <= cap;   // (empty buckets and idle lanes fit)
+    for (unsigned long long k = 0; k < mine && at + k < cap; ++k)
+        put_tile(a, list, at + k, s, lb, (uint32_t)k, fits ? x : 0ull, n);
+    if (!fits) put_unlisted(a, h, gb);
+    for (uint64_t big = __ballot(!few); big; big &= big - 1) {
+        const int l = __builtin_ctzll(big);
+        const unsigned long long nl = __shfl(nt, l, 64), xl = __shfl(x, l, 64);
+        const int sl = __shfl(s, l, 64), ml = __shfl(n, l, 64);
+        const uint32_t bl = (uint32_t)__shfl((int)lb, l, 64);
+        // over as many lists as give each 64 tiles, from the given one on: lane i fills the
+        // part of list i, tiles i, i + lists, ...
+        const int lists = nl < 64ull * NLIST ? (int)((nl + 63ull) / 64ull) : NLIST;
+        const int to = (list + lane) & (NLIST - 1);
+        const bool fill = lane < lists;
+        const unsigned long long part = fill ? (nl + (unsigned)(lists - 1 - lane)) / (unsigned)lists : 0ull;
+        const unsigned long long b = fill ? atomicAdd(&a.total[CTR_TILES(h, to)], part) : 0ull;
+        const bool all = !__ballot(fill && b + part > cap);
+        for (unsigned long long k = 0; k < part && b + k < cap; ++k)
+            put_tile(a, to, b + k, sl, bl, (uint32_t)(k * (unsigned)lists + (unsigned)lane), all ? xl : 0ull, ml);
+        if (!all && lane == l) put_unlisted(a, h, gb);
+    }
+}
+
+// The tile lists of an iteration: half step & 1, the next one's in the other; those of a
+// launch's first iteration in 2.
+__device__ __forceinline__ int cur_half(const EngineArgs &a) { return (int)(*a.step & 1ull); }
+
+// Sum of |C| over a bucket's n entries by a wavefront.
 __device__ __forceinline__ unsigned long long abs_sum4(int4 v) {
     return (unsigned long long)(abs(v.x)) + (unsigned long long)(abs(v.y)) +
            (unsigned long long)(abs(v.z)) + (unsigned long long)(abs(v.w));
 }
+__device__ __forceinline__ unsigned long long bucket_walkers(const SysDesc &d, int64_t lb, int n) {
+    const int e = 4 * (threadIdx.x & 63);
+    int4 q = make_int4(0, 0, 0, 0);
+    if (e < n) {
+        q = gload_i4(d.pop + lb * BQ + e);
+        if (e + 1 >= n) q.y = 0;
+        if (e + 2 >= n) q.z = 0;
+        if (e + 3 >= n) q.w = 0;
+    }
+    return wave_sum(abs_sum4(q));
+}
 
-__global__ __launch_bounds__(256) void k_chunk_sum(EngineArgs a,
-                                                   const SysDesc *__restrict__ desc) {
-    __shared__ unsigned long long sh[4][4];
-    const int64_t nch = *a.nchunks;
-    const int64_t per = (nch + SCAN_G - 1) / SCAN_G;
-    const int64_t c0 = (int64_t)blockIdx.x * per;
-    const int64_t c1 = c0 + per < nch ? c0 + per : nch;
-    const int tsh = __builtin_ctzll((unsigned long long)a.tile);
-    const unsigned long long tm = (unsigned long long)a.tile - 1ull;
-    const int t = threadIdx.x;
-    unsigned long long *const nws = sums(a, cur_half(a));
-    unsigned long long *const rg = ranges(a, cur_half(a));
-    unsigned long long bs = 0, bt = 0;    // range totals, kept by thread 0
-    for (int64_t c = c0; c < c1; c += 4) {
-        unsigned long long v[4];
+// ---------------------------------------------------------------------------
+// K1: the tiles of the current list (the first iteration of a launch). A wavefront takes
+// up to 64 consecutive buckets, fewer in a small list; four buckets' loads are in flight
+// at a time.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void k_tiles(EngineArgs a, const SysDesc *__restrict__ desc) {
+    const int lane = threadIdx.x & 63;
+    const int64_t nbk = *a.nchunks * BPC, waves = (int64_t)gridDim.x * 4;
+    const int64_t share = (nbk + waves - 1) / waves;
+    const int per = (int)(share < 64 ? (share + 3) / 4 * 4 : 64);
+    for (int64_t b0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * per; b0 < nbk; b0 += waves * per) {
+        unsigned long long x = 0;
+        int sx = 0, nx = 0;
+        uint32_t lx = 0;
+        for (int k = 0; k < per && b0 + k < nbk; k += BPC) {   // one chunk: BPC buckets of a system
+            const int sy = __builtin_amdgcn_readfirstlane(a.chunk_sys[(b0 + k) / BPC]);
+            if (sy < 0) continue;
+            const SysDesc &d = desc[sy];
+            if (!participating(d, a.status[sy])) continue;
+            const int64_t lb = (int64_t)a.chunk_local[(b0 + k) / BPC] * BPC;
+            int n[BPC];
+            int4 q[BPC];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            v[k] = 0;
-            const int64_t cc = c + k;
-            if (cc < c1) {
-                const int sy = a.chunk_sys[cc];
-                if (sy >= 0) {
-                    // the chunk's four buckets, one per wavefront, four entries per lane
-                    const SysDesc &d = desc[sy];
-                    const int64_t lb = (int64_t)a.chunk_local[cc] * BPC + (t >> 6);
-                    const int e = 4 * (t & 63);
-                    const int n = d.bcnt[lb];
-                    if (participating(d, a.status[sy]) && e < n) {
-                        int4 q = *reinterpret_cast<const int4 *>(d.pop + lb * BQ + e);
-                        if (e + 1 >= n) q.y = 0;
-                        if (e + 2 >= n) q.z = 0;
-                        if (e + 3 >= n) q.w = 0;
-                        v[k] = abs_sum4(q);
-                    }
+            for (int u = 0; u < BPC; ++u) {
+                n[u] = d.bcnt[lb + u];
+                q[u] = gload_i4(d.pop + (lb + u) * BQ + 4 * lane);   // (past the entries: masked)
+            }
+#pragma unroll
+            for (int u = 0; u < BPC; ++u) {
+                const int e = 4 * lane;
+                if (e >= n[u]) q[u].x = 0;
+                if (e + 1 >= n[u]) q[u].y = 0;
+                if (e + 2 >= n[u]) q[u].z = 0;
+                if (e + 3 >= n[u]) q[u].w = 0;
+                const unsigned long long w = wave_sum(abs_sum4(q[u]));
+                if (lane == k + u) {
+                    x = w;
+                    sx = sy;
+                    nx = n[u];
+                    lx = (uint32_t)(lb + u);
                 }
             }
         }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const unsigned long long w = wave_sum(v[k]);
-            if ((t & 63) == 0) sh[k][t >> 6] = w;
-        }
-        __syncthreads();
-        if (t == 0) {
-            for (int k = 0; k < 4 && c + k < c1; ++k) {
-                const unsigned long long x = sh[k][0] + sh[k][1] + sh[k][2] + sh[k][3];
-                nws[c + k] = x;
-                bs += x;
-                bt += (x + tm) >> tsh;
-            }
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-        rg[blockIdx.x] = bs;
-        rg[SCAN_G + blockIdx.x] = bt;
+        emit_tiles(a, 2, (int)((b0 / per) & (NLIST - 1)), b0 + lane, sx, lx, x, nx);
     }
 }
 
 // ---------------------------------------------------------------------------
-// K2a: exclusive scan of the SCAN_G range totals (one workgroup, two per
-// thread); also resets the dynamic work counters of the spawn and post kernels
-// and the range sums that k_post accumulates for the next iteration.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void k_scan(EngineArgs a) {
-    __shared__ unsigned long long part[1024], tpart[1024];
-    const int t = threadIdx.x;
-    unsigned long long *const rg = ranges(a, cur_half(a));
-    unsigned long long *const rn = ranges(a, cur_half(a) ^ 1u);
-    rn[2 * t] = 0ull;
-    rn[2 * t + 1] = 0ull;
-    rn[SCAN_G + 2 * t] = 0ull;
-    rn[SCAN_G + 2 * t + 1] = 0ull;
-    const unsigned long long s0 = rg[2 * t], s1 = rg[2 * t + 1];
-    const unsigned long long t0 = rg[SCAN_G + 2 * t], t1 = rg[SCAN_G + 2 * t + 1];
-    part[t] = s0 + s1;
-    tpart[t] = t0 + t1;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        const unsigned long long v = t >= off ? part[t - off] : 0ull;
-        const unsigned long long vt = t >= off ? tpart[t - off] : 0ull;
-        __syncthreads();
-        part[t] += v;
-        tpart[t] += vt;
-        __syncthreads();
-    }
-    const unsigned long long run = part[t] - (s0 + s1), trun = tpart[t] - (t0 + t1);
-    rg[2 * SCAN_G + 2 * t] = run;
-    rg[2 * SCAN_G + 2 * t + 1] = run + s0;
-    rg[3 * SCAN_G + 2 * t] = trun;
-    rg[3 * SCAN_G + 2 * t + 1] = trun + t0;
-    if (t == 1023) {
-        a.total[0] = part[1023];
-        a.total[1] = tpart[1023];
-        a.work[0] = 0u;
-        a.work[1] = 0u;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// K2b: per chunk, the exclusive scans of |C| sums (attempt offsets) and of
-// spawn tiles, inside each range from the range's offset.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_scan_down(EngineArgs a) {
-    __shared__ unsigned long long ws[4], wt[4];
-    const int64_t nch = *a.nchunks;
-    const int64_t per = (nch + SCAN_G - 1) / SCAN_G;
-    const int64_t c0 = (int64_t)blockIdx.x * per;
-    const int64_t c1 = c0 + per < nch ? c0 + per : nch;
-    const int tsh = __builtin_ctzll((unsigned long long)a.tile);
-    const unsigned long long tm = (unsigned long long)a.tile - 1ull;
-    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    const unsigned long long *const nws = sums(a, cur_half(a));
-    const unsigned long long *const rg = ranges(a, cur_half(a));
-    unsigned long long base = rg[2 * SCAN_G + blockIdx.x];
-    unsigned long long tbase = rg[3 * SCAN_G + blockIdx.x];
-    for (int64_t c = c0; c < c1; c += 256) {
-        const int64_t i = c + t;
-        const unsigned long long v = i < c1 ? nws[i] : 0ull;
-        const unsigned long long vt = (v + tm) >> tsh;
-        // inclusive scans inside the wavefront
-        unsigned long long x = v, xt = vt;
-        for (int o = 1; o < 64; o <<= 1) {
-            const unsigned long long y = __shfl_up(x, o, 64);
-            const unsigned long long yt = __shfl_up(xt, o, 64);
-            if (lane >= o) {
-                x += y;
-                xt += yt;
-            }
-        }
-        if (lane == 63) {
-            ws[w] = x;
-            wt[w] = xt;
-        }
-        __syncthreads();
-        unsigned long long pre = 0, pret = 0;
-        for (int k = 0; k < w; ++k) {
-            pre += ws[k];
-            pret += wt[k];
-        }
-        // The chunk of each of its tiles, for k_spawn's tile grabs: up to eight by the
-        // chunk's thread, the rest (the reference determinant's chunk has thousands)
-        // by the whole wavefront.
-        const unsigned long long to = tbase + pret + xt - vt;
-        const unsigned long long cap = (unsigned long long)a.tile_cap;
-        if (i < c1) {
-            a.chunk_off[i] = base + pre + x - v;
-            a.chunk_toff[i] = to;
-            const unsigned long long te = to + (vt < 8ull ? vt : 8ull);
-            for (unsigned long long k = to; k < te && k < cap; ++k) a.tile_chunk[k] = (uint32_t)i;
-        }
-        for (uint64_t big = __ballot(i < c1 && vt > 8ull); big; big &= big - 1) {
-            const int l = __builtin_ctzll(big);
-            const unsigned long long tl = __shfl(to, l, 64), vl = __shfl(vt, l, 64);
-            const unsigned long long te = tl + vl < cap ? tl + vl : cap;
-            for (unsigned long long k = tl + 8ull + (unsigned long long)lane; k < te; k += 64ull)
-                a.tile_chunk[k] = (uint32_t)(c + 64 * w + l);
-        }
-        base += ws[0] + ws[1] + ws[2] + ws[3];
-        tbase += wt[0] + wt[1] + wt[2] + wt[3];
-        __syncthreads();
-    }
-}
-
-// ---------------------------------------------------------------------------
-// K3: spawning. Attempts are numbered globally; a workgroup takes a tile of
-// consecutive attempts, stages the keys and populations of the chunk(s)
-// covering it in LDS with a prefix sum of |C|, and each thread walks a run of
-// consecutive attempts: (slot, walker ordinal k) by one binary search, then
-// k+1 / next occupied slot.
+// K3: spawning. Every wavefront works on its own, with no workgroup barrier: it takes a
+// tile (consecutive attempts of one bucket), stages the bucket's entries in LDS with the
+// first attempt of each, and runs through the attempts 64 at a time. An attempt's entry is
+// found by a maximum over the lanes below it of the entries that begin there. Attempts
+// that are left over (fewer than 64) wait in registers for the next tile's, so that every
+// step but a wavefront's last one is full.
+//
+// An attempt draws its excitation and is then tested against an upper bound of its
+// acceptance probability, from a table of bounds on the matrix elements; only attempts
+// that pass are queued (per wavefront, in LDS) and evaluated 64 at a time: matrix
+// element, pgen, acceptance. A rejected attempt would have been rejected by the full
+// test too (the bound holds for every rounding), so the walkers are the same; what is
+// saved is the element's two gathers and the division for most attempts, and wavefronts
+// that run them for a few lanes only. Single excitations are queued apart.
 // ---------------------------------------------------------------------------
 
 // A spawn record into its child's bucket's slots, at the place the bucket's counter
@@ -1021,25 +1147,6 @@ __device__ __forceinline__ void put_record(const EngineArgs &a, const SysDesc &d
     put_rec(recs_of(a) + d.rec0 + (int64_t)b * d.rec_r + k, D, v, init ? 1u : 0u);
 }
 
-// Work queued in LDS by the attempt loop and drained by the whole workgroup:
-// single excitations (their matrix element is an O(N) gather loop that would
-// stall a wavefront for one lane) and accepted spawns (their merge into the
-// table is a chain of HBM round trips, overlapped with the other workgroups'
-// spawning).
-struct SingleItem {
-    det_t D;             // source determinant
-    uint32_t w0, w1, w2; // type/acceptance, electron and hole words
-    int32_t C;           // source population (sign)
-    uint32_t init;       // initiator flag of the source
-    uint32_t pad;
-};
-
-constexpr int SPAWN_GRAB = 8;    // spawn tiles per dynamic grab at most (one counter serves the chip)
-constexpr int SGL_QUEUE = 128 / FQ_DET_WORDS;   // (two words: the spawn kernel's LDS in 40 KB)
-constexpr int SPW_QUEUE = 256;
-constexpr int SGL_DRAIN = 48;     // drain the queues once they hold this many items
-constexpr int SPW_DRAIN = 192;     // (a tile adds about 30 spawns; a fuller queue is merged inline)
-
 // The acceptance uniform: the type word's uniform rescaled within the chosen
 // type's interval [0, P_double) or [P_double, 1); given the type it is uniform
 // on [0, 1) and independent of the orbital words.
@@ -1048,8 +1155,10 @@ __device__ __forceinline__ double accept_uniform(const SysDesc &d, uint32_t w0) 
     return u < d.p_double ? u * d.inv_p_double : (u - d.p_double) * d.inv_p_single;
 }
 
+// Walkers spawned (signed; 0: none) from a walker of a determinant with negative (neg) or
+// positive population.
 __device__ __forceinline__ int32_t accept(const SysDesc &d, double hel, double pgen, double ua,
-                                          int32_t C, uint32_t *status) {
+                                          bool neg, uint32_t *status) {
     const double pr = (d.tau * fabs(hel)) / pgen;
     const double fl = floor(pr);
     if (fl > 1073741824.0) {
@@ -1057,334 +1166,501 @@ __device__ __forceinline__ int32_t accept(const SysDesc &d, double hel, double p
         return 0;
     }
     const int32_t m = (int32_t)fl + (ua < pr - fl ? 1 : 0);
-    return ((C > 0) == (hel > 0.0)) ? -m : m;
+    return (!neg == (hel > 0.0)) ? -m : m;
 }
 
-struct SpawnQueues {
-    SingleItem sgl[SGL_QUEUE];
-    det_t spd[SPW_QUEUE];
-    int2 spv[SPW_QUEUE];   // (signed walkers, initiator flag)
-    int nsgl, nspw, sys;
-    uint32_t dead;             // the drained system's status, as seen by thread 0
+constexpr int SPAWN_WAVES = 4;    // wavefronts of a k_spawn workgroup
+// Queue items of a wavefront: double excitations from the bottom, singles from the top;
+// at most 63 and SGL_DRAIN - 1 before a step adds up to 64.
+constexpr int SGL_DRAIN = FQ_DET_WORDS == 1 ? 48 : 32;   // (two words: four workgroups in LDS)
+constexpr int SPAWN_QUEUE = SGL_DRAIN + 128;
+static_assert(63 + SGL_DRAIN - 1 + 64 <= SPAWN_QUEUE, "a step's attempts fit the queue");
+constexpr uint32_t ENT_NEG = 1u << 31, ENT_INIT = 1u << 30, ENT_FIRST = 1u << 29;
+constexpr uint32_t ENT_REL = (1u << 22) - 1u;
+constexpr int TILE_MAX = 1 << TILE_MAX_SH(FQ_DET_WORDS);
+constexpr int ORB_BITS = 7;       // orbital numbers in a queue item
+constexpr uint32_t ORB_MASK = (1u << ORB_BITS) - 1u;
+
+// Bound tables in LDS for one-word determinants (with two words they would take a
+// workgroup per CU).
+constexpr int BOUND_N = 32 * FQ_DET_WORDS;
+constexpr int BOUND_LDS = FQ_DET_WORDS == 1 ? BOUND_N * BOUND_N : 2;
+
+template <bool PLAIN>
+struct SpawnWave {
+    det_t key[BQ];                   // staged entries: determinant,
+    uint32_t ent[BQ];                // its first attempt in the tile | sign | initiator | it
+                                     // began before the tile (k0 attempts earlier)
+    alignas(8) uint8_t head[TILE_MAX];   // entry that begins at an attempt (0: none, or entry 0)
+    det_t qd[SPAWN_QUEUE];           // queued attempts: determinant,
+    uint2 qm[SPAWN_QUEUE];           // type word (deferred single: ordinal), orbitals | flags
+    det_t cm[PLAIN ? 1 : NCLASS];    // class masks of the system
+    uint32_t k0;
 };
 
-// Add the wavefront's spawning events of system s to its counter and reset the
-// per-thread tallies. The counter is one address for the whole chip, so it is
-// touched once per wavefront per system, not per tile.
-__device__ __forceinline__ void flush_spawn_count(unsigned long long *counter,
-                                                  unsigned long long &spawned) {
-    const unsigned long long ws = wave_sum(spawned);
-    if ((threadIdx.x & 63) == 0 && ws) atomicAdd(counter, ws);
-    spawned = 0;
+__device__ __forceinline__ float half_to_float(uint16_t h) {
+    _Float16 x;
+    __builtin_memcpy(&x, &h, 2);
+    return (float)x;
+}
+// x0 y0 + x1 y1 of half-precision numbers, in single precision (no subnormals among them).
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float half_dot2(uint16_t x0, uint16_t x1, uint16_t y0, uint16_t y1) {
+    const uint32_t x = (uint32_t)x0 | ((uint32_t)x1 << 16), y = (uint32_t)y0 | ((uint32_t)y1 << 16);
+    return __builtin_amdgcn_fdot2(__builtin_bit_cast(half2_t, x), __builtin_bit_cast(half2_t, y), 0.0f, false);
 }
 
-// Drain both queues of system s with the whole workgroup (call uniformly).
-// cm_lds: the LDS copy of the system's class masks (the descriptor's own copy is
-// read instead for one-word determinants). PLAIN: as for k_spawn.
-template <bool PLAIN>
-__device__ void drain_queues(SpawnQueues &Q, const EngineArgs &a, const SysDesc &d, int s,
-                             const uint32_t *sel8, const double *recip, const det_t *cm_lds,
-                             unsigned long long &spawned) {
-    const int t = threadIdx.x;
-#if FQ_DET_WORDS == 1
-    const det_t *const cmk = d.cmask;
-#else
-    const det_t *const cmk = cm_lds;
-#endif
-    uint32_t *status = &a.status[s];
-    // a system whose record buffer overflowed re-runs the iteration: drop its queued work
-    // (decided once for the workgroup: other workgroups may set the status meanwhile)
-    if (t == 0) Q.dead = *(volatile uint32_t *)status;
-    __syncthreads();
-    const bool dead = Q.dead != 0;
-    const int nsgl = dead ? 0 : (Q.nsgl < SGL_QUEUE ? Q.nsgl : SGL_QUEUE);
-    for (int j = t; j < nsgl; j += blockDim.x) {
-        const SingleItem it = Q.sgl[j];
-        Excit ex;
-        const bool ok = PLAIN || d.n_class == 2
-                            ? excite_single(d, ClassView<true>{valid_of(d), nullptr}, it.D, it.w1, it.w2, sel8, ex)
-                            : excite_single(d, ClassView<false>{valid_of(d), cmk}, it.D, it.w1, it.w2, sel8, ex);
-        if (!ok || (!PLAIN && d.space && !in_space(d, ex.det))) continue;
-        if (!PLAIN && d.hphf) {
-            if (!to_function(d, cmk, recip, it.D, ex)) continue;
+// One queued attempt of system s (item i of a wavefront's queue; kind 0: double, 1: single):
+// matrix element, pgen, acceptance, record. Returns whether it spawned.
+template <bool PLAIN, int KIND>
+__device__ __forceinline__ bool evaluate(const EngineArgs &a, const SysDesc *__restrict__ desc, int s,
+                                     const SpawnSys &hs, const uint8_t *s_sel8,
+                                     const double *s_recip, const det_t *cm,
+                                     const SpawnWave<PLAIN> &Q, int i) {
+    const SysDesc &d = desc[s];
+    uint32_t *const status = &a.status[s];
+    const bool defer = hs.defer != 0, c1 = PLAIN || hs.c1 != 0, coupled = !PLAIN && hs.coupled != 0;
+    const ClassView<true> cv1{hs.valid, nullptr};
+    const ClassView<false> cvg{hs.valid, cm};
+    const det_t D = Q.qd[i];
+    const uint2 it = Q.qm[i];
+    const bool neg = (it.y >> 28) & 1u;
+    uint32_t w0 = it.x;
+    Excit ex;
+    bool ok = true;
+    if (KIND == 0) {
+        const int p = (int)(it.y & ORB_MASK), q = (int)((it.y >> ORB_BITS) & ORB_MASK);
+        const int ia = (int)((it.y >> (2 * ORB_BITS)) & ORB_MASK);
+        const int ib = (int)((it.y >> (3 * ORB_BITS)) & ORB_MASK);
+        ex.det = D ^ DBIT(p) ^ DBIT(q) ^ DBIT(ia) ^ DBIT(ib);
+        if (c1)
+            ex.pgen = ((p ^ q) & 1) == 0 ? (p & 1 ? d.pgen_c1[1] : d.pgen_c1[0])
+                                         : (ia & 1 ? d.pgen_c1[3] : d.pgen_c1[2]);
+        else
+            ex.pgen = pgen_target(d, cm, s_recip, D, ex.det);
+        if (!coupled) ex.hel = hel_double(d, D, p, q, ia, ib);
+    } else {
+        if (defer) {
+            // (the ordinal was queued: the same words again)
+            const uint4 w = spawn_words(hs, D, it.x);
+            w0 = w.x;
+            ok = c1 ? excite_single(d, cv1, D, w.y, w.z, s_sel8, ex)
+                    : excite_single(d, cvg, D, w.y, w.z, s_sel8, ex);
         } else {
-            ex.hel = hel_single(d, it.D, ex.p, ex.a);
+            ex.p = (int)(it.y & ORB_MASK);
+            ex.a = (int)((it.y >> ORB_BITS) & ORB_MASK);
+            ex.det = D ^ DBIT(ex.p) ^ DBIT(ex.a);
+            ex.pgen = c1 ? single_pgen(d, cv1, D, ex.p) : single_pgen(d, cvg, D, ex.p);
         }
-        const double hel = ex.hel;
-        if (hel == 0.0) continue;
-        const int32_t v = accept(d, hel, ex.pgen, accept_uniform(d, it.w0), it.C, status);
-        if (v == 0) continue;
-        ++spawned;
-        const det_t Dn = ex.det;
-        const bool init = it.init != 0;
-        if (Dn == ref_of(d)) {
-            __hip_atomic_fetch_add(&a.d0acc[s], (long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            continue;
-        }
-        const int qq = atomicAdd(&Q.nspw, 1);
-        if (qq < SPW_QUEUE) {
-            Q.spd[qq] = Dn;
-            Q.spv[qq] = make_int2(v, init ? 1 : 0);
-        } else {
-            put_record(a, d, Dn, v, init, status);
-        }
+        if (ok && !coupled) ex.hel = hel_single(d, D, ex.p, ex.a);
     }
-    __syncthreads();
-    const int nspw = dead ? 0 : (Q.nspw < SPW_QUEUE ? Q.nspw : SPW_QUEUE);
-    for (int j = t; j < nspw; j += blockDim.x) {
-        const int2 v = Q.spv[j];
-        put_record(a, d, Q.spd[j], v.x, v.y != 0, status);
-    }
-    __syncthreads();
-    if (t == 0) {
-        Q.nsgl = 0;
-        Q.nspw = 0;
-    }
-    __syncthreads();
+    if (!PLAIN && ok && d.space && !in_space(d, ex.det)) ok = false;
+    if (!PLAIN && ok && coupled) ok = to_function(d, cm, s_recip, D, ex);
+    if (!ok || ex.hel == 0.0) return false;
+    const int32_t v = accept(d, ex.hel, ex.pgen, accept_uniform(d, w0), neg, status);
+    if (v == 0) return false;
+    if (ex.det == ref_of(d))
+        __hip_atomic_fetch_add(&a.d0acc[s], (long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+        put_record(a, d, ex.det, v, ((it.y >> 29) & 1u) != 0u, status);
+    return true;
 }
 
-// Last index i < n with v[i] <= x, for v non-decreasing with v[0] <= x, by a
-// whole wavefront: 64 samples per round, so 2^17 entries take three dependent
-// loads instead of seventeen. Call with all 64 lanes active.
-__device__ __forceinline__ int64_t last_le(const unsigned long long *v, int64_t n,
-                                           unsigned long long x, int lane) {
-    int64_t lo = 0, hi = n;
-    while (hi - lo > 64) {
-        const int64_t step = (hi - lo + 63) >> 6;
-        const int64_t i = lo + (int64_t)lane * step;
-        const bool le = i < hi && v[i] <= x;
-        const int k = __popcll(__ballot(le)) - 1;   // samples <= x form a prefix of lanes
-        lo = lo + (int64_t)k * step;
-        hi = lo + step < hi ? lo + step : hi;
-    }
-    const int64_t i = lo + lane;
-    const bool le = i < hi && v[i] <= x;
-    return lo + __popcll(__ballot(le)) - 1;
-}
-
-// At most 80 VGPRs: six wavefronts per SIMD (the LDS use allows six workgroups per CU);
-// four with two-word determinants (more registers and LDS per attempt).
+// One-word determinants: at most 96 VGPRs, five wavefronts per SIMD (the LDS allows five
+// workgroups per CU); four with two words.
 // PLAIN: every system of the launch has no point group, no restricted space and plain
 // determinants (EngineArgs::plain), so those branches are compiled out.
+#define SPAWN_WPE(PLAIN) (FQ_DET_WORDS == 1 ? 5 : 4)
 template <bool PLAIN>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FQ_DET_WORDS == 1 ? 6 : 4, FQ_DET_WORDS == 1 ? 6 : 4)))
-void k_spawn(EngineArgs a, const SysDesc *__restrict__ desc) {
-    // inclusive sums of |C| over the staged entries, relative to the tile's first attempt
-    // and clamped to 32 bits (the entries a thread can start in stay exact: a tile has at
-    // most 2^20 attempts and |C| < 2^31)
-    __shared__ int32_t s_rel[CHUNK];
-    __shared__ det_t s_det[CHUNK];
-    __shared__ int32_t s_pop[CHUNK];
-    __shared__ unsigned long long s_wsum[4];   // per wavefront: walkers | entries << 48
-    __shared__ long long s_c;
-    __shared__ unsigned int s_tile;
-    __shared__ double s_recip[65];
-    __shared__ uint32_t s_sel8[256];
-    __shared__ det_t s_cm[NCLASS];
-    __shared__ SpawnQueues Q;
-    const unsigned long long n_tiles = a.total[1];
-    const int64_t nch = *a.nchunks;
-    const unsigned long long tile = (unsigned long long)a.tile;
-    const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
-    if (t > 0 && t <= 64) s_recip[t] = 1.0 / (double)t;
-    s_sel8[t] = sel8_entry((uint32_t)t);
-    if (t == 0) {
-        s_recip[0] = 0.0;
-        Q.nsgl = 0;
-        Q.nspw = 0;
-        Q.sys = -1;
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPAWN_WPE(PLAIN), SPAWN_WPE(PLAIN))))
+void k_spawn(EngineArgs a, const SysDesc *__restrict__ desc, int first) {
+    __shared__ SpawnWave<PLAIN> L[SPAWN_WAVES];
+    __shared__ uint8_t s_sel8[8 * 256];
+    __shared__ double s_recip[PLAIN ? 1 : 65];
+    __shared__ uint16_t s_bound[BOUND_LDS];
+    __shared__ unsigned long long s_spawned;   // spawning events of system s_tsys,
+    __shared__ int s_done;                     // wavefronts that have added theirs
+    __shared__ unsigned int s_len[NLIST];      // listed tiles per list
+    __shared__ int s_nd[SPAWN_WAVES], s_ns[SPAWN_WAVES];   // items left queued at the end
+    // (everything but the lanes' own attempts is uniform, and has to be seen to be: the
+    // descriptor's fields are then scalar loads)
+    const int t = threadIdx.x, lane = t & 63, wid = __builtin_amdgcn_readfirstlane(t >> 6);
+    SpawnWave<PLAIN> &W = L[wid];
+    const int half = cur_half(a), h = first ? 2 : half;
+    if (blockIdx.x == 0 && t < NLIST) {   // k_post's counters of this iteration
+        a.work[CTR_POST(t)] = 0u;
+        a.total[CTR_TILES(half ^ 1, t)] = 0ull;
+        if (t == 0) a.total[CTR_UNLISTED(half ^ 1)] = 0ull;
     }
+    // the lane's list's length, and over all lists
+    unsigned int n_list = 0;
+    if (lane < NLIST) {
+        const unsigned long long n = a.total[CTR_TILES(h, lane)];
+        n_list = (unsigned int)(n < (unsigned long long)a.list_cap ? n : (unsigned long long)a.list_cap);
+    }
+    const unsigned int n_tiles =
+        (unsigned int)__builtin_amdgcn_readlane((int)wave_incl_sum32(n_list), 63);
+    if (t < NLIST) s_len[t] = n_list;
+    if (!PLAIN && t > 0 && t <= 64) s_recip[t] = 1.0 / (double)t;
+    for (uint32_t k = 0; k < 8; ++k) s_sel8[(k << 8) | t] = sel8_entry(k, (uint32_t)t);
+    if (t == 0) {
+        if (!PLAIN) s_recip[0] = 0.0;
+        s_spawned = 0ull;
+        s_done = 0;
+    }
+    // Tiles per share: a wavefront's whole part in one when it is small (neighbouring tiles
+    // are mostly of one system, and a change of system empties the queues), an eighth of it
+    // when it is large (so that the faster wavefronts take more).
+    const unsigned int n_waves = SPAWN_WAVES * gridDim.x;
+    const unsigned int per_wave = (n_tiles + n_waves - 1u) / n_waves;
+    Handout ho{a.work + CTR_SPAWN(0), s_len, SPAWN_WAVES,
+               per_wave < 4u ? (per_wave > 0u ? per_wave : 1u)
+                             : per_wave < 32u ? 4u : per_wave < 128u ? per_wave / 8u : 16u,
+               (int)(blockIdx.x & (NLIST - 1)), true};
+    // The system of the workgroup's first tile: its bound table serves from LDS (a tile of
+    // another system reads its own from memory), and what is left queued of it at the end
+    // is evaluated together.
+    const int home = (int)(blockIdx.x & (NLIST - 1));
+    const unsigned int first_tile = (blockIdx.x / NLIST) * SPAWN_WAVES * ho.share;
+    const uint64_t any = __ballot(n_list > 0u);
+    const bool own = first_tile < (unsigned int)__builtin_amdgcn_readlane((int)n_list, home);
+    const int tlist = own ? home : any ? __builtin_ctzll(any) : -1;
+    const int tsys = tlist >= 0 ? __builtin_amdgcn_readfirstlane(ld_uniform(
+                                      a.tiles + 4 * ((int64_t)tlist * a.list_cap + (own ? first_tile : 0u))))
+                                : -1;
+    if (FQ_DET_WORDS == 1 && tsys >= 0)
+        for (int i = t; i < BOUND_LDS / 2; i += 256)
+            ((uint32_t *)s_bound)[i] = *gp((const uint32_t *)desc[tsys].bound + i);
     __syncthreads();
-    unsigned int next_tile = 0, grab_end = 0;   // wavefront 0's current grab of tiles
-    // tiles per grab: SPAWN_GRAB when every workgroup gets many, fewer for small launches
-    // (so that the tiles still spread over the workgroups)
-    const unsigned long long per_wg = n_tiles / (4ull * gridDim.x);
-    const unsigned int grab = per_wg >= (unsigned long long)SPAWN_GRAB ? (unsigned int)SPAWN_GRAB
-                              : per_wg > 0ull ? (unsigned int)per_wg : 1u;
-    unsigned long long spawned = 0;             // this thread's spawning events of system Q.sys
+
+    const unsigned int rank = (blockIdx.x / NLIST) * SPAWN_WAVES + (unsigned int)wid;
+    unsigned int g_at = 0, g_n = 0;    // the rest of the share at hand
+    // Buckets whose tiles are not listed (a list was too small), from a counter of their own.
+    int mode = 0;                      // 0: listed tiles, 1: unlisted buckets, 2: none left
+    uint32_t f_lb = 0, f_j = 0, f_n = 0;
+    int f_sys = 0, f_ne = 0;
+    unsigned long long f_x = 0;
+
+    // The tile at hand (uniform): system, bucket, number in the bucket, attempts, entries.
+    int ts = -1, t_ne = 0;
+    uint32_t t_lb = 0, t_j = 0;
+    int t_n = 0;
+    bool t_big = false;
+    bool have = false, run = false, end = false;   // fetched, staged, nothing left to fetch
+    int cur = -1;                      // system of the queued work and tallies
+    int nd = 0, ns = 0;                // queued doubles and singles
+    uint32_t spawned = 0;              // this lane's spawning events of system cur
+    SpawnSys hs{};
+    bool stopped = false;
+    int xs = 0;                        // attempt of the tile that lane 0 takes next
+    uint32_t sl0 = 0, k0 = 0;          // last entry of the step before; W.k0
+    int np = 0;                        // attempts waiting in lanes 0 .. np - 1:
+    det_t pD = det_t(0ull);            // determinant, ordinal, flags
+    uint32_t pk = 0, pf = 0;
+
     for (;;) {
-        // Tiles never cross a chunk: chunk c owns ceil(N_c / tile) consecutive tiles.
-        // They are handed out dynamically, so no workgroup waits for a second round.
-        if (wid == 0) {
-            if (next_tile >= grab_end) {
-                unsigned int g = 0;
-                if (lane == 0) g = atomicAdd(&a.work[0], grab);
-                next_tile = __shfl(g, 0, 64);
-                grab_end = next_tile + grab;
+        if (!have && !run && !end) {
+            // the next tile
+            if (mode == 0) {
+                if (g_n == 0u && !handout_next(ho, rank, g_at, g_n)) {
+                    mode = a.total[CTR_UNLISTED(h)] > 0ull ? 1 : 2;
+                } else {
+                    const v4i32 e = ld_uniform((const v4i32 *)(
+                        a.tiles + 4 * ((int64_t)ho.list * a.list_cap + (int64_t)g_at)));
+                    ts = __builtin_amdgcn_readfirstlane(e.x);
+                    t_lb = (uint32_t)__builtin_amdgcn_readfirstlane(e.y);
+                    t_j = (uint32_t)__builtin_amdgcn_readfirstlane(e.z);
+                    const uint32_t nn = (uint32_t)__builtin_amdgcn_readfirstlane(e.w);
+                    t_n = (int)(nn & ((1u << TILE_ENT_SHIFT) - 1u));
+                    t_ne = (int)((nn & ~TILE_BIG) >> TILE_ENT_SHIFT);
+                    t_big = (nn & TILE_BIG) != 0u;
+                    ++g_at;
+                    --g_n;
+                    have = true;
+                }
             }
-            const unsigned int tix = next_tile++;
-            if (lane == 0) s_tile = tix;
-            if (tix < n_tiles) {
-                const int64_t cc = tix < (unsigned long long)a.tile_cap
-                                       ? (int64_t)a.tile_chunk[tix]
-                                       : last_le(a.chunk_toff, nch, tix, lane);
-                if (lane == 0) s_c = cc;
-            }
-        }
-        __syncthreads();
-        const unsigned long long tix = s_tile;
-        const int64_t c = s_c;
-        __syncthreads();
-        if (tix >= n_tiles) break;
-        const unsigned long long off_c = a.chunk_off[c];
-        const unsigned long long nw_c = sums(a, cur_half(a))[c];
-        const unsigned long long j = tix - a.chunk_toff[c];
-        const int s = __builtin_amdgcn_readfirstlane(a.chunk_sys[c]);
-        const SysDesc &d = desc[s];
-        uint32_t *status = &a.status[s];
-        if (Q.sys != s) {
-            // queued work and tallies belong to another system: finish them first
-            if (Q.sys >= 0) {
-                const int qs = __builtin_amdgcn_readfirstlane(Q.sys);
-                if (Q.nsgl > 0 || Q.nspw > 0) drain_queues<PLAIN>(Q, a, desc[qs], qs, s_sel8, s_recip, s_cm, spawned);
-                flush_spawn_count(&a.spawns[qs], spawned);
-            }
-            __syncthreads();
-            if (t == 0) Q.sys = s;
-            // the class masks of the new system (not read by the plain variant), ordered
-            // before use by the barrier below
-            if (!PLAIN && t < NCLASS) s_cm[t] = cmask_of(d, t);
-        }
-        // Stage the chunk's entries that hold walkers (its four buckets, one per
-        // wavefront, four entries per lane), compacted, with the inclusive prefix sum
-        // of |C|. Only the lanes over a bucket's entries read (the entries are packed
-        // at the front of the bucket).
-        const int64_t lb = (int64_t)a.chunk_local[c] * BPC + wid;
-        const int64_t base = lb * BQ + 4 * lane;
-        const int n_b = d.bcnt[lb] - 4 * lane;
-        int4 pv = make_int4(0, 0, 0, 0);
-#if FQ_DET_WORDS == 1
-        ulonglong2 k01 = make_ulonglong2(0ull, 0ull), k23 = make_ulonglong2(0ull, 0ull);
-        if (n_b > 0) {
-            pv = gload_i4(d.pop + base);
-            k01 = gload_u2(d.key + base);
-            k23 = gload_u2(d.key + base + 2);
-        }
-#else
-        det_t kk[4] = {det_t(0ull), det_t(0ull), det_t(0ull), det_t(0ull)};
-        if (n_b > 0) {
-            pv = gload_i4(d.pop + base);
-            for (int u = 0; u < 4; ++u) kk[u] = ldk(keys_of(d) + base + u);
-        }
-#endif
-        const int32_t pa[4] = {0 < n_b ? pv.x : 0, 1 < n_b ? pv.y : 0, 2 < n_b ? pv.z : 0,
-                               3 < n_b ? pv.w : 0};
-#if FQ_DET_WORDS == 1
-        const uint64_t ka[4] = {k01.x, k01.y, k23.x, k23.y};
-#else
-        const det_t ka[4] = {kk[0], kk[1], kk[2], kk[3]};
-#endif
-        const int nocc = (pa[0] != 0) + (pa[1] != 0) + (pa[2] != 0) + (pa[3] != 0);
-        unsigned long long run = 0;
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            run += (unsigned long long)(pa[u] < 0 ? -(int64_t)pa[u] : (int64_t)pa[u]);
-        // one scan of both: a lane's walkers (< 2^33) with its entry count (<= 4) above
-        // bit 48; over the workgroup the sums stay below 2^41 and 2^10
-        const unsigned long long mine = run | ((unsigned long long)nocc << 48);
-        const unsigned long long xs = wave_incl_scan(mine);
-        if (lane == 63) s_wsum[wid] = xs;
-        __syncthreads();
-        unsigned long long before = xs - mine;
-        for (int w = 0; w < wid; ++w) before += s_wsum[w];
-        unsigned long long wbefore = before & ((1ull << 48) - 1ull);
-        int pos = (int)(before >> 48);
-        const int n_occ = (int)((s_wsum[0] + s_wsum[1] + s_wsum[2] + s_wsum[3]) >> 48);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (pa[u] == 0) continue;
-            wbefore += (unsigned long long)(pa[u] < 0 ? -(int64_t)pa[u] : (int64_t)pa[u]);
-            s_pop[pos] = pa[u];
-            s_det[pos] = ka[u];
-            const long long rel = (long long)wbefore - (long long)(j * tile);
-            s_rel[pos] = (int32_t)(rel < INT32_MIN ? INT32_MIN : rel > INT32_MAX ? INT32_MAX : rel);
-            ++pos;
-        }
-        __syncthreads();
-        // This tile's attempts, split into 256 consecutive runs whose lengths differ by
-        // at most one (the longer runs first), so no wavefront idles lanes at the end.
-        const unsigned long long lo_t = off_c + j * tile;
-        const unsigned long long hi_t = (lo_t + tile < off_c + nw_c) ? lo_t + tile : off_c + nw_c;
-        const unsigned long long n_t = hi_t - lo_t;   // <= tile <= 2^20
-        const unsigned long long q_t = n_t >> 8, r_t = n_t & 255ull;
-        const unsigned long long tt = (unsigned long long)t;
-        unsigned long long at = lo_t + tt * q_t + (tt < r_t ? tt : r_t);
-        const unsigned long long at_end = at + q_t + (tt < r_t ? 1ull : 0ull);
-        // no attempts for a system that has stopped this iteration (its record buffer overflowed)
-        const bool stopped = __builtin_amdgcn_readfirstlane(*(volatile uint32_t *)status) != 0;
-        const bool defer = d.p_double >= 0.5;   // singles are rare: queue them
-        const bool c1 = PLAIN || d.n_class == 2;           // no point group: classes are the spins
-        const bool restricted = !PLAIN && d.space != 0;    // children outside the space are null
-        const bool coupled = !PLAIN && d.hphf != 0;        // walkers on spin-coupled functions
-        ClassView<true> cv1{valid_of(d), nullptr};
-        ClassView<false> cvg{valid_of(d), s_cm};
-        if (at < at_end && !stopped) {
-            const int32_t xr = (int32_t)(at - lo_t);   // this thread's first attempt in the tile
-            int sl = 0, hi = n_occ - 1;  // first occupied entry with inclusive sum past it
-            while (sl < hi) {
-                const int mid = (sl + hi) >> 1;
-                if (s_rel[mid] > xr) hi = mid;
-                else sl = mid + 1;
-            }
-            uint32_t k = sl ? (uint32_t)(xr - s_rel[sl - 1]) : (uint32_t)(at - off_c);
-            for (;;) {
-                const int32_t C = s_pop[sl];
-                const det_t D = s_det[sl];
-                const int64_t absC = C < 0 ? -(int64_t)C : (int64_t)C;
-                const bool init = absC > d.n_a || D == ref_of(d);
-                const uint4 w = draw_words(d.seed, D, k, d.iter, 0u);
-                Excit ex;
-                int r = c1 ? excite(d, cv1, D, w, s_recip, s_sel8, defer, ex)
-                           : excite(d, cvg, D, w, s_recip, s_sel8, defer, ex);
-                if (r == EX_SINGLE_DEFERRED) {
-                    const int q = atomicAdd(&Q.nsgl, 1);
-                    if (q < SGL_QUEUE) {
-                        Q.sgl[q] = SingleItem{D, w.x, w.y, w.z, C, init ? 1u : 0u, 0u};
-                        r = EX_NULL;
+            if (mode == 1) {
+                if (f_j >= f_n) {
+                    unsigned int g = 0;
+                    if (lane == 0) g = atomicAdd(&a.work[CTR_FALLBACK], 1u);
+                    g = (unsigned int)__builtin_amdgcn_readfirstlane((int)g);
+                    if ((unsigned long long)g >= a.total[CTR_UNLISTED(h)]) {
+                        mode = 2;
                     } else {
-                        // queue full: generate it here
-                        const bool ok = c1 ? excite_single(d, cv1, D, w.y, w.z, s_sel8, ex)
-                                           : excite_single(d, cvg, D, w.y, w.z, s_sel8, ex);
-                        r = ok ? EX_OK : EX_NULL;
-                        if (ok) ex.hel = hel_single(d, D, ex.p, ex.a);
+                        const uint32_t gb = a.unlisted[g];
+                        f_sys = __builtin_amdgcn_readfirstlane(a.chunk_sys[gb / BPC]);
+                        f_lb = (uint32_t)a.chunk_local[gb / BPC] * BPC + gb % BPC;
+                        f_ne = desc[f_sys].bcnt[f_lb];
+                        f_x = bucket_walkers(desc[f_sys], f_lb, f_ne);
+                        f_n = (uint32_t)((f_x + (1ull << a.wsh) - 1ull) >> a.wsh);
+                        f_j = 0u;
                     }
                 }
-                if (r == EX_OK && restricted && !in_space(d, ex.det)) r = EX_NULL;
-                if (r == EX_OK && coupled && !to_function(d, s_cm, s_recip, D, ex)) r = EX_NULL;
-                if (r == EX_OK) {
-                    if (ex.hel != 0.0) {
-                        const int32_t v = accept(d, ex.hel, ex.pgen, accept_uniform(d, w.x), C, status);
-                        if (v != 0 && ex.det == ref_of(d)) {
-                            ++spawned;
-                            __hip_atomic_fetch_add(&a.d0acc[s], (long long)v, __ATOMIC_RELAXED,
-                                                   __HIP_MEMORY_SCOPE_AGENT);
-                        } else if (v != 0) {
-                            ++spawned;
-                            const int q = atomicAdd(&Q.nspw, 1);
-                            if (q < SPW_QUEUE) {
-                                Q.spd[q] = ex.det;
-                                Q.spv[q] = make_int2(v, init ? 1 : 0);
-                            } else {
-                                put_record(a, d, ex.det, v, init, status);
-                            }
+                if (mode == 1 && f_j < f_n) {
+                    const unsigned long long rest = f_x - ((unsigned long long)f_j << a.wsh);
+                    ts = __builtin_amdgcn_readfirstlane(f_sys);
+                    t_lb = (uint32_t)__builtin_amdgcn_readfirstlane((int)f_lb);
+                    t_j = (uint32_t)__builtin_amdgcn_readfirstlane((int)f_j);
+                    t_n = __builtin_amdgcn_readfirstlane(
+                        (int)(rest < (1ull << a.wsh) ? (uint32_t)rest : 1u << a.wsh));
+                    t_ne = __builtin_amdgcn_readfirstlane(f_ne);
+                    t_big = true;
+                    ++f_j;
+                    have = true;
+                }
+            }
+            if (mode == 2) end = true;
+        }
+        // waiting and queued work belongs to the current system: finished before another
+        // one's tile
+        // (at the end, what is left of the table's system is evaluated by the workgroup)
+        const bool flush = !run && (end || (have && ts != cur));
+        const bool rest = end && cur == tsys;
+        if (flush && np == 0 && (rest || (nd == 0 && ns == 0))) {
+            if (rest) break;
+            if (cur >= 0) {
+                const unsigned long long w = wave_sum((unsigned long long)spawned);
+                spawned = 0;
+                if (lane == 0 && w) {
+                    if (cur == tsys)
+                        atomicAdd(&s_spawned, w);
+                    else
+                        atomicAdd(&a.spawns[cur * SPAWN_SLOTS + (blockIdx.x & (SPAWN_SLOTS - 1))], w);
+                }
+            }
+            if (end) break;
+            cur = ts;
+            hs = spawn_sys(desc[uni((uint32_t)cur)]);
+            // no attempts for a system that has stopped (paused after a spill). A plain load:
+            // reading past the caches, once per tile, was one address for the whole chip
+            // (60 to 100 us of an iteration of eight systems).
+            stopped = uni(a.status[uni((uint32_t)cur)]) != 0u;
+            if (!PLAIN && lane < NCLASS) W.cm[lane] = cmask_of(desc[cur], lane);
+        }
+        const int s = __builtin_amdgcn_readfirstlane(cur >= 0 ? cur : 0);
+        const SysDesc &d = desc[s];
+        if (have && ts == cur) {
+            // Stage the bucket's entries (entry u 64 + lane; packed, so no compaction).
+            have = false;
+            run = true;
+            if (stopped) t_n = 0;
+            const int64_t base = (int64_t)t_lb * BQ + lane;
+            const int R = (t_ne + 63) >> 6;
+            int32_t pv[4] = {0, 0, 0, 0};
+            det_t kv[4] = {det_t(0ull), det_t(0ull), det_t(0ull), det_t(0ull)};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (u >= R) break;
+                if ((u << 6) + lane < t_ne) {
+                    pv[u] = *gp(d.pop + base + (u << 6));
+                    kv[u] = ldk(keys_of(d) + base + (u << 6));
+                }
+            }
+            static_assert(TILE_MAX <= 64 * 8, "one 8-byte store per lane clears the heads");
+            if (8 * lane < TILE_MAX) ((uint64_t *)W.head)[lane] = 0ull;
+            wave_sync();
+            // the first attempt of each entry, relative to the tile's first (in 32 bits when
+            // the bucket's walkers fit, which the tile says)
+            const unsigned long long off = (unsigned long long)t_j << a.wsh;
+            unsigned long long before = 0;
+            bool k0_here = false;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (u >= R) break;
+                const uint32_t ab = (uint32_t)(pv[u] < 0 ? -pv[u] : pv[u]);
+                int32_t st, en;
+                if (!t_big) {
+                    const uint32_t incl = wave_incl_sum32(ab);
+                    en = (int32_t)((uint32_t)before - (uint32_t)off + incl);
+                    st = en - (int32_t)ab;
+                    before += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+                } else {
+                    const unsigned long long incl = wave_incl_scan((unsigned long long)ab);
+                    const long long e64 = (long long)(before + incl) - (long long)off;
+                    const long long s64 = e64 - (long long)ab;
+                    const long long lim = 1ll << 30;
+                    en = (int32_t)(e64 > lim ? lim : e64 < -lim ? -lim : e64);
+                    st = (int32_t)(s64 > lim ? lim : s64 < -2 * lim ? -2 * lim : s64);
+                    before += __shfl(incl, 63, 64);
+                }
+                const int e = (u << 6) + lane;
+                if (e < t_ne) {
+                    const bool init = (int64_t)ab > d.n_a || kv[u] == ref_of(d);
+                    W.key[e] = kv[u];
+                    W.ent[e] = (st < 0 ? ENT_FIRST : (uint32_t)st & ENT_REL) | (pv[u] < 0 ? ENT_NEG : 0u) |
+                               (init ? ENT_INIT : 0u);
+                    if (ab != 0u && en > 0 && st < t_n) W.head[st < 0 ? 0 : st] = (uint8_t)e;
+                    if (st <= 0 && en > 0) {
+                        W.k0 = (uint32_t)(-st);
+                        k0_here = true;
+                    }
+                }
+            }
+            wave_sync();
+            k0 = __ballot(k0_here) ? (uint32_t)__builtin_amdgcn_readfirstlane((int)W.k0) : 0u;
+            xs = -np;
+            sl0 = 0u;
+        }
+        const bool defer = hs.defer != 0;   // singles are rare: queued by ordinal, drawn again later
+        const bool c1 = PLAIN || hs.c1 != 0;
+        const bool coupled = !PLAIN && hs.coupled != 0;
+        const ClassView<true> cv1{hs.valid, nullptr};
+        const ClassView<false> cvg{hs.valid, W.cm};
+        // 64 attempts when that many are at hand, or the waiting ones of a system that ends
+        const int n_at = run ? t_n : 0;
+        const bool go = run ? n_at - xs >= 64 : flush && np > 0;
+        if (go || run) {
+            const int x = run ? xs + lane : lane - np;
+            const bool act = x < n_at;
+            bool qdbl = false, qsgl = false;
+            uint32_t meta = 0u, word = 0u;
+            det_t D = pD;
+            uint32_t k = pk, ent = pf;
+            if (run) {
+                // the entries of the attempts of this tile (x >= 0)
+                const bool in = act && x >= 0;
+                uint32_t hd = in ? (uint32_t)W.head[x] : 0u;
+                hd = wave_incl_max32(hd);
+                hd = hd > sl0 ? hd : sl0;
+                sl0 = (uint32_t)__builtin_amdgcn_readlane((int)hd, 63);
+                if (in) {
+                    ent = W.ent[hd];
+                    D = W.key[hd];
+                    k = (uint32_t)x - (ent & ENT_REL) + (ent & ENT_FIRST ? k0 : 0u);
+                }
+            }
+            if (!go) {
+                // fewer than 64 are left: they wait
+                pD = D;
+                pk = k;
+                pf = ent;
+                np = n_at - xs;
+                run = false;
+                continue;
+            }
+            if (run) xs += 64;
+            np = 0;
+            if (act) {
+                const uint4 w = spawn_words(hs, D, k);
+                word = w.x;
+                meta = (ent & ENT_NEG ? 1u << 28 : 0u) | (ent & ENT_INIT ? 1u << 29 : 0u);
+                if (hs.has_double && w.x <= hs.dbl_thr) {
+                    DoubleDraw x;
+                    const bool ok = c1 ? draw_double_c1(hs, D, w, s_sel8, x)
+                                       : draw_double(d, cvg, D, w, s_recip, s_sel8, x);
+                    qdbl = ok;
+                    if (defer) {
+                        // |H| <= s_pa' s_qb' (+ s_pb' s_qa' for like spins), a' of p's spin
+                        const bool sw = ((x.a ^ x.p) & 1) != 0, same = ((x.p ^ x.q) & 1) == 0;
+                        const int ap = (sw ? x.b : x.a) >> 1, bp = (sw ? x.a : x.b) >> 1;
+                        const int rp = (x.p >> 1) * BOUND_N, rq = (x.q >> 1) * BOUND_N;
+                        uint16_t t0, t1, t2, t3;
+                        if (FQ_DET_WORDS == 1 && cur == tsys) {
+                            t0 = s_bound[rp + ap];
+                            t1 = s_bound[rp + bp];
+                            t2 = s_bound[rq + bp];
+                            t3 = s_bound[rq + ap];
+                        } else {
+                            t0 = *gp(d.bound + rp + ap);
+                            t1 = *gp(d.bound + rp + bp);
+                            t2 = *gp(d.bound + rq + bp);
+                            t3 = *gp(d.bound + rq + ap);
+                        }
+                        float b = half_dot2(t0, same ? t1 : (uint16_t)0, t2, t3);
+                        if (coupled) {
+                            // the partner's element counts too where it is within reach;
+                            // otherwise sqrt2 covers a closed pair
+                            const det_t T = D ^ DBIT(x.p) ^ DBIT(x.q) ^ DBIT(x.a) ^ DBIT(x.b);
+                            b = dpopc(spin_flip(T) ^ D) <= 4 ? INFINITY : b * 1.41422f;
+                        }
+                        const float u = (float)w.x;
+                        if (c1) {
+                            const bool odd = (x.pc & 1) != 0;
+                            const float f = pick_if((x.pc & 2) != 0, pick_if(odd, hs.f3, hs.f2),
+                                                    pick_if(odd, hs.f1, hs.f0));
+                            qdbl = ok && !(u > b * f);
+                        } else {
+                            qdbl = ok && !(u * (float)x.pgen > b * hs.ft);
                         }
                     }
-                }
-                if (++at >= at_end) break;
-                if ((int64_t)(++k) >= absC) {
-                    k = 0;
-                    ++sl;
+                    meta |= (uint32_t)x.p | ((uint32_t)x.q << ORB_BITS) |
+                            ((uint32_t)x.a << (2 * ORB_BITS)) | ((uint32_t)x.b << (3 * ORB_BITS));
+                } else if (defer) {
+                    qsgl = true;
+                    word = k;
+                } else {
+                    Excit ex;
+                    const bool ok = c1 ? excite_single(d, cv1, D, w.y, w.z, s_sel8, ex)
+                                       : excite_single(d, cvg, D, w.y, w.z, s_sel8, ex);
+                    if (ok) {
+                        const int i = (ex.p >> 1) * BOUND_N + (ex.a >> 1);
+                        float b = half_to_float(FQ_DET_WORDS == 1 && cur == tsys ? s_bound[i]
+                                                                                 : *gp(d.bound + i));
+                        if (coupled) b = dpopc(spin_flip(ex.det) ^ D) <= 4 ? INFINITY : b * 1.41422f;
+                        qsgl = !((float)w.x * hs.sg_mul - hs.sg_sub > b * (hs.ft * (float)ex.nt));
+                        meta |= (uint32_t)ex.p | ((uint32_t)ex.a << ORB_BITS);
+                    }
                 }
             }
+            const uint64_t md = __ballot(qdbl), ms = __ballot(qsgl);
+            const uint64_t below = (1ull << lane) - 1ull;
+            if (qdbl) {
+                const int i = nd + __popcll(md & below);
+                W.qd[i] = D;
+                W.qm[i] = make_uint2(word, meta);
+            }
+            if (qsgl) {
+                const int i = SPAWN_QUEUE - 1 - ns - __popcll(ms & below);
+                W.qd[i] = D;
+                W.qm[i] = make_uint2(word, meta);
+            }
+            nd += __popcll(md);
+            ns += __popcll(ms);
+            wave_sync();
         }
-        __syncthreads();
-        if (Q.nsgl >= SGL_DRAIN || Q.nspw >= SPW_DRAIN) drain_queues<PLAIN>(Q, a, d, s, s_sel8, s_recip, s_cm, spawned);
+        // Evaluate what is queued: 64 at a time, all of it before another system's tile.
+        if (nd >= (flush && !rest && nd > 0 ? 1 : 64)) {
+            const int n = nd < 64 ? nd : 64;
+            nd -= n;
+            if (lane < n) spawned += evaluate<PLAIN, 0>(a, desc, s, hs, s_sel8, s_recip, W.cm, W, nd + lane);
+        }
+        if (ns >= (flush && !rest && ns > 0 ? 1 : SGL_DRAIN)) {
+            const int n = ns < 64 ? ns : 64;
+            ns -= n;
+            if (lane < n)
+                spawned += evaluate<PLAIN, 1>(a, desc, s, hs, s_sel8, s_recip, W.cm, W, SPAWN_QUEUE - 1 - ns - lane);
+        }
     }
+    // What the wavefronts left queued of the table's system, shared out evenly: a launch of
+    // few attempts per wavefront would evaluate mostly nearly empty batches.
+    if (lane == 0) {
+        s_nd[wid] = cur == tsys ? nd : 0;
+        s_ns[wid] = cur == tsys ? ns : 0;
+    }
+    if (!PLAIN && tsys >= 0 && lane < NCLASS) W.cm[lane] = cmask_of(desc[tsys], lane);
+    if (tsys >= 0) hs = spawn_sys(desc[uni((uint32_t)tsys)]);
     __syncthreads();
-    if (Q.sys >= 0) {
-        const int qs = __builtin_amdgcn_readfirstlane(Q.sys);
-        if (Q.nsgl > 0 || Q.nspw > 0) drain_queues<PLAIN>(Q, a, desc[qs], qs, s_sel8, s_recip, s_cm, spawned);
-        flush_spawn_count(&a.spawns[qs], spawned);
+    if (tsys >= 0) {
+        const int i0 = 64 * wid + lane;
+        int i = i0, v = 0;
+        while (v < SPAWN_WAVES - 1 && i >= s_nd[v]) i -= s_nd[v++];
+        if (i < s_nd[v]) spawned += evaluate<PLAIN, 0>(a, desc, tsys, hs, s_sel8, s_recip, W.cm, L[v], i);
+        i = i0;
+        v = 0;
+        while (v < SPAWN_WAVES - 1 && i >= s_ns[v]) i -= s_ns[v++];
+        if (i < s_ns[v])
+            spawned += evaluate<PLAIN, 1>(a, desc, tsys, hs, s_sel8, s_recip, W.cm, L[v], SPAWN_QUEUE - 1 - i);
+    }
+    {
+        const uint32_t w = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum32(spawned), 63);
+        if (lane == 0 && w) atomicAdd(&s_spawned, (unsigned long long)w);
+    }
+    // the workgroup's spawning events of its table's system, by the last wavefront done
+    if (lane == 0) {
+        if (atomicAdd(&s_done, 1) == SPAWN_WAVES - 1) {
+            const unsigned long long w = atomicAdd(&s_spawned, 0ull);
+            if (w) atomicAdd(&a.spawns[tsys * SPAWN_SLOTS + (blockIdx.x & (SPAWN_SLOTS - 1))], w);
+        }
     }
 }
 
@@ -1419,13 +1695,6 @@ constexpr uint32_t F_MAYBE = 2u;        // record: found the hash full in this r
 constexpr uint32_t F_DEFER = 4u;        // record: left for a later round
 constexpr uint32_t F_STAGED = 8u;       // record: holds a merged child outside the bucket
 constexpr int OWN_SHIFT = 2;            // hash slot: the record that entered the child
-
-// Orders the LDS accesses of a wavefront's lanes around it (LDS operations of one
-// wavefront complete in issue order, so no wait is needed, only no code motion).
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
 
 // Home slot: a multiplicative hash of the folded words (the determinants of one
 // bucket agree in the bits of mix64 that chose the bucket, not in these).
@@ -1713,20 +1982,24 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
     __shared__ uint8_t s_cnext[POST_WIN];            // its walkers spawn next iteration
     __shared__ int16_t s_bn[POST_WIN * BPC];         // entries per bucket
     __shared__ uint32_t s_nr[POST_WIN * BPC];        // records per bucket
-    __shared__ unsigned long long s_cnws[POST_WIN];  // the chunk's sum of |C| after the iteration
-    __shared__ int s_cdone[POST_WIN];                // wavefronts done with the chunk
+    __shared__ unsigned long long s_bnw[POST_WIN * BPC];   // walkers per bucket that spawn next
     __shared__ int s_qn, s_qsys;
     __shared__ int s_tabsys;                         // system whose pair table is staged (-1: none)
     __shared__ int s_ncl[POST_WAVES];
     __shared__ int64_t s_win;                        // first chunk of the window taken
+    __shared__ unsigned int s_len[NLIST];            // windows per list
+    __shared__ int s_list;                           // list taken from
     const int64_t nch = *a.nchunks;
     const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
     WaveLds &W = L.w[wid];
-    unsigned long long *const nws_next = sums(a, cur_half(a) ^ 1u);
-    unsigned long long *const rg_next = ranges(a, cur_half(a) ^ 1u);
-    const int64_t per_range = (nch + SCAN_G - 1) / SCAN_G;
-    const int tsh = __builtin_ctzll((unsigned long long)a.tile);
-    const unsigned long long tm = (unsigned long long)a.tile - 1ull;
+    if (blockIdx.x == 0 && t < NLIST) {   // k_spawn's counters, for the next iteration
+        a.work[CTR_SPAWN(t)] = 0u;
+        a.total[CTR_TILES(2, t)] = 0ull;
+        if (t == 0) {
+            a.work[CTR_FALLBACK] = 0u;
+            a.total[CTR_UNLISTED(2)] = 0ull;
+        }
+    }
     // Which systems take part is decided from the status at the start: bits set while
     // this kernel runs (population overflow) are fatal to their system anyway.
     for (int i = t; i < a.max_sys && i < POST_MAX_SYS; i += 256) s_stat[i] = a.status[i];
@@ -1753,16 +2026,42 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                        in_lds ? L.tab.jk : nullptr);
         __syncthreads();
     };
-    // The workgroups take windows of consecutive chunks from a shared counter (so the
+    // The workgroups take windows of consecutive chunks from shared counters (so the
     // faster ones take more): POST_WIN chunks when every workgroup gets many, fewer for
     // small launches; inside a window the wavefronts run through the chunks
-    // independently, and the last one done with a chunk writes the chunk's sum for the
-    // next iteration.
+    // independently. When it is done, its buckets' tiles are appended to the next
+    // iteration's list.
     const int64_t per_wg = nch / (4 * (int64_t)gridDim.x);
     const int gwin = per_wg >= POST_WIN ? POST_WIN : per_wg > 0 ? (int)per_wg : 1;
+    // List l holds the windows of the l-th of NLIST equal ranges of windows; the last
+    // wavefront does the taking.
+    const auto win0 = [&](int l) { return (uint32_t)((nch + gwin - 1) / gwin) * (uint64_t)l / NLIST; };
+    if (t < NLIST) s_len[t] = (unsigned int)(win0(t + 1) - win0(t));
+    if (t == 0) {
+        s_list = (int)(blockIdx.x & (NLIST - 1));
+        s_win = -1;
+    }
     for (;;) {
         __syncthreads();   // the previous window is done
-        if (t == 0) s_win = (int64_t)atomicAdd(&a.work[1], 1u) * gwin;
+        const int64_t prev0 = s_win;
+        const int prevn = prev0 < 0 ? 0 : (int)(nch - prev0 < gwin ? nch - prev0 : gwin);
+        __syncthreads();
+        if (wid == POST_WAVES - 1) {
+            unsigned int at = 0, count = 0;
+            Handout ho{a.work + CTR_POST(0), s_len, 1u, 1u, __builtin_amdgcn_readfirstlane(s_list), prev0 < 0};
+            const bool more = handout_next(ho, blockIdx.x / NLIST, at, count);
+            if (lane == 0) {
+                s_win = more ? (int64_t)(win0(ho.list) + at) * gwin : nch;
+                s_list = ho.list;
+            }
+        }
+        // list the tiles of the window just done
+        if (t < (prevn * BPC + 63) / 64 * 64) {   // (whole wavefronts)
+            const bool in = t < prevn * BPC;
+            emit_tiles(a, cur_half(a) ^ 1, (int)((prev0 / gwin) & (NLIST - 1)), prev0 * BPC + t, in ? s_csys[t / BPC] : 0,
+                       in ? (uint32_t)(s_cloc[t / BPC] * BPC + t % BPC) : 0u, in ? s_bnw[t] : 0ull,
+                       in ? s_bn[t] : 0);
+        }
         __syncthreads();
         const int64_t c0 = s_win;
         if (c0 >= nch) break;
@@ -1787,8 +2086,6 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
             s_csys[t] = live ? sc : -1;
             s_cloc[t] = a.chunk_local[c0 + t];
             s_cnext[t] = next ? 1 : 0;
-            s_cnws[t] = 0ull;
-            s_cdone[t] = 0;
         }
         uint32_t nrec = 0;
         if (t < nwin * BPC) {
@@ -2132,6 +2429,7 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                         *gp(d.pop + base + (u << 6) + lane) = npv[u];
                 if (lane == 0) {
                     d.bcnt[lb] = np_;
+                    s_bn[ci * BPC + wid] = (int16_t)np_;
                     cnt += (uint64_t)np_;
                 }
                 born = K + wave_total8(reborn);
@@ -2175,15 +2473,7 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
             if (lane == 0) {
                 a.chunk_stat[c * POST_WAVES + wid] = cs;
                 // walkers that spawn next iteration: none if the system stops after this one
-                if (s_cnext[ci] && nwb) atomicAdd(&s_cnws[ci], nwb);
-                if (atomicAdd(&s_cdone[ci], 1) == POST_WAVES - 1) {
-                    const unsigned long long x = atomicAdd(&s_cnws[ci], 0ull);
-                    nws_next[c] = x;
-                    if (x) {
-                        atomicAdd(&rg_next[c / per_range], x);
-                        atomicAdd(&rg_next[SCAN_G + c / per_range], (x + tm) >> tsh);
-                    }
-                }
+                s_bnw[ci * BPC + wid] = s_cnext[ci] ? nwb : 0ull;
             }
         }
     }
@@ -2205,7 +2495,7 @@ __global__ __launch_bounds__(256) void k_reduce(EngineArgs a) {
     const int64_t per = (d.nchunks + FIN_BLOCKS - 1) / FIN_BLOCKS;
     const int64_t lo = (int64_t)blockIdx.x * per;
     const int64_t hi = lo + per < d.nchunks ? lo + per : d.nchunks;
-    int64_t nw = 0, nd = 0, merged = 0, aborted = 0, att = 0, used = 0, born = 0;
+    int64_t nw = 0, nd = 0, merged = 0, aborted = 0, used = 0, born = 0;
     double num = 0.0;
     for (int64_t i = lo + t; i < hi; i += 256) {
         for (int w = 0; w < POST_WAVES; ++w) {
@@ -2218,14 +2508,12 @@ __global__ __launch_bounds__(256) void k_reduce(EngineArgs a) {
             born += cs.born;
             num = num + cs.num;
         }
-        att += (int64_t)sums(a, cur_half(a))[d.gchunk0 + i];
     }
     FinPart p;
     p.nw = block_sum((long long)nw, shi);
     p.nd = block_sum((long long)nd, shi);
     p.merged = block_sum((long long)merged, shi);
     p.aborted = block_sum((long long)aborted, shi);
-    p.attempts = block_sum((long long)att, shi);
     p.used = block_sum((long long)used, shi);
     p.born = block_sum((long long)born, shi);
     p.num = block_sum(num, shd);
@@ -2248,10 +2536,12 @@ __global__ __launch_bounds__(64) void k_finalize(EngineArgs a) {
     const int64_t c0 = a.c0[s];
     const int64_t merged = wave_sum((long long)p.merged);
     const int64_t aborted = wave_sum((long long)p.aborted);
-    const int64_t att = wave_sum((long long)p.attempts);
     const int64_t used = wave_sum((long long)p.used);
     const int64_t born = wave_sum((long long)p.born);
     const double num = wave_sum(p.num);
+    unsigned long long spawned = t < SPAWN_SLOTS ? a.spawns[s * SPAWN_SLOTS + t] : 0ull;
+    if (t < SPAWN_SLOTS) a.spawns[s * SPAWN_SLOTS + t] = 0ull;
+    spawned = wave_sum(spawned);
     if (t == 0) {
         const int64_t done = d.iter + 1;
         {
@@ -2275,8 +2565,9 @@ __global__ __launch_bounds__(64) void k_finalize(EngineArgs a) {
         r.nw = nw;
         r.nd = nd;
         r.c0 = c0;
-        r.attempts = att;
-        r.spawns = (int64_t)a.spawns[s];
+        r.attempts = d.nw;   // one per walker at the iteration's start
+        d.nw = nw;
+        r.spawns = (int64_t)spawned;
         r.merged = merged;
         r.aborted = aborted;
         r.born = born;
@@ -2296,30 +2587,27 @@ __global__ __launch_bounds__(64) void k_finalize(EngineArgs a) {
             a.spilled[s] = 0u;
         }
         a.rec[(int64_t)s * REC_CAP + (done % REC_CAP)] = r;
-        a.spawns[s] = 0ull;
         d.iter = done;
     }
 }
 
 static_assert(FIN_BLOCKS == 64, "k_finalize sums one share per lane of a wavefront");
-static_assert(SCAN_G == 2048, "k_scan takes two range totals per thread of 1024");
 static_assert(POST_WAVES * 64 == 256, "one ChunkStat share per wavefront of a k_post workgroup");
 
 void launch_iteration(const EngineArgs &a, int post_grid, int spawn_grid, bool first,
                       hipStream_t s, hipEvent_t *ev) {
     if (ev) (void)hipEventRecord(ev[0], s);
     if (first)
-        hipLaunchKernelGGL(k_chunk_sum, dim3(SCAN_G), dim3(256), 0, s, a, (const SysDesc *)a.desc);
+        hipLaunchKernelGGL(k_tiles, dim3((unsigned)post_grid), dim3(256), 0, s, a,
+                           (const SysDesc *)a.desc);
     if (ev) (void)hipEventRecord(ev[1], s);
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, a);
-    hipLaunchKernelGGL(k_scan_down, dim3(SCAN_G), dim3(256), 0, s, a);
     if (ev) (void)hipEventRecord(ev[2], s);
     if (a.plain)
         hipLaunchKernelGGL(k_spawn<true>, dim3((unsigned)spawn_grid), dim3(256), 0, s, a,
-                           (const SysDesc *)a.desc);
+                           (const SysDesc *)a.desc, first ? 1 : 0);
     else
         hipLaunchKernelGGL(k_spawn<false>, dim3((unsigned)spawn_grid), dim3(256), 0, s, a,
-                           (const SysDesc *)a.desc);
+                           (const SysDesc *)a.desc, first ? 1 : 0);
     if (ev) (void)hipEventRecord(ev[3], s);
     hipLaunchKernelGGL(k_post, dim3((unsigned)post_grid), dim3(256), 0, s, a,
                        (const SysDesc *)a.desc);
@@ -2554,7 +2842,8 @@ static int cu_count() {
     return cus;
 }
 int post_grid_size() { return cu_count() * 4; }    // four workgroups per CU
-int spawn_grid_size() { return cu_count() * 6; }   // six resident workgroups per CU
+// the spawning kernel's resident workgroups (five per CU; four with two words)
+int spawn_grid_size(int W) { return cu_count() * (W == 1 ? 5 : 4); }
 #endif
 
 #if FQ_DET_WORDS == 2
