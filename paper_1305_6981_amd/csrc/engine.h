@@ -11,6 +11,8 @@ constexpr int CHUNK = 1024;          // four consecutive buckets: the unit of at
                                      // spawn staging, and one workgroup's unit in annihilation
 constexpr int BPC = CHUNK / BQ;      // buckets per chunk
 constexpr int BUCKET_FILL = 128;     // planned mean entries per bucket (half full)
+constexpr int BUCKET_RECS = 32;      // planned mean spawn records per bucket at most: a
+                                     // wavefront merges 64 in one round
 constexpr int NCLASS = 16;           // symmetry classes: 2 spins x up to 8 abelian irreps
 constexpr int REC_CAP = 256;         // per-system ring of per-iteration records
 constexpr int MAX_GRAPH_ITERS = 64;  // iterations captured in one graph launch
@@ -29,7 +31,7 @@ constexpr int N_TOTAL = CTR_UNLISTED(3);
 constexpr int TILE_MAX_SH(int W) { return W == 1 ? 9 : 8; }   // log2 of a wavefront's largest
                                      // spawn tile (W words per determinant)
 constexpr int SPAWN_SLOTS = 16;      // shares of a system's spawning-event counter
-constexpr int FIN_BLOCKS = 64;       // workgroups per system reducing the chunk statistics
+constexpr int ACC_SLOTS = 64;        // shares of a system's iteration statistics
 
 // Status bits set on the device.
 constexpr uint32_t ST_TABLE_FULL = 1u;     // the spawn-record buffer overflowed: the iteration
@@ -54,25 +56,16 @@ struct IterRecord {
     int32_t varying, status;
 };
 
-// Statistics of one bucket of an iteration (one share per wavefront of a chunk).
-// counts packs three numbers below 2^21: entries | merged spawn targets << 21 |
-// occupied << 42.
-struct ChunkStat {
-    int64_t nw, aborted;
-    uint64_t counts;
-    double num;
-    int64_t born;
-};
-constexpr int CNT_SHIFT_MERGED = 21, CNT_SHIFT_ND = 42;
-constexpr int POST_WAVES = BPC;   // wavefronts of a k_post workgroup: one bucket and one
-                                   // ChunkStat share each
-constexpr uint64_t CNT_FIELD = (1ull << 21) - 1;
-
-// One workgroup's share of a system's iteration statistics.
-struct FinPart {
+// Statistics of an iteration (a share of them). In k_post's lanes three of the counts are
+// kept in one word, each below 2^21: entries | merged spawn targets << 21 | occupied << 42.
+struct __attribute__((aligned(128))) IterStat {
     int64_t nw, nd, merged, aborted, used, born;
     double num;
 };
+constexpr int CNT_SHIFT_MERGED = 21, CNT_SHIFT_ND = 42;
+constexpr int POST_WAVES = BPC;   // wavefronts of a k_post workgroup: one bucket and one
+                                   // of a chunk each
+constexpr uint64_t CNT_FIELD = (1ull << 21) - 1;
 
 // Per-system descriptor, resident in device memory. The first block is
 // written by the host at admission / growth; the second block is updated by
@@ -155,14 +148,14 @@ struct EngineArgs {
     SysDesc *desc;
     int32_t max_sys;
     int32_t wsh;                     // log2 of a spawn tile's attempts
+    int32_t post_seg;                // chunks between k_post's looks at its queue of new dets
     unsigned int *work;              // [N_WORK] shares taken of each list (reset per iteration)
     uint32_t *status;                // per system: ST_* bits (kept apart from the read-only
     unsigned long long *spawns;      // descriptors); [SPAWN_SLOTS] spawning events each
     const int32_t *chunk_sys;        // system of each global chunk (-1: unused)
     const int32_t *chunk_local;      // chunk index inside its system's table
     unsigned long long *step;        // iterations run by this handle (its parity selects total)
-    ChunkStat *chunk_stat;           // [chunks][POST_WAVES]
-    FinPart *fin_part;               // [max_sys][FIN_BLOCKS]
+    IterStat *acc;                   // [max_sys][ACC_SLOTS] the iteration's statistics
     int64_t *c0;                     // [max_sys] population on the reference after the iteration
     unsigned long long *total;       // [N_TOTAL] lengths of the lists of spawn tiles
     const int64_t *nchunks;          // global chunks in use

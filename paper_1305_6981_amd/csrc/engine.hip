@@ -216,6 +216,7 @@ struct SysHost {
     int64_t growth = 0;        // expected per-iteration increase of the entries
     double spawn_rate = 1.0;   // mean growth of the records per iteration in the last launch
     int64_t rec_r = 0;         // record slots per bucket
+    bool no_split = false;     // no room for buckets planned by their records
     int64_t rec_peak = 0;      // most records of one bucket in the last launch (0: unknown)
     double h_max = 0.0;        // scale of the largest off-diagonal elements
     int64_t pop_max = 0;       // largest |C| of the list as loaded
@@ -252,7 +253,6 @@ struct fciqmc_t {
     int32_t *d_chunk_sys = nullptr, *d_chunk_local = nullptr;
     unsigned long long *d_total = nullptr;  // lengths of the tile lists
     uint32_t *d_unlisted = nullptr;         // buckets whose tiles did not fit
-    ChunkStat *d_chunk_stat = nullptr;
     int32_t *d_tiles = nullptr;             // the spawn tiles, 16 B each
     bool tile_map_off = false;              // its allocation failed once: search instead
     void *d_stage = nullptr;                // this device's staging area (not owned)
@@ -268,7 +268,7 @@ struct fciqmc_t {
     uint32_t *d_spilled = nullptr;
     int64_t tile_cap = 0;
     unsigned long long *d_step = nullptr;   // iterations run (its parity selects d_total)
-    FinPart *d_fin = nullptr;               // [max_sys][FIN_BLOCKS]
+    IterStat *d_acc = nullptr;              // [max_sys][ACC_SLOTS]
     int64_t *d_c0 = nullptr;                // [max_sys]
     int64_t *d_nchunks = nullptr;
     uint32_t *d_err = nullptr;
@@ -276,7 +276,7 @@ struct fciqmc_t {
     int post_grid = 1024;
     int tile = 2048;
     bool shape_set = false;                 // the launch shape was set or tuned: used as it is
-    std::map<std::array<int, 5>, hipGraphExec_t> graphs;   // by iterations, kernel variant, shape
+    std::map<std::array<int, 6>, hipGraphExec_t> graphs;   // by iterations, kernel variant, shape
     bool use_graph = true;
     bool profiling = false;
     hipEvent_t ev[NKERN + 1] = {};
@@ -302,8 +302,7 @@ EngineArgs make_args(fciqmc_t *h) {
     a.chunk_sys = h->d_chunk_sys;
     a.chunk_local = h->d_chunk_local;
     a.step = h->d_step;
-    a.chunk_stat = h->d_chunk_stat;
-    a.fin_part = h->d_fin;
+    a.acc = h->d_acc;
     a.c0 = h->d_c0;
     a.total = h->d_total;
     a.nchunks = h->d_nchunks;
@@ -344,11 +343,19 @@ EngineArgs make_args(fciqmc_t *h) {
 // is all latency (a tile's staging and its lanes' runs of attempts one after another),
 // and idle workgroups still cost their start. Powers of two, so that a growing list
 // meets few shapes (each is captured once).
+// post_seg: chunks whose new determinants fill about two thirds of k_post's queue, by the
+// fastest-growing list's last iteration (at most a whole window).
 struct Shape {
-    int wsh, spawn_grid, post_grid;
+    int wsh, spawn_grid, post_grid, post_seg;
 };
 Shape launch_shape(const fciqmc_t *h) {
-    Shape o{std::clamp((int)std::log2((double)h->tile) - 2, 6, TILE_MAX_SH(h->W)), h->spawn_grid, h->post_grid};
+    Shape o{std::clamp((int)std::log2((double)h->tile) - 2, 6, TILE_MAX_SH(h->W)), h->spawn_grid,
+            h->post_grid, 32};
+    for (int s = 0; s < h->max_sys; ++s) {
+        const SysHost &S = h->sys[s];
+        if (!S.active || S.fatal) continue;
+        while (o.post_seg > 1 && S.last.born * o.post_seg > 700 * (S.cap / CHUNK)) o.post_seg /= 2;
+    }
     if (h->shape_set) return o;
     int64_t walkers = 0;
     for (int s = 0; s < h->max_sys; ++s)
@@ -441,14 +448,12 @@ int relayout(fciqmc_t *h) {
         hipFree(h->d_chunk_sys);
         hipFree(h->d_chunk_local);
         hipFree(h->d_unlisted);
-        hipFree(h->d_chunk_stat);
         hipFree(h->d_bhist);
         h->d_chunk_sys = nullptr;
         h->chunk_alloc = 0;
         HIP_TRY(hipMalloc(&h->d_chunk_sys, na * sizeof(int32_t)));
         HIP_TRY(hipMalloc(&h->d_chunk_local, na * sizeof(int32_t)));
         HIP_TRY(hipMalloc(&h->d_unlisted, BPC * na * sizeof(uint32_t)));
-        HIP_TRY(hipMalloc(&h->d_chunk_stat, na * POST_WAVES * sizeof(ChunkStat)));
         HIP_TRY(hipMalloc(&h->d_bhist, BPC * na * sizeof(uint32_t)));
         h->chunk_alloc = na;
         drop_graphs(h);
@@ -1223,7 +1228,8 @@ int capture_or_get(fciqmc_t *h, int L, hipGraphExec_t *out) {
     const Shape sh = launch_shape(h);
     EngineArgs a = make_args(h);
     a.wsh = sh.wsh;
-    const std::array<int, 5> key = {L, a.plain, sh.wsh, sh.spawn_grid, sh.post_grid};
+    a.post_seg = sh.post_seg;
+    const std::array<int, 6> key = {L, a.plain, sh.wsh, sh.spawn_grid, sh.post_grid, sh.post_seg};
     auto it = h->graphs.find(key);
     if (it != h->graphs.end()) {
         *out = it->second;
@@ -1265,6 +1271,14 @@ int plan_launch(fciqmc_t *h, int L, int *L_out) {
                                                  round_cap(S.cap + S.cap / 2));
             const int rc = rebucket_system(h, s, nc, 0);
             if (rc) return rc;
+        }
+        // Many records per determinant (a lattice: one to twenty) would make buckets planned
+        // by their entries merge in several rounds, from memory: more buckets then, unless
+        // the device has no room for them.
+        if (S.last.spawns > S.cap / BQ * (BUCKET_RECS + BUCKET_RECS / 2) && !S.no_split) {
+            const int rc = rebucket_system(h, s, round_cap(S.last.spawns / BUCKET_RECS * BQ), 0);
+            if (rc == FCIQMC_ECAPACITY) S.no_split = true;
+            else if (rc) return rc;
         }
         const int64_t room = (S.cap * 5 / 8 - used) / g;
         allowed = (int)std::max<int64_t>(1, std::min<int64_t>(allowed, room));
@@ -1314,6 +1328,7 @@ int run_iterations(fciqmc_t *h, int L, bool sample) {
     const Shape sh = launch_shape(h);
     EngineArgs a = make_args(h);
     a.wsh = sh.wsh;
+    a.post_seg = sh.post_seg;
     if (h->profiling) {
         for (int i = 0; i < L; ++i) {
             FQ_LAUNCH(h->W, launch_iteration, a, sh.post_grid, sh.spawn_grid, i == 0, h->stream, h->ev);
@@ -1527,7 +1542,8 @@ int create_handle(int max_slots, void *stream, int W, fciqmc_t **out) {
     HIP_TRY(hipMalloc(&h->d_nchunks, sizeof(int64_t)));
     HIP_TRY(hipMalloc(&h->d_step, sizeof(unsigned long long)));
     HIP_TRY(hipMemsetAsync(h->d_step, 0, sizeof(unsigned long long), h->stream));
-    HIP_TRY(hipMalloc(&h->d_fin, sizeof(FinPart) * FIN_BLOCKS * max_slots));
+    HIP_TRY(hipMalloc(&h->d_acc, sizeof(IterStat) * ACC_SLOTS * max_slots));
+    HIP_TRY(hipMemsetAsync(h->d_acc, 0, sizeof(IterStat) * ACC_SLOTS * max_slots, h->stream));
     HIP_TRY(hipMalloc(&h->d_c0, sizeof(int64_t) * max_slots));
     HIP_TRY(hipMalloc(&h->d_err, sizeof(uint32_t)));
     HIP_TRY(hipMalloc(&h->d_rec_max, sizeof(uint32_t) * max_slots));
@@ -1611,13 +1627,12 @@ void release(fciqmc_t *h) {
     hipFree(h->d_total);
     hipFree(h->d_nchunks);
     hipFree(h->d_step);
-    hipFree(h->d_fin);
+    hipFree(h->d_acc);
     hipFree(h->d_c0);
     hipFree(h->d_err);
     hipFree(h->d_chunk_sys);
     hipFree(h->d_chunk_local);
     hipFree(h->d_unlisted);
-    hipFree(h->d_chunk_stat);
     hipFree(h->d_tiles);
     hipFree(h->d_recs);
     hipFree(h->d_rec_max);

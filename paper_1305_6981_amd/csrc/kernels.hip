@@ -6,13 +6,10 @@
 // distribution of determinants over processes by a hash (Sec. 4.1), with a
 // wavefront in the role of a process. Four consecutive buckets form a chunk,
 // the unit of attempt mapping. One iteration of every active system is
-// six launches (seven in the first iteration of a launch sequence):
+// three launches (four in the first iteration of a launch sequence):
 //
-//   k_chunk_sum   sum |C| over each bucket and over fixed contiguous ranges of
-//                 buckets (first iteration of a launch sequence only;
-//                 afterwards k_post provides the sums)
-//   k_scan        exclusive scan of the range sums (one workgroup)
-//   k_scan_down   per bucket: global attempt offset and spawn-tile offset
+//   k_tiles       lists the spawn tiles, runs of attempts of one bucket (first iteration
+//                 of a launch sequence only; afterwards k_post does)
 //   k_spawn       one spawning attempt per walker (Sec. 2, Eq. pspawn): random
 //                 excitation with its pgen (Sec. 5), Slater-Condon element,
 //                 acceptance; each accepted spawn becomes a record (child,
@@ -25,11 +22,9 @@
 //                 new determinants placed into the holes left by emptied
 //                 entries, the bucket re-packed, H_DD of new determinants from a
 //                 pair table staged in LDS; estimator partial sums (Eq. ProjE);
-//                 the next iteration's bucket and range sums of |C|
-//   k_reduce      per system, 64 workgroups: fixed-order reduction of the
-//                 bucket statistics over fixed ranges of buckets
-//   k_finalize    per system, one wavefront: sum of the 64 shares, the shift
-//                 update, the per-iteration record
+//                 the next iteration's spawn tiles
+//   k_finalize    per system, one wavefront: the iteration's statistics, which k_post's
+//                 workgroups add up in a few shares, the shift update, the record
 //
 // All floating-point decisions follow the same operation order as the CPU
 // oracle and are compiled with -ffp-contract=off.
@@ -1946,6 +1941,26 @@ __device__ __forceinline__ void flush_new_dets(const SysDesc &d, const uint32_t 
     }
 }
 
+// Adding up statistics: by their owner, and (any order) into a system's share in memory.
+__device__ __forceinline__ void add_stat(IterStat &x, const IterStat &y) {
+    x.nw += y.nw;
+    x.nd += y.nd;
+    x.merged += y.merged;
+    x.aborted += y.aborted;
+    x.used += y.used;
+    x.born += y.born;
+    x.num = x.num + y.num;
+}
+__device__ __forceinline__ void add_stat_global(IterStat *x, const IterStat &y) {
+    atomicAdd((unsigned long long *)&x->nw, (unsigned long long)y.nw);
+    atomicAdd((unsigned long long *)&x->nd, (unsigned long long)y.nd);
+    if (y.merged) atomicAdd((unsigned long long *)&x->merged, (unsigned long long)y.merged);
+    if (y.aborted) atomicAdd((unsigned long long *)&x->aborted, (unsigned long long)y.aborted);
+    atomicAdd((unsigned long long *)&x->used, (unsigned long long)y.used);
+    if (y.born) atomicAdd((unsigned long long *)&x->born, (unsigned long long)y.born);
+    if (y.num != 0.0) unsafeAtomicAdd(&x->num, y.num);
+}
+
 __device__ __forceinline__ uint64_t lanes_below(int lane) { return (1ull << lane) - 1ull; }
 
 // Sum over the wavefront's lanes of a per-lane count v < 8, from ballots of its bits.
@@ -1989,6 +2004,8 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
     __shared__ int64_t s_win;                        // first chunk of the window taken
     __shared__ unsigned int s_len[NLIST];            // windows per list
     __shared__ int s_list;                           // list taken from
+    __shared__ IterStat s_acc[POST_WAVES];           // statistics of system s_accsys
+    __shared__ int s_accsys;
     const int64_t nch = *a.nchunks;
     const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
     WaveLds &W = L.w[wid];
@@ -2007,6 +2024,8 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
         s_qn = 0;
         s_qsys = -1;
         s_tabsys = -1;
+        s_accsys = -1;
+        for (int w = 0; w < POST_WAVES; ++w) s_acc[w] = IterStat{};
     }
     auto flush = [&]() {   // (uniform) H_DD of the queued new determinants
         const SysDesc &dq = desc[s_qsys];
@@ -2025,6 +2044,26 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
         flush_new_dets(dq, s_queue, s_qn < POST_QUEUE ? s_qn : POST_QUEUE, L.tab.hpp,
                        in_lds ? L.tab.jk : nullptr);
         __syncthreads();
+    };
+    auto flush_stat = [&]() {   // (thread f < 7 hands over the f-th number)
+        if (s_accsys < 0 || t > 6) return;
+        IterStat *const to = a.acc + s_accsys * ACC_SLOTS + (blockIdx.x & (ACC_SLOTS - 1));
+        if (t < 6) {
+            unsigned long long x = 0;
+            for (int w = 0; w < POST_WAVES; ++w) {
+                unsigned long long *const f = (unsigned long long *)&s_acc[w] + t;
+                x += *f;
+                *f = 0ull;
+            }
+            if (x) atomicAdd((unsigned long long *)to + t, x);
+        } else {
+            double x = 0.0;
+            for (int w = 0; w < POST_WAVES; ++w) {
+                x = x + s_acc[w].num;
+                s_acc[w].num = 0.0;
+            }
+            if (x != 0.0) unsafeAtomicAdd(&to->num, x);   // (the hardware's add: device memory)
+        }
     };
     // The workgroups take windows of consecutive chunks from shared counters (so the
     // faster ones take more): POST_WIN chunks when every workgroup gets many, fewer for
@@ -2072,8 +2111,15 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
             flush();
             if (t == 0) s_qn = 0;
         }
+        // the workgroup's statistics belong to one system: handed over at a change
+        const int wsys = a.chunk_sys[c0];
+        const bool change = s_accsys != wsys;
+        if (change) flush_stat();
         __syncthreads();
-        if (t == 0 && s_qn == 0) s_qsys = -1;
+        if (t == 0) {
+            if (s_qn == 0) s_qsys = -1;
+            s_accsys = wsys;
+        }
         const int nwin = (int)(nch - c0 < gwin ? nch - c0 : gwin);
         if (t < nwin) {
             const int sc = a.chunk_sys[c0 + t];
@@ -2109,7 +2155,21 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
         uint64_t a_cnt = 0;
         double a_num = 0.0;
         for (int ci = 0; ci < nwin; ++ci) {
-            const int64_t c = c0 + ci;
+            // The queue of new determinants serves one system and holds POST_QUEUE; what does
+            // not go through it is computed in place, a chain of gathers that stops the
+            // wavefront for 100 us. So the workgroup meets to empty it where the window
+            // changes system (not a batch's every system in one window), and every post_seg
+            // chunks where the lists grow fast.
+            if (ci > 0 && (s_csys[ci] != s_csys[ci - 1] || ci % a.post_seg == 0)) {   // (uniform)
+                __syncthreads();
+                if (s_qn >= POST_FLUSH || (s_qn > 0 && s_csys[ci] != s_qsys)) {
+                    flush();
+                    if (t == 0) s_qn = 0;
+                }
+                __syncthreads();
+                if (t == 0 && s_qn == 0) s_qsys = -1;
+                __syncthreads();
+            }
             const int s = s_csys[ci];
             const bool live = s >= 0;
             int64_t nw = 0, aborted = 0;
@@ -2453,14 +2513,25 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
             a_cnt += cnt;
             a_num = a_num + num;
             a_born += born;
-            // the statistics share of this wavefront: its accumulated buckets when the
-            // system changes after this chunk or the window ends (fixed-order reduction),
-            // nothing otherwise
+            // the wavefront's statistics, when the system changes after this chunk or the
+            // window ends: into the workgroup's sums, or (another system) the system's
             const bool last = ci + 1 == nwin || s_csys[ci + 1] != s;
-            ChunkStat cs{0, 0, 0ull, 0.0, 0};
+            if (last && live) {
+                IterStat st;
+                st.nw = wave_sum((long long)a_nw);
+                st.aborted = wave_sum((long long)a_ab);
+                const uint64_t c3 = wave_sum((unsigned long long)a_cnt);
+                st.used = (int64_t)(c3 & CNT_FIELD);
+                st.merged = (int64_t)((c3 >> CNT_SHIFT_MERGED) & CNT_FIELD);
+                st.nd = (int64_t)(c3 >> CNT_SHIFT_ND);
+                st.born = a_born;
+                st.num = wave_sum(a_num);
+                if (lane == 0) {
+                    if (s == s_accsys) add_stat(s_acc[wid], st);
+                    else add_stat_global(a.acc + s * ACC_SLOTS + (blockIdx.x & (ACC_SLOTS - 1)), st);
+                }
+            }
             if (last) {
-                cs = ChunkStat{(int64_t)wave_sum((long long)a_nw), (int64_t)wave_sum((long long)a_ab),
-                               (uint64_t)wave_sum((unsigned long long)a_cnt), wave_sum(a_num), a_born};
                 a_nw = a_ab = a_born = 0;
                 a_cnt = 0ull;
                 a_num = 0.0;
@@ -2471,66 +2542,31 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                       ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), 63) << 32);
             }
             if (lane == 0) {
-                a.chunk_stat[c * POST_WAVES + wid] = cs;
                 // walkers that spawn next iteration: none if the system stops after this one
                 s_bnw[ci * BPC + wid] = s_cnext[ci] ? nwb : 0ull;
             }
         }
     }
     __syncthreads();
+    flush_stat();
     if (s_qn > 0) flush();   // uniform
 }
 
 // ---------------------------------------------------------------------------
-// K5a: per system, FIN_BLOCKS workgroups each reduce one contiguous range of
-// the system's chunk statistics (fixed ranges and trees: deterministic).
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_reduce(EngineArgs a) {
-    __shared__ long long shi[256];
-    __shared__ double shd[256];
-    const int s = blockIdx.y;
-    const SysDesc &d = a.desc[s];
-    if (!participating(d, a.status[s])) return;   // uniform across the workgroup
-    const int t = threadIdx.x;
-    const int64_t per = (d.nchunks + FIN_BLOCKS - 1) / FIN_BLOCKS;
-    const int64_t lo = (int64_t)blockIdx.x * per;
-    const int64_t hi = lo + per < d.nchunks ? lo + per : d.nchunks;
-    int64_t nw = 0, nd = 0, merged = 0, aborted = 0, used = 0, born = 0;
-    double num = 0.0;
-    for (int64_t i = lo + t; i < hi; i += 256) {
-        for (int w = 0; w < POST_WAVES; ++w) {
-            const ChunkStat cs = a.chunk_stat[(d.gchunk0 + i) * POST_WAVES + w];
-            used += (int64_t)(cs.counts & CNT_FIELD);
-            merged += (int64_t)((cs.counts >> CNT_SHIFT_MERGED) & CNT_FIELD);
-            nd += (int64_t)(cs.counts >> CNT_SHIFT_ND);
-            nw += cs.nw;
-            aborted += cs.aborted;
-            born += cs.born;
-            num = num + cs.num;
-        }
-    }
-    FinPart p;
-    p.nw = block_sum((long long)nw, shi);
-    p.nd = block_sum((long long)nd, shi);
-    p.merged = block_sum((long long)merged, shi);
-    p.aborted = block_sum((long long)aborted, shi);
-    p.used = block_sum((long long)used, shi);
-    p.born = block_sum((long long)born, shi);
-    p.num = block_sum(num, shd);
-    if (t == 0) a.fin_part[(int64_t)s * FIN_BLOCKS + blockIdx.x] = p;
-}
-
-// ---------------------------------------------------------------------------
-// K5b: per system (one wavefront): sum of the FIN_BLOCKS shares by a fixed
-// butterfly, the shift update, the per-iteration record.
+// K5: per system (one wavefront): sum of the ACC_SLOTS shares of its statistics, the shift
+// update, the per-iteration record.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(64) void k_finalize(EngineArgs a) {
     const int s = blockIdx.x;
     if (s == 0 && threadIdx.x == 0) *a.step += 1ull;   // every kernel of this iteration has read it
     SysDesc &d = a.desc[s];
-    if (!participating(d, a.status[s])) return;   // uniform across the wavefront
     const int t = threadIdx.x;
-    const FinPart p = a.fin_part[(int64_t)s * FIN_BLOCKS + t];
+    IterStat p{};
+    if (t < ACC_SLOTS) {   // (emptied also for a system that has just stopped)
+        p = a.acc[s * ACC_SLOTS + t];
+        a.acc[s * ACC_SLOTS + t] = IterStat{};
+    }
+    if (!participating(d, a.status[s])) return;   // uniform across the wavefront
     const int64_t nw = wave_sum((long long)p.nw);
     const int64_t nd = wave_sum((long long)p.nd);
     const int64_t c0 = a.c0[s];
@@ -2591,8 +2627,8 @@ __global__ __launch_bounds__(64) void k_finalize(EngineArgs a) {
     }
 }
 
-static_assert(FIN_BLOCKS == 64, "k_finalize sums one share per lane of a wavefront");
-static_assert(POST_WAVES * 64 == 256, "one ChunkStat share per wavefront of a k_post workgroup");
+static_assert(ACC_SLOTS <= 64 && SPAWN_SLOTS <= 64, "k_finalize sums one share per lane of a wavefront");
+static_assert(POST_WAVES * 64 == 256, "one bucket of a chunk per wavefront of a k_post workgroup");
 
 void launch_iteration(const EngineArgs &a, int post_grid, int spawn_grid, bool first,
                       hipStream_t s, hipEvent_t *ev) {
@@ -2612,7 +2648,6 @@ void launch_iteration(const EngineArgs &a, int post_grid, int spawn_grid, bool f
     hipLaunchKernelGGL(k_post, dim3((unsigned)post_grid), dim3(256), 0, s, a,
                        (const SysDesc *)a.desc);
     if (ev) (void)hipEventRecord(ev[4], s);
-    hipLaunchKernelGGL(k_reduce, dim3(FIN_BLOCKS, (unsigned)a.max_sys), dim3(256), 0, s, a);
     hipLaunchKernelGGL(k_finalize, dim3((unsigned)a.max_sys), dim3(64), 0, s, a);
     if (ev) (void)hipEventRecord(ev[5], s);
 }
