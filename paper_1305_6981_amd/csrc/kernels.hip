@@ -730,11 +730,14 @@ __device__ double fn_diag(const SysDesc &d, det_t D) { return fn_diag_from(d, D,
 
 // Projected-energy element <Phi_0|H|Phi_D> (Eq. ProjE) and whether it can be
 // nonzero (D within a double excitation of the reference, or its partner).
+// (PLAIN: determinants, EngineArgs::plain.)
+template <bool PLAIN>
 __device__ __forceinline__ bool near_ref(const SysDesc &d, det_t D) {
-    return dpopc(D ^ ref_of(d)) <= 4 || (d.hphf && dpopc(spin_flip(D) ^ ref_of(d)) <= 4);
+    return dpopc(D ^ ref_of(d)) <= 4 || (!PLAIN && d.hphf && dpopc(spin_flip(D) ^ ref_of(d)) <= 4);
 }
-__device__ double ref_hel(const SysDesc &d, det_t D) {
-    return d.hphf ? fn_hel(d, ref_of(d), D) : hel_to_ref(d, D);
+template <bool PLAIN>
+__device__ __forceinline__ double ref_hel(const SysDesc &d, det_t D) {
+    return !PLAIN && d.hphf ? fn_hel(d, ref_of(d), D) : hel_to_ref(d, D);
 }
 
 // The probability that excite() draws T from det (Secs. 5.1, 5.2) by the same
@@ -1690,6 +1693,8 @@ constexpr uint32_t F_MAYBE = 2u;        // record: found the hash full in this r
 constexpr uint32_t F_DEFER = 4u;        // record: left for a later round
 constexpr uint32_t F_STAGED = 8u;       // record: holds a merged child outside the bucket
 constexpr int OWN_SHIFT = 2;            // hash slot: the record that entered the child
+constexpr int DIAG_SPILL = BQ;          // (see place() in k_post)
+constexpr int DIAG_SHIFT = 4;           // staged record: place()'s answer + 1
 
 // Home slot: a multiplicative hash of the folded words (the determinants of one
 // bucket agree in the bits of mix64 that chose the bucket, not in these).
@@ -1968,6 +1973,8 @@ __device__ __forceinline__ int wave_total8(int v) {
     return __popcll(__ballot(v & 1)) + 2 * __popcll(__ballot(v & 2)) + 4 * __popcll(__ballot(v & 4));
 }
 
+// PLAIN: as for k_spawn.
+template <bool PLAIN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4)))
 void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
     // Each wavefront's working set, and (between chunks only) the pair table from
@@ -2007,6 +2014,9 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
     __shared__ IterStat s_acc[POST_WAVES];           // statistics of system s_accsys
     __shared__ int s_accsys;
     const int64_t nch = *a.nchunks;
+    // (The wavefront's number, a segment's system and a bucket's sizes are left to vector
+    // registers: as scalars they cost 135 spilled scalar registers and scalar loads at each
+    // use, 1.44 instead of 1.23 ms at 1.4e8 walkers.)
     const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
     WaveLds &W = L.w[wid];
     if (blockIdx.x == 0 && t < NLIST) {   // k_spawn's counters, for the next iteration
@@ -2067,11 +2077,12 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
     };
     // The workgroups take windows of consecutive chunks from shared counters (so the
     // faster ones take more): POST_WIN chunks when every workgroup gets many, fewer for
-    // small launches; inside a window the wavefronts run through the chunks
+    // small launches, down to one window each (a window costs a dozen us of its own: the
+    // counter, the metadata's chain of loads, the barriers); inside a window the wavefronts run through the chunks
     // independently. When it is done, its buckets' tiles are appended to the next
     // iteration's list.
-    const int64_t per_wg = nch / (4 * (int64_t)gridDim.x);
-    const int gwin = per_wg >= POST_WIN ? POST_WIN : per_wg > 0 ? (int)per_wg : 1;
+    const int64_t per_wg = (nch + gridDim.x - 1) / gridDim.x;
+    const int gwin = per_wg <= 8 ? (int)per_wg : per_wg < 32 ? 8 : per_wg < 4 * POST_WIN ? (int)(per_wg / 4) : POST_WIN;
     // List l holds the windows of the l-th of NLIST equal ranges of windows; the last
     // wavefront does the taking.
     const auto win0 = [&](int l) { return (uint32_t)((nch + gwin - 1) / gwin) * (uint64_t)l / NLIST; };
@@ -2080,98 +2091,97 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
         s_list = (int)(blockIdx.x & (NLIST - 1));
         s_win = -1;
     }
+    // Each pass takes a segment: consecutive chunks of one system in the window at hand, at
+    // most post_seg (or first the next window). Between segments the workgroup meets and
+    // empties its queue of new determinants when it holds one per thread or belongs to
+    // another system. What does not go through the queue (one system at a time, POST_QUEUE
+    // places) is computed in place, a chain of gathers that stops a wavefront for 100 us;
+    // hence a segment per system, shorter ones where lists grow fast. The queue is kept over
+    // windows: small launches bring few new determinants per window, and emptying it is a
+    // latency of its own.
+    int64_t c0 = 0;
+    int nwin = 0, ci = 0;      // the window's chunks, and the segment's first
+    bool begin = true;
     for (;;) {
-        __syncthreads();   // the previous window is done
-        const int64_t prev0 = s_win;
-        const int prevn = prev0 < 0 ? 0 : (int)(nch - prev0 < gwin ? nch - prev0 : gwin);
-        __syncthreads();
-        if (wid == POST_WAVES - 1) {
-            unsigned int at = 0, count = 0;
-            Handout ho{a.work + CTR_POST(0), s_len, 1u, 1u, __builtin_amdgcn_readfirstlane(s_list), prev0 < 0};
-            const bool more = handout_next(ho, blockIdx.x / NLIST, at, count);
-            if (lane == 0) {
-                s_win = more ? (int64_t)(win0(ho.list) + at) * gwin : nch;
-                s_list = ho.list;
+        __syncthreads();   // the previous segment is done
+        const bool fresh = ci >= nwin;
+        if (fresh) {
+            if (wid == POST_WAVES - 1) {
+                unsigned int at = 0, count = 0;
+                Handout ho{a.work + CTR_POST(0), s_len, 1u, 1u, __builtin_amdgcn_readfirstlane(s_list), begin};
+                const bool more = handout_next(ho, blockIdx.x / NLIST, at, count);
+                if (lane == 0) {
+                    s_win = more ? (int64_t)(win0(ho.list) + at) * gwin : nch;
+                    s_list = ho.list;
+                }
             }
+            // list the tiles of the window just done
+            if (t < (nwin * BPC + 63) / 64 * 64) {   // (whole wavefronts)
+                const bool in = t < nwin * BPC;
+                emit_tiles(a, cur_half(a) ^ 1, (int)((c0 / gwin) & (NLIST - 1)), c0 * BPC + t,
+                           in ? s_csys[t / BPC] : 0, in ? (uint32_t)(s_cloc[t / BPC] * BPC + t % BPC) : 0u,
+                           in ? s_bnw[t] : 0ull, in ? s_bn[t] : 0);
+            }
+            __syncthreads();
+            c0 = (int64_t)uni((uint64_t)s_win);
+            begin = false;
+            ci = 0;
+            nwin = (int)(nch - c0 < gwin ? nch - c0 : gwin);
         }
-        // list the tiles of the window just done
-        if (t < (prevn * BPC + 63) / 64 * 64) {   // (whole wavefronts)
-            const bool in = t < prevn * BPC;
-            emit_tiles(a, cur_half(a) ^ 1, (int)((prev0 / gwin) & (NLIST - 1)), prev0 * BPC + t, in ? s_csys[t / BPC] : 0,
-                       in ? (uint32_t)(s_cloc[t / BPC] * BPC + t % BPC) : 0u, in ? s_bnw[t] : 0ull,
-                       in ? s_bn[t] : 0);
-        }
-        __syncthreads();
-        const int64_t c0 = s_win;
-        if (c0 >= nch) break;
-        // The queue is kept over windows of one system (small launches bring few new
-        // determinants per window, and a flush is a latency of its own): it is emptied when
-        // it holds one per thread or the window begins with another system.
-        if (s_qn >= POST_FLUSH || (s_qn > 0 && a.chunk_sys[c0] != s_qsys)) {   // (uniform)
+        const bool done = c0 >= nch;
+        const int nsys = done ? -2 : fresh ? a.chunk_sys[c0] : s_csys[ci];
+        if (s_qn >= POST_FLUSH || (s_qn > 0 && nsys != s_qsys)) {   // (uniform)
             flush();
             if (t == 0) s_qn = 0;
         }
         // the workgroup's statistics belong to one system: handed over at a change
-        const int wsys = a.chunk_sys[c0];
-        const bool change = s_accsys != wsys;
-        if (change) flush_stat();
+        if (fresh && nsys != s_accsys) flush_stat();
+        if (done) break;
         __syncthreads();
         if (t == 0) {
             if (s_qn == 0) s_qsys = -1;
-            s_accsys = wsys;
+            if (fresh) s_accsys = nsys;
         }
-        const int nwin = (int)(nch - c0 < gwin ? nch - c0 : gwin);
-        if (t < nwin) {
-            const int sc = a.chunk_sys[c0 + t];
-            bool live = false, next = false;
-            if (sc >= 0) {
-                const SysDesc &dc = desc[sc];
-                live = participating(dc, sc < POST_MAX_SYS ? s_stat[sc] : a.status[sc]);
-                next = live && dc.iter + 1 < dc.stop_at;
+        if (fresh) {
+            if (t < nwin) {
+                const int sc = a.chunk_sys[c0 + t];
+                bool live = false, next = false;
+                if (sc >= 0) {
+                    const SysDesc &dc = desc[sc];
+                    live = participating(dc, sc < POST_MAX_SYS ? s_stat[sc] : a.status[sc]);
+                    next = live && dc.iter + 1 < dc.stop_at;
+                }
+                s_csys[t] = live ? sc : -1;
+                s_cloc[t] = a.chunk_local[c0 + t];
+                s_cnext[t] = next ? 1 : 0;
             }
-            s_csys[t] = live ? sc : -1;
-            s_cloc[t] = a.chunk_local[c0 + t];
-            s_cnext[t] = next ? 1 : 0;
-        }
-        uint32_t nrec = 0;
-        if (t < nwin * BPC) {
-            nrec = a.bhist[c0 * BPC + t];
-            if (nrec) a.bhist[c0 * BPC + t] = 0u;   // counted afresh next iteration
-            s_nr[t] = nrec;
-            // the fullest bucket, from which the host plans the slots (of an abandoned
-            // iteration too: its dropped records were counted)
-            const int sr = nrec ? a.chunk_sys[c0 + t / BPC] : -1;
-            if (sr >= 0 && nrec > a.rec_max[sr]) atomicMax(&a.rec_max[sr], nrec);
-        }
-        __syncthreads();
-        if (t < nwin * BPC) {
-            const int sc = s_csys[t / BPC];
-            s_bn[t] = sc >= 0 ? (int16_t)desc[sc].bcnt[(int64_t)s_cloc[t / BPC] * BPC + t % BPC] : 0;
+            uint32_t nrec = 0;
+            if (t < nwin * BPC) {
+                nrec = a.bhist[c0 * BPC + t];
+                if (nrec) a.bhist[c0 * BPC + t] = 0u;   // counted afresh next iteration
+                s_nr[t] = nrec;
+                // the fullest bucket, from which the host plans the slots (of an abandoned
+                // iteration too: its dropped records were counted)
+                const int sr = nrec ? a.chunk_sys[c0 + t / BPC] : -1;
+                if (sr >= 0 && nrec > a.rec_max[sr]) atomicMax(&a.rec_max[sr], nrec);
+            }
+            __syncthreads();
+            if (t < nwin * BPC) {
+                const int sc = s_csys[t / BPC];
+                s_bn[t] = sc >= 0 ? (int16_t)desc[sc].bcnt[(int64_t)s_cloc[t / BPC] * BPC + t % BPC] : 0;
+            }
         }
         __syncthreads();
-        // this wavefront's statistics over consecutive buckets of one system (per lane;
-        // reduced when the system changes and at the end of the window)
+        // this wavefront's statistics over the segment's buckets (per lane)
         int64_t a_nw = 0, a_ab = 0, a_born = 0;
         uint64_t a_cnt = 0;
         double a_num = 0.0;
-        for (int ci = 0; ci < nwin; ++ci) {
-            // The queue of new determinants serves one system and holds POST_QUEUE; what does
-            // not go through it is computed in place, a chain of gathers that stops the
-            // wavefront for 100 us. So the workgroup meets to empty it where the window
-            // changes system (not a batch's every system in one window), and every post_seg
-            // chunks where the lists grow fast.
-            if (ci > 0 && (s_csys[ci] != s_csys[ci - 1] || ci % a.post_seg == 0)) {   // (uniform)
-                __syncthreads();
-                if (s_qn >= POST_FLUSH || (s_qn > 0 && s_csys[ci] != s_qsys)) {
-                    flush();
-                    if (t == 0) s_qn = 0;
-                }
-                __syncthreads();
-                if (t == 0 && s_qn == 0) s_qsys = -1;
-                __syncthreads();
-            }
-            const int s = s_csys[ci];
-            const bool live = s >= 0;
+        const int s = s_csys[ci];
+        const bool live = s >= 0;
+        const uint64_t cut = __ballot(lane > ci && (lane >= nwin || s_csys[lane & (POST_WIN - 1)] != s ||
+                                                    lane % a.post_seg == 0));
+        const int seg_end = __builtin_ctzll(cut);   // (lane POST_WIN >= nwin is always set)
+        for (; ci < seg_end; ++ci) {
             int64_t nw = 0, aborted = 0;
             uint64_t cnt = 0;                 // entries | merged targets << 21 | occupied << 42
             double num = 0.0;
@@ -2379,7 +2389,7 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                     nw += an;
                     nwb += (unsigned long long)an;
                     cnt += np != 0 ? 1ull << CNT_SHIFT_ND : 0ull;
-                    nearm |= (np != 0 && !is_ref && near_ref(d, D)) ? 1u << u : 0u;
+                    nearm |= (np != 0 && !is_ref && near_ref<PLAIN>(d, D)) ? 1u << u : 0u;
                     keepm |= (np != 0 || is_ref) ? 1u << u : 0u;   // the reference keeps its entry at 0
                 }
                 if (ovf) atomicOr(status, ST_POP_OVERFLOW);
@@ -2398,10 +2408,10 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                 // New determinants: children outside the bucket with an initiator parent go
                 // to the emptied positions first, then past the end; the others are discarded.
                 int K = 0;
-                int calls = 0;
-                uint32_t nearn = 0u;   // fast path: bit 0, this lane's new determinant
-                                       // contributes to the projected energy
-                auto place = [&](det_t D, long long sp, bool init) {   // (all lanes; D = 0: none)
+                // (all lanes; D = 0: none.) Returns where the determinant's diagonal element is
+                // still to be computed: its position in the bucket, DIAG_SPILL + its place in
+                // the spill list, or -1 (none, or queued).
+                auto place = [&](det_t D, long long sp, bool init) -> int {
                     const bool real = D != det_t(0ull) && sp != 0;
                     if (real) cnt += 1ull << CNT_SHIFT_MERGED;
                     if (real && !init) aborted += sp < 0 ? -sp : sp;
@@ -2409,37 +2419,34 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                     const uint64_t m = __ballot(nd);
                     const int k = K + __popcll(m & lanes_below(lane));
                     K += __popcll(m);
-                    const int call = calls++;
-                    if (!nd) return;
+                    if (!nd) return -1;
                     const int64_t an = sp < 0 ? -sp : sp;
                     nw += an;
                     cnt += 1ull << CNT_SHIFT_ND;
-                    if (call < 32 && near_ref(d, D)) nearn |= 1u << call;
                     const int pos = k < H ? (int)W.free_[k] : n + (k - H);
                     if (pos < BQ) {
                         nwb += (unsigned long long)an;
                         stk(keys_of(d) + base + pos, D);
                         *gp(d.pop + base + pos) = (int32_t)sp;
                         const int q = s_qsys == s ? atomicAdd(&s_qn, 1) : POST_QUEUE;
-                        if (q < POST_QUEUE) {
-                            s_queue[q] = (uint32_t)(base + pos);
-                        } else {   // (another system's window, or many new determinants)
-                            *gp(d.hdiag + base + pos) = fn_diag(d, D);
-                        }
+                        if (q >= POST_QUEUE) return pos;   // (many new determinants)
+                        s_queue[q] = (uint32_t)(base + pos);
                     } else {
                         // the bucket is full: completed in the spill list, re-bucketed by the host
                         const unsigned long long j = atomicAdd(a.sp_count, 1ull);
                         if (j < (unsigned long long)a.sp_cap) {
                             spill_dets(a)[j] = D;
                             a.sp_pop[j] = (int32_t)sp;
-                            a.sp_hd[j] = fn_diag(d, D);
                             a.sp_sys[j] = s;
                             a.spilled[s] = 1u;
+                            return DIAG_SPILL + (int)j;
                         } else {
                             atomicOr(status, ST_SPILL_FULL);
                         }
                     }
+                    return -1;
                 };
+                int diag = -1;         // fast path: place()'s answer for this lane's child
                 long long rsp = 0ll;   // fast path: walkers that arrived for this lane's child
                 if (nr <= (uint32_t)NREC) {
                     // one lane per distinct child: the lane that entered it into the hash
@@ -2449,16 +2456,17 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                     if (rsp > 2147483647ll || rsp < -2147483647ll) {
                         atomicOr(status, ST_POP_OVERFLOW);
                         rsp = 0ll;
-                        place(det_t(0ull), 0ll, false);
-                    } else {
-                        place(cand ? rd : det_t(0ull), rsp, (f & F_INIT) != 0u);
                     }
+                    rf = cand ? f & F_INIT : 0u;   // (set: a new determinant)
+                    diag = place(cand && rsp != 0ll ? rd : det_t(0ull), rsp, (f & F_INIT) != 0u);
                 } else {
                     for (uint32_t i0 = 0; i0 < nr; i0 += 64) {
                         const uint32_t i = i0 + lane;
-                        const bool in = i < nr && (seg[i].tag & F_STAGED);
-                        place(in ? seg[i].det : det_t(0ull), in ? (long long)seg[i].w : 0ll,
-                              in && (seg[i].tag & F_INIT));
+                        const rec_t r = get_rec(seg + (i < nr ? i : 0u));
+                        const bool in = i < nr && (r.tag & F_STAGED);
+                        const int at = place(in ? r.det : det_t(0ull), in ? (long long)r.w : 0ll,
+                                             in && (r.tag & F_INIT));
+                        if (at >= 0) seg[i].tag = r.tag | (uint32_t)(at + 1) << DIAG_SHIFT;
                     }
                 }
                 // Re-pack: n' = (kept entries) + (new determinants); when fewer new
@@ -2493,18 +2501,33 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                     cnt += (uint64_t)np_;
                 }
                 born = K + wave_total8(reborn);
-                // Projected-energy numerator (Eq. ProjE): the occupied determinants within a
-                // double excitation of the reference, taken last, when few values are live.
+                // Projected-energy numerator (Eq. ProjE), the occupied determinants within a
+                // double excitation of the reference, and the diagonal elements still to be
+                // computed, taken last, when few values are live: a lane's entries (bits 0-3
+                // of todo) and its new determinant (bits 4 and 5; many of them on the slow
+                // path).
+                const bool fast = nr <= (uint32_t)NREC;
+                for (uint32_t i0 = 0; i0 == 0 || (!fast && i0 < nr); i0 += 64) {
+                    bool fresh_det = fast && rown && rf != 0u && rsp != 0ll;
+                    if (!fast) {
+                        const uint32_t i = i0 + lane;
+                        const rec_t r = get_rec(seg + (i < nr ? i : 0u));
+                        fresh_det = i < nr && (r.tag & F_STAGED) && (r.tag & F_INIT) && r.w != 0;
+                        rd = r.det;
+                        rsp = r.w;
+                        diag = fresh_det ? (int)(r.tag >> DIAG_SHIFT) - 1 : -1;
+                    }
+                    uint32_t todo = (i0 == 0 ? nearm : 0u) |
+                                    (fresh_det && near_ref<PLAIN>(d, rd) ? 1u << 4 : 0u) |
+                                    (diag >= 0 ? 1u << 5 : 0u);
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if ((nearm >> u) & 1u) num = num + ref_hel(d, kin[u]) * (double)npv[u];
-                if (nr <= (uint32_t)NREC) {
-                    if (nearn & 1u) num = num + ref_hel(d, rd) * (double)rsp;
-                } else {
-                    for (uint32_t i = lane; i < nr; i += 64) {
-                        const rec_t r = get_rec(seg + i);
-                        if ((r.tag & F_STAGED) && r.w != 0 && (r.tag & F_INIT) && near_ref(d, r.det))
-                            num = num + ref_hel(d, r.det) * (double)r.w;
+                    for (int u = 0; u < 4; ++u)
+                        if ((todo >> u) & 1u) num = num + ref_hel<PLAIN>(d, kin[u]) * (double)npv[u];
+                    if ((todo >> 4) & 1u) num = num + ref_hel<PLAIN>(d, rd) * (double)rsp;
+                    if ((todo >> 5) & 1u) {
+                        double *const to = diag >= DIAG_SPILL ? a.sp_hd + (diag - DIAG_SPILL)
+                                                              : d.hdiag + base + diag;
+                        *gp(to) = fn_diag(d, rd);
                     }
                 }
             }
@@ -2513,10 +2536,9 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
             a_cnt += cnt;
             a_num = a_num + num;
             a_born += born;
-            // the wavefront's statistics, when the system changes after this chunk or the
-            // window ends: into the workgroup's sums, or (another system) the system's
-            const bool last = ci + 1 == nwin || s_csys[ci + 1] != s;
-            if (last && live) {
+            // the wavefront's statistics at the segment's end: into the workgroup's sums, or
+            // (another system) the system's
+            if (ci + 1 == seg_end && live) {
                 IterStat st;
                 st.nw = wave_sum((long long)a_nw);
                 st.aborted = wave_sum((long long)a_ab);
@@ -2531,11 +2553,6 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                     else add_stat_global(a.acc + s * ACC_SLOTS + (blockIdx.x & (ACC_SLOTS - 1)), st);
                 }
             }
-            if (last) {
-                a_nw = a_ab = a_born = 0;
-                a_cnt = 0ull;
-                a_num = 0.0;
-            }
             {   // the wavefront's total, by DPP (all lanes active here)
                 const unsigned long long x = wave_incl_scan(nwb);
                 nwb = (unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, 63) |
@@ -2547,9 +2564,6 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
             }
         }
     }
-    __syncthreads();
-    flush_stat();
-    if (s_qn > 0) flush();   // uniform
 }
 
 // ---------------------------------------------------------------------------
@@ -2645,8 +2659,12 @@ void launch_iteration(const EngineArgs &a, int post_grid, int spawn_grid, bool f
         hipLaunchKernelGGL(k_spawn<false>, dim3((unsigned)spawn_grid), dim3(256), 0, s, a,
                            (const SysDesc *)a.desc, first ? 1 : 0);
     if (ev) (void)hipEventRecord(ev[3], s);
-    hipLaunchKernelGGL(k_post, dim3((unsigned)post_grid), dim3(256), 0, s, a,
-                       (const SysDesc *)a.desc);
+    if (a.plain)
+        hipLaunchKernelGGL(k_post<true>, dim3((unsigned)post_grid), dim3(256), 0, s, a,
+                           (const SysDesc *)a.desc);
+    else
+        hipLaunchKernelGGL(k_post<false>, dim3((unsigned)post_grid), dim3(256), 0, s, a,
+                           (const SysDesc *)a.desc);
     if (ev) (void)hipEventRecord(ev[4], s);
     hipLaunchKernelGGL(k_finalize, dim3((unsigned)a.max_sys), dim3(64), 0, s, a);
     if (ev) (void)hipEventRecord(ev[5], s);
