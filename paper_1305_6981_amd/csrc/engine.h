@@ -199,6 +199,11 @@ constexpr size_t NOALLOC_BYTES = NOALLOC_FLAGS_OFF + 4 * (size_t)NOALLOC_MAX_DET
 // two words in fq::w2). Determinant arrays hold the width's words per entry.
 constexpr int NKERN = 5;   // profiled kernel groups: chunk sums, scans, spawn, annihilation
                            // (record sort + death/annihilation pass), statistics/shift
+// Device sort: longest list (32-bit positions), and the words its digit counts take (a
+// total per digit, then one count per digit and run of 1024 entries).
+constexpr int64_t SORT_MAX = (int64_t)1 << 31;
+constexpr int64_t sort_hist_words(int64_t n) { return 256 * (1 + (n + 1023) / 1024); }
+
 #define FQ_WIDTH_LAUNCHERS                                                                     \
     /* first: the spawn tiles are listed from the tables (the first iteration of a launch,    \
        after any host-side change); later iterations use the list the previous iteration's    \
@@ -215,9 +220,17 @@ constexpr int NKERN = 5;   // profiled kernel groups: chunk sums, scans, spawn, 
                                const int32_t *sp_pop, const double *sp_hd,                    \
                                const int32_t *sp_sys, int64_t n_sp, uint32_t *d_err,          \
                                hipStream_t s);                                                 \
+    /* Adds the occupied entries of nb buckets to *count and writes the first `limit`. */     \
     hipError_t launch_compact(const uint64_t *key, const int32_t *pop, const int32_t *cnt,    \
                               int64_t nb, uint64_t *out_det, int32_t *out_pop,                \
-                              unsigned long long *count, hipStream_t s);                      \
+                              unsigned long long *count, int64_t limit, hipStream_t s);       \
+    /* Stable sort of n (<= SORT_MAX) entries by the low `passes` bytes of the determinant;   \
+       the result is in key2/val2 if passes is odd. hist: sort_hist_words(n) words. */        \
+    hipError_t launch_sort(uint64_t *key, int32_t *val, uint64_t *key2, int32_t *val2,        \
+                           uint32_t *hist, int64_t n, int passes, hipStream_t s);             \
+    /* Initiator flag of each of n entries: |pop| > n_a, or the reference. */                 \
+    hipError_t launch_flags(const uint64_t *key, const int32_t *val, int64_t n, int32_t n_a,  \
+                            uint64_t d0, uint64_t d0_hi, uint32_t *flags, hipStream_t s);     \
     /* H_DD (or the function's diagonal) of one determinant, words lo and hi. */              \
     hipError_t launch_e0(const SysDesc *desc, int32_t sys, uint64_t lo, uint64_t hi,          \
                          double *out, hipStream_t s);

@@ -30,6 +30,8 @@
 // oracle and are compiled with -ffp-contract=off.
 #include "engine.h"
 
+#include <utility>
+
 #ifndef FQ_DET_WORDS
 #define FQ_DET_WORDS 1
 #endif
@@ -2724,38 +2726,197 @@ __global__ void k_rebucket(SysDesc *desc, int32_t sys, const det_t *skey, const 
 }
 
 // Occupied entries (population != 0) of nb buckets, in any order, into odet/opop
-// (at most `limit` written; *count gets the total). One counter atomic per wavefront.
+// (at most `limit` written; *count gets the total, also with limit 0). A wavefront takes a
+// whole chunk's 1024 slots, so that one counter atomic serves up to 1024 entries: all of them
+// go to one address, which takes about 100 a microsecond (with one per 64 slots, the counter
+// alone took 20 ms on a list of 8e7).
 __global__ __launch_bounds__(256) void k_compact(const det_t *kv, const int32_t *pop,
                                                  const int32_t *cnt, int64_t nb, det_t *odet,
                                                  int32_t *opop, unsigned long long *count,
                                                  int64_t limit) {
+    constexpr int R = CHUNK / 64;
     const int lane = threadIdx.x & 63;
-    const int64_t ns = nb * BQ;
-    for (int64_t base = (int64_t)blockIdx.x * blockDim.x; base < ns;
-         base += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t i = base + threadIdx.x;
-        bool take = false;
-        det_t D = det_t(0ull);
-        int32_t p = 0;
-        if (i < ns && (int)(i % BQ) < cnt[i / BQ]) {
-            D = kv[i];
-            p = pop[i];
-            take = p != 0;
+    const int64_t nc = nb / BPC;   // (buckets come in whole chunks)
+    for (int64_t c = blockIdx.x * 4ll + (threadIdx.x >> 6); c < nc; c += gridDim.x * 4ll) {
+        const int64_t base = c * CHUNK;
+        int32_t p[R];
+        int total = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int64_t i = base + r * 64 + lane;
+            p[r] = (int)(i % BQ) < cnt[i / BQ] ? pop[i] : 0;
+            total += __popcll(__ballot(p[r] != 0));
         }
-        const uint64_t m = __ballot(take);
-        if (!m) continue;
+        if (!total) continue;
         unsigned long long b = 0;
-        const int first = __builtin_ctzll(m);
-        if (lane == first) b = atomicAdd(count, (unsigned long long)__popcll(m));
-        b = __shfl(b, first, 64);
-        if (take) {
+        if (lane == 0) b = atomicAdd(count, (unsigned long long)total);
+        b = __shfl(b, 0, 64);
+        if (b >= (unsigned long long)limit) continue;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint64_t m = __ballot(p[r] != 0);
             const unsigned long long j = b + (unsigned long long)__popcll(m & ((1ull << lane) - 1ull));
-            if (j < (unsigned long long)limit) {
-                odet[j] = D;
-                opop[j] = p;
+            if (p[r] != 0 && j < (unsigned long long)limit) {
+                odet[j] = kv[base + r * 64 + lane];
+                opop[j] = p[r];
             }
+            b += (unsigned long long)__popcll(m);
         }
     }
+}
+
+// ---------------------------------------------------------------------------
+// Sorting a list by determinant: a least-significant-digit radix sort of (determinant,
+// population) by 8-bit digits, three launches per digit. A wavefront owns SORT_RUN
+// consecutive entries through all of them, so the passes need no workgroup barrier and are
+// stable. Bound by memory: per digit every determinant is read twice and each entry
+// written once, in runs as long as a digit's share of a wavefront's entries.
+// Lanes of the same digit are found with eight ballots, not with LDS atomics: most
+// determinants of a list agree in most digits (the electrons below the Fermi level), and
+// 64 atomics on one counter are served one after another.
+// ---------------------------------------------------------------------------
+constexpr int SORT_RUN = 1024;
+
+__device__ __forceinline__ uint32_t sort_digit(det_t D, int shift) {
+    return (uint32_t)lo64(D >> shift) & 255u;
+}
+// Lanes of this wavefront with ok and the same digit.
+__device__ __forceinline__ uint64_t same_digit(uint32_t g, bool ok) {
+    uint64_t m = __ballot(ok);
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        const uint64_t v = __ballot((g >> b) & 1u);
+        m &= ((g >> b) & 1u) ? v : ~v;
+    }
+    return m;
+}
+
+// Occurrences of each digit in each run: hist[digit * nr + run].
+__global__ __launch_bounds__(256) void k_sort_count(const det_t *key, int64_t n, int64_t nr,
+                                                    int shift, uint32_t *hist) {
+    __shared__ uint32_t s_n[4][256];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int64_t run = blockIdx.x * 4ll + wid;
+    if (run >= nr) return;   // (no barrier below: a wavefront uses its own counters only)
+    for (int q = lane; q < 256; q += 64) s_n[wid][q] = 0u;
+    wave_sync();
+#pragma unroll 4
+    for (int r = 0; r < SORT_RUN / 64; ++r) {
+        const int64_t i = run * SORT_RUN + r * 64 + lane;
+        const bool ok = i < n;
+        const uint32_t g = ok ? sort_digit(key[i], shift) : 0u;
+        const uint64_t m = same_digit(g, ok);
+        if (ok && lane == __builtin_ctzll(m)) s_n[wid][g] += (uint32_t)__popcll(m);
+        wave_sync();
+    }
+    for (int q = lane; q < 256; q += 64) hist[q * nr + run] = s_n[wid][q];
+}
+
+// One workgroup per digit: its counts become their running sum over the runs, its total
+// goes to tot[digit].
+__global__ __launch_bounds__(256) void k_sort_scan(uint32_t *hist, int64_t nr, uint32_t *tot) {
+    __shared__ uint32_t s_w[4];
+    const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+    uint32_t *row = hist + (int64_t)blockIdx.x * nr;
+    uint32_t carry = 0;
+    for (int64_t b = 0; b < nr; b += 256) {
+        const uint32_t v = b + t < nr ? row[b + t] : 0u;
+        uint32_t x = v;
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        if (lane == 63) s_w[wid] = x;
+        __syncthreads();
+        uint32_t before = carry;
+        for (int w = 0; w < wid; ++w) before += s_w[w];
+        carry += s_w[0] + s_w[1] + s_w[2] + s_w[3];
+        if (b + t < nr) row[b + t] = before + x - v;
+        __syncthreads();
+    }
+    if (t == 0) tot[blockIdx.x] = carry;
+}
+
+// Every run's entries to their places.
+__global__ __launch_bounds__(256) void k_sort_move(const det_t *key, const int32_t *val, int64_t n,
+                                                   int64_t nr, int shift, const uint32_t *hist,
+                                                   const uint32_t *tot, det_t *okey,
+                                                   int32_t *oval) {
+    __shared__ uint32_t s_at[4][256];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    const int64_t run = blockIdx.x * 4ll + wid;
+    if (run >= nr) return;
+    uint32_t c[4], sum = 0;
+    for (int q = 0; q < 4; ++q) sum += c[q] = tot[lane * 4 + q];
+    uint32_t x = sum;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(x, o, 64);
+        if (lane >= o) x += y;
+    }
+    uint32_t at = x - sum;   // entries of smaller digits
+    for (int q = 0; q < 4; ++q) {
+        s_at[wid][lane * 4 + q] = at + hist[(lane * 4 + q) * nr + run];
+        at += c[q];
+    }
+    wave_sync();
+#pragma unroll 4
+    for (int r = 0; r < SORT_RUN / 64; ++r) {
+        const int64_t i = run * SORT_RUN + r * 64 + lane;
+        const bool ok = i < n;
+        const det_t D = ok ? key[i] : det_t(0ull);
+        const int32_t p = ok ? val[i] : 0;
+        const uint32_t g = sort_digit(D, shift);
+        const uint64_t m = same_digit(g, ok);
+        const uint32_t first = ok ? s_at[wid][g] : 0u;
+        wave_sync();
+        if (ok && lane == __builtin_ctzll(m)) s_at[wid][g] = first + (uint32_t)__popcll(m);
+        wave_sync();
+        const uint32_t j = first + (uint32_t)__popcll(m & ((1ull << lane) - 1ull));
+        if (ok) {
+            okey[j] = D;
+            oval[j] = p;
+        }
+    }
+}
+
+// Initiator flag of each of n entries: |pop| > n_a, or the reference.
+__global__ void k_flags(const det_t *key, const int32_t *val, int64_t n, int32_t n_a, uint64_t d0,
+                        uint64_t d0_hi, uint32_t *flags) {
+    const det_t ref = make_det(d0, d0_hi);
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t a = val[i] < 0 ? -(int64_t)val[i] : (int64_t)val[i];
+        flags[i] = (a > (int64_t)n_a || key[i] == ref) ? 1u : 0u;
+    }
+}
+
+hipError_t launch_flags(const uint64_t *key, const int32_t *val, int64_t n, int32_t n_a,
+                        uint64_t d0, uint64_t d0_hi, uint32_t *flags, hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    const int64_t g = (n + 255) / 256;
+    hipLaunchKernelGGL(k_flags, dim3((unsigned)(g < 8192 ? g : 8192)), dim3(256), 0, s,
+                       (const det_t *)key, val, n, n_a, d0, d0_hi, flags);
+    return hipGetLastError();
+}
+
+hipError_t launch_sort(uint64_t *key, int32_t *val, uint64_t *key2, int32_t *val2, uint32_t *hist,
+                       int64_t n, int passes, hipStream_t s) {
+    if (n < 1 || n > SORT_MAX || passes < 1 || passes > 8 * FQ_DET_WORDS)
+        return hipErrorInvalidValue;
+    const int64_t nr = (n + SORT_RUN - 1) / SORT_RUN;
+    uint32_t *tot = hist, *rows = hist + 256;
+    det_t *a = (det_t *)key, *b = (det_t *)key2;
+    const dim3 grid((unsigned)((nr + 3) / 4));
+    for (int k = 0; k < passes; ++k) {
+        hipLaunchKernelGGL(k_sort_count, grid, dim3(256), 0, s, (const det_t *)a, n, nr, 8 * k, rows);
+        hipLaunchKernelGGL(k_sort_scan, dim3(256), dim3(256), 0, s, rows, nr, tot);
+        hipLaunchKernelGGL(k_sort_move, grid, dim3(256), 0, s, (const det_t *)a,
+                           (const int32_t *)val, n, nr, 8 * k, (const uint32_t *)rows,
+                           (const uint32_t *)tot, b, val2);
+        std::swap(a, b);
+        std::swap(val, val2);
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_load(SysDesc *d_desc, int32_t sys, const uint64_t *det, const int32_t *pop,
@@ -2782,10 +2943,11 @@ hipError_t launch_rebucket(SysDesc *d_desc, int32_t sys, const uint64_t *src_key
 
 hipError_t launch_compact(const uint64_t *key, const int32_t *pop, const int32_t *cnt, int64_t nb,
                           uint64_t *out_det, int32_t *out_pop, unsigned long long *count,
-                          hipStream_t s) {
-    const int64_t g = (nb * BQ + 255) / 256;
-    hipLaunchKernelGGL(k_compact, dim3((unsigned)(g < 65536 ? g : 65536)), dim3(256), 0, s,
-                       (const det_t *)key, pop, cnt, nb, (det_t *)out_det, out_pop, count, nb * BQ);
+                          int64_t limit, hipStream_t s) {
+    const int64_t g = (nb / BPC + 3) / 4;
+    if (g == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_compact, dim3((unsigned)(g < 8192 ? g : 8192)), dim3(256), 0, s,
+                       (const det_t *)key, pop, cnt, nb, (det_t *)out_det, out_pop, count, limit);
     return hipGetLastError();
 }
 
@@ -2823,23 +2985,11 @@ __global__ void k_stage_bitonic(uint64_t *key, int32_t *val, int64_t P, int64_t 
     }
 }
 
-__global__ void k_stage_flags(const uint64_t *key, const int32_t *val, int64_t n, int32_t n_a,
-                              uint64_t d0, uint32_t *flags) {
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
-         i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t a = val[i] < 0 ? -(int64_t)val[i] : (int64_t)val[i];
-        flags[i] = (a > (int64_t)n_a || key[i] == d0) ? 1u : 0u;
-    }
-}
-
 hipError_t launch_stage_flags(void *stage, int64_t n, int32_t n_a, uint64_t d0, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
     char *p = (char *)stage;
-    const int64_t g = (n + 255) / 256;
-    hipLaunchKernelGGL(k_stage_flags, dim3((unsigned)(g < 8192 ? g : 8192)), dim3(256), 0, s,
-                       (const uint64_t *)(p + NOALLOC_KEYS_OFF), (const int32_t *)(p + NOALLOC_VALS_OFF),
-                       n, n_a, d0, (uint32_t *)(p + NOALLOC_FLAGS_OFF));
-    return hipGetLastError();
+    return launch_flags((const uint64_t *)(p + NOALLOC_KEYS_OFF),
+                        (const int32_t *)(p + NOALLOC_VALS_OFF), n, n_a, d0, 0,
+                        (uint32_t *)(p + NOALLOC_FLAGS_OFF), s);
 }
 
 hipError_t launch_stage_compact(const uint64_t *key, const int32_t *pop, const int32_t *cnt,
@@ -2847,11 +2997,8 @@ hipError_t launch_stage_compact(const uint64_t *key, const int32_t *pop, const i
     char *p = (char *)stage;
     unsigned long long *count = (unsigned long long *)p;
     hipLaunchKernelGGL(k_stage_clear, dim3(1), dim3(64), 0, s, count);
-    const int64_t g = (nb * BQ + 255) / 256;
-    hipLaunchKernelGGL(k_compact, dim3((unsigned)(g < 65536 ? g : 65536)), dim3(256), 0, s, key,
-                       pop, cnt, nb, (uint64_t *)(p + NOALLOC_KEYS_OFF),
-                       (int32_t *)(p + NOALLOC_VALS_OFF), count, (int64_t)NOALLOC_MAX_DETS);
-    return hipGetLastError();
+    return launch_compact(key, pop, cnt, nb, (uint64_t *)(p + NOALLOC_KEYS_OFF),
+                          (int32_t *)(p + NOALLOC_VALS_OFF), count, (int64_t)NOALLOC_MAX_DETS, s);
 }
 
 hipError_t launch_stage_sort(void *stage, int64_t n, hipStream_t s) {
