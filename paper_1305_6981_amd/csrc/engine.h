@@ -204,6 +204,18 @@ constexpr int NKERN = 5;   // profiled kernel groups: chunk sums, scans, spawn, 
 constexpr int64_t SORT_MAX = (int64_t)1 << 31;
 constexpr int64_t sort_hist_words(int64_t n) { return 256 * (1 + (n + 1023) / 1024); }
 
+// What the check of a walker list finds. `bad`: the first entry the system cannot hold, as
+// its number * 8 + the reason.
+enum { LIST_COUNTS = 1, LIST_RANGE = 2, LIST_SPACE = 3, LIST_PAIR = 4 };
+struct ListCheck {
+    unsigned long long bad = ~0ull;
+    unsigned long long nw = 0, nd = 0;   // walkers, entries with walkers
+    uint32_t most = 0;                   // largest |population|
+    int32_t c0 = 0, have_ref = 0;        // the reference's population, whether it has walkers
+    int32_t unsorted = 0;                // not strictly ascending, or an entry without walkers
+    int32_t twice = 0;
+};
+
 #define FQ_WIDTH_LAUNCHERS                                                                     \
     /* first: the spawn tiles are listed from the tables (the first iteration of a launch,    \
        after any host-side change); later iterations use the list the previous iteration's    \
@@ -211,7 +223,16 @@ constexpr int64_t sort_hist_words(int64_t n) { return 256 * (1 + (n + 1023) / 10
     void launch_iteration(const EngineArgs &a, int post_grid, int spawn_grid, bool first,      \
                           hipStream_t s, hipEvent_t *ev /* NKERN + 1 events or nullptr */);     \
     hipError_t launch_load(SysDesc *d_desc, int32_t sys, const uint64_t *det,                 \
-                           const int32_t *pop, int64_t n, uint32_t *d_err, hipStream_t s);      \
+                           const int32_t *pop, int64_t n, int add_ref, uint32_t *d_err,        \
+                           hipStream_t s);                                                     \
+    /* The checks and sums of a list to be loaded, into *out (which begins as the host's     \
+       ListCheck{}); na, nb: electrons of either spin. */                                     \
+    hipError_t launch_check_list(const SysDesc *desc, int32_t sys, const uint64_t *det,       \
+                                 const int32_t *pop, int64_t n, int na, int nb,               \
+                                 ListCheck *out, hipStream_t s);                              \
+    /* Sets out->twice if a sorted list has walkers twice on one determinant. */              \
+    hipError_t launch_twice(const uint64_t *det, const int32_t *pop, int64_t n,               \
+                            ListCheck *out, hipStream_t s);                                   \
     /* Move every entry of the buckets (src_*, src_nb buckets, counts src_cnt) and the spill  \
        entries of system sys into the descriptor's (empty) buckets. */                        \
     hipError_t launch_rebucket(SysDesc *d_desc, int32_t sys, const uint64_t *src_key,         \

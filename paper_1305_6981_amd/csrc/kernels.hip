@@ -2687,13 +2687,94 @@ __device__ __forceinline__ bool bucket_put(const SysDesc &d, det_t D, int32_t p,
     return true;
 }
 
+// (add_ref: the reference is not among the entries and is put in without walkers)
 __global__ void k_load(SysDesc *desc, int32_t sys, const det_t *det, const int32_t *pop,
-                       int64_t n, uint32_t *err) {
+                       int64_t n, int add_ref, uint32_t *err) {
     const SysDesc &d = desc[sys];
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n + add_ref;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const det_t D = i < n ? det[i] : ref_of(d);
+        const int32_t p = i < n ? pop[i] : 0;
+        if (p == 0 && i < n) continue;
+        if (!bucket_put(d, D, p, fn_diag(d, D))) atomicOr(err, 1u);
+    }
+}
+
+// What a walker list to be loaded into system sys holds: its sums, whether it ascends
+// strictly without an empty entry, and the first entry that the system cannot hold (entry
+// number * 8 + reason, LIST_*). Bound by the list's memory traffic.
+__global__ __launch_bounds__(256) void k_check_list(const SysDesc *desc, int32_t sys,
+                                                    const det_t *det, const int32_t *pop,
+                                                    int64_t n, int na, int nb, ListCheck *out) {
+    const SysDesc &d = desc[sys];
+    const det_t ref = ref_of(d), valid = valid_of(d);
+    unsigned long long bad = ~0ull;
+    long long nw = 0;
+    int nd = 0, unsorted = 0;
+    uint32_t most = 0;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
          i += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t p = pop[i];
+        if (p == 0) {
+            unsorted = 1;
+            continue;
+        }
         const det_t D = det[i];
-        if (!bucket_put(d, D, pop[i], fn_diag(d, D))) atomicOr(err, 1u);
+        if (i + 1 < n && !(D < det[i + 1])) unsorted = 1;
+        int why = 0;
+        if ((bool)(D & ~valid) || dpopc(D & even_bits()) != na || dpopc(D & odd_bits()) != nb)
+            why = LIST_COUNTS;
+        else if (p == INT32_MIN)
+            why = LIST_RANGE;
+        else if (!in_space(d, D))
+            why = LIST_SPACE;
+        else if (d.hphf) {
+            const det_t f = spin_flip(D);
+            if (f < D || (f == D && d.hphf < 0)) why = LIST_PAIR;
+        }
+        const unsigned long long at = (unsigned long long)i * 8ull + (unsigned long long)why;
+        if (why && at < bad) bad = at;
+        if (D == ref) {
+            out->c0 = p;
+            out->have_ref = 1;
+        }
+        const uint32_t q = p < 0 ? 0u - (uint32_t)p : (uint32_t)p;
+        nw += q;
+        nd++;
+        most = q > most ? q : most;
+    }
+    nw = wave_sum(nw);
+    const long long nds = wave_sum((long long)nd);
+    for (int o = 32; o; o >>= 1) {
+        const unsigned long long b = __shfl_xor(bad, o, 64);
+        const uint32_t q = __shfl_xor(most, o, 64);
+        bad = b < bad ? b : bad;
+        most = q > most ? q : most;
+    }
+    const bool any = __ballot(unsorted) != 0;
+    if ((threadIdx.x & 63) == 0) {
+        if (nds) {
+            atomicAdd(&out->nw, (unsigned long long)nw);
+            atomicAdd(&out->nd, (unsigned long long)nds);
+            atomicMax(&out->most, most);
+        }
+        if (bad != ~0ull) atomicMin(&out->bad, bad);
+        if (any) atomicOr(&out->unsorted, 1);
+    }
+}
+
+// Whether a sorted list holds two entries with walkers on one determinant (entries without
+// walkers between them do not count).
+__global__ __launch_bounds__(256) void k_twice(const det_t *det, const int32_t *pop, int64_t n,
+                                               ListCheck *out) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        if (pop[i] == 0) continue;
+        for (int64_t j = i - 1; j >= 0 && det[j] == det[i]; --j)
+            if (pop[j] != 0) {
+                out->twice = 1;
+                break;
+            }
     }
 }
 
@@ -2920,11 +3001,30 @@ hipError_t launch_sort(uint64_t *key, int32_t *val, uint64_t *key2, int32_t *val
 }
 
 hipError_t launch_load(SysDesc *d_desc, int32_t sys, const uint64_t *det, const int32_t *pop,
-                       int64_t n, uint32_t *d_err, hipStream_t s) {
+                       int64_t n, int add_ref, uint32_t *d_err, hipStream_t s) {
+    if (n + add_ref <= 0) return hipSuccess;
+    const int64_t g = (n + add_ref + 255) / 256;
+    hipLaunchKernelGGL(k_load, dim3((unsigned)(g < 65536 ? g : 65536)), dim3(256), 0, s, d_desc,
+                       sys, (const det_t *)det, pop, n, add_ref, d_err);
+    return hipGetLastError();
+}
+
+hipError_t launch_check_list(const SysDesc *desc, int32_t sys, const uint64_t *det,
+                             const int32_t *pop, int64_t n, int na, int nb, ListCheck *out,
+                             hipStream_t s) {
     if (n <= 0) return hipSuccess;
     const int64_t g = (n + 255) / 256;
-    hipLaunchKernelGGL(k_load, dim3((unsigned)(g < 65536 ? g : 65536)), dim3(256), 0, s, d_desc,
-                       sys, (const det_t *)det, pop, n, d_err);
+    hipLaunchKernelGGL(k_check_list, dim3((unsigned)(g < 2048 ? g : 2048)), dim3(256), 0, s, desc,
+                       sys, (const det_t *)det, pop, n, na, nb, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_twice(const uint64_t *det, const int32_t *pop, int64_t n, ListCheck *out,
+                        hipStream_t s) {
+    if (n <= 0) return hipSuccess;
+    const int64_t g = (n + 255) / 256;
+    hipLaunchKernelGGL(k_twice, dim3((unsigned)(g < 65536 ? g : 65536)), dim3(256), 0, s,
+                       (const det_t *)det, pop, n, out);
     return hipGetLastError();
 }
 
