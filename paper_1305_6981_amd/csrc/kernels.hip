@@ -730,6 +730,12 @@ __device__ __forceinline__ double fn_diag_from(const SysDesc &d, det_t D, double
 }
 __device__ double fn_diag(const SysDesc &d, det_t D) { return fn_diag_from(d, D, hdiag_of(d, D)); }
 
+// The same, with nothing to add for determinants (PLAIN: EngineArgs::plain).
+template <bool PLAIN>
+__device__ __forceinline__ double diag_from(const SysDesc &d, det_t D, double hd) {
+    return PLAIN ? hd : fn_diag_from(d, D, hd);
+}
+
 // Projected-energy element <Phi_0|H|Phi_D> (Eq. ProjE) and whether it can be
 // nonzero (D within a double excitation of the reference, or its partner).
 // (PLAIN: determinants, EngineArgs::plain.)
@@ -1847,21 +1853,93 @@ __device__ __forceinline__ int wl_claim_limited(det_t D, WaveLds &W, int *ncl, b
 }
 #endif
 
-// H_DD = E_core + sum_p h_pp + sum_{p<q} [(pp|qq) - (pq|qp)], accumulated in
-// ascending (p, q) order from the LDS copies of h_pp and of the pair table (its
-// upper triangle, row after row: entry (p, q) at pair_row(p, n) + q), for two
-// determinants with the same number of electrons at once: the two sums are
-// independent chains that hide each other's add latency, and each keeps the
-// order of a single sum.
+// The LDS copy of the pair table is its upper triangle, row after row: entry (p, q) at
+// pair_row(p, n) + q (one entry before the first is readable, see hdiag_lds).
 __device__ __forceinline__ int pair_row(int p, int n) { return p * (2 * n - p - 3) / 2 - 1; }
-
-// The table loads of four partners q are issued before their four dependent adds, so a
-// sum waits once per four loads instead of once per load (nel: electrons, uniform).
 __device__ __forceinline__ int take_low(det_t &m) {
     const int q = dctz(m);
     m &= m - 1ull;
     return q;
 }
+#if FQ_DET_WORDS == 1
+// H_DD = E_core + sum_p h_pp + sum_{p<q} [(pp|qq) - (pq|qp)], accumulated in ascending
+// (p, q) order from the LDS copies of h_pp and of the pair table (nel: electrons, uniform).
+// A chain of N (N - 1) / 2 dependent adds: bound by latency where a workgroup has few new
+// determinants, by the instructions between the adds where it has many. So the occupied
+// spin orbitals are taken out of the determinant once, a byte each, and the sum walks over
+// words of four of them: while four entries are added, the next four are read. (Finding each
+// partner's bit in the 64-bit word as it came up is eight instructions a pair.) A word's
+// entries outside the sum (partners up to i, past the last) are read as well and left out:
+// q <= p falls on an earlier row, at least on entry -1. A function of its own: inlined, its
+// values spilled registers of the whole kernel. k_post with it, in us: 24 electrons 117 -> 103
+// (3.5e6 walkers) and 1281 -> 1195 (1.4e8), 10 electrons 86 -> 78 (1.1e7).
+typedef uint32_t v16u32 __attribute__((ext_vector_type(16)));
+typedef __attribute__((address_space(3))) const double lds_double;
+__device__ __attribute__((noinline)) double hdiag_lds(double e_core, det_t D, int nel, lds_double *hpp,
+                                 lds_double *jk, int n) {
+    nel = (int)uni((uint32_t)nel);
+    n = (int)uni((uint32_t)n);
+    const int words = (nel + 3) >> 2;
+    v16u32 occ = 0u;
+    double x = e_core;
+    for (int w = 0; w < words; ++w) {
+        uint32_t v = 0u;
+        double h[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (4 * w + u >= nel) break;
+            const int q = take_low(D);
+            v |= (uint32_t)q << (8 * u);
+            h[u] = hpp[q];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (4 * w + u < nel) x = x + h[u];
+        occ[w] = v;
+    }
+    if (nel < 2) return x;
+    int i = 0, w = 0;   // electron i with the partners in word w
+    lds_double *row = jk + pair_row((int)(occ[0] & 255u), n);
+    double c[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) c[u] = row[(occ[0] >> (8 * u)) & 255u];
+    for (;;) {
+        int i2 = i, w2 = w + 1;
+        if (w2 >= words) {
+            i2 = i + 1;
+            w2 = (i2 + 1) >> 2;
+        }
+        const bool more = i2 < nel - 1;
+        double e[4] = {0.0, 0.0, 0.0, 0.0};
+        if (more) {
+            if (i2 != i) row = jk + pair_row((int)((occ[i2 >> 2] >> (8 * (i2 & 3))) & 255u), n);
+            const uint32_t v = occ[w2];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) e[u] = row[(v >> (8 * u)) & 255u];
+        }
+        const int lo = i + 1 - 4 * w, hi = nel - 4 * w;
+        if (lo <= 0 && hi >= 4) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x = x + c[u];
+        } else {
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (u >= lo && u < hi) x = x + c[u];
+        }
+        if (!more) break;
+        i = i2;
+        w = w2;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) c[u] = e[u];
+    }
+    return x;
+}
+#endif
+
+#if FQ_DET_WORDS == 2
+// The same for two determinants of two words with the same number of electrons at once: two
+// independent chains that hide each other's add latency. The table loads of four partners q
+// are issued before their four dependent adds, so a sum waits once per four loads.
 __device__ __forceinline__ void hdiag_lds2(double e_core, det_t da, det_t db, int nel,
                                            const double *hpp, const double *jk, int n,
                                            double &ra, double &rb) {
@@ -1897,7 +1975,6 @@ __device__ __forceinline__ void hdiag_lds2(double e_core, det_t da, det_t db, in
     rb = xb;
 }
 
-#if FQ_DET_WORDS == 2
 // As hdiag_lds2, with the pair table read from global memory ([n_so][NSO_MAX],
 // entry (p, q) at p NSO_MAX + q): for more than 64 spin orbitals, whose upper
 // triangle would take 65 KB of LDS.
@@ -1923,9 +2000,22 @@ __device__ __forceinline__ void hdiag_glb2(double e_core, det_t da, det_t db, co
 #endif
 
 // Diagonal elements of the queued new determinants (positions in the system's
-// arrays, all of one system, so all with the same electron count), two per
-// thread at a time; the pair table from LDS (jk), or from global memory when jk is
-// null (two-word determinants of more than 64 spin orbitals).
+// arrays, all of one system, so all with the same electron count). One word: a lane each,
+// the pair table in LDS. Two words: two per thread at a time; the pair table from LDS (jk),
+// or from global memory when jk is null (more than 64 spin orbitals).
+#if FQ_DET_WORDS == 1
+template <bool PLAIN>
+__device__ __forceinline__ void flush_new_dets(const SysDesc &d, const uint32_t *queue, int n,
+                                               const double *hpp, const double *jk) {
+    for (int j = threadIdx.x; j < n; j += (int)blockDim.x) {
+        const uint32_t i = queue[j];
+        const det_t k = ldk(keys_of(d) + i);
+        const double h = hdiag_lds(d.e_core, k, d.N, (lds_double *)hpp, (lds_double *)jk, d.n_so);
+        *gp(d.hdiag + i) = diag_from<PLAIN>(d, k, h);
+    }
+}
+#else
+template <bool PLAIN>
 __device__ __forceinline__ void flush_new_dets(const SysDesc &d, const uint32_t *queue, int n,
                                                const double *hpp, const double *jk) {
     const int step = 2 * (int)blockDim.x;
@@ -1935,18 +2025,109 @@ __device__ __forceinline__ void flush_new_dets(const SysDesc &d, const uint32_t 
         const uint32_t i1 = two ? queue[j + blockDim.x] : i0;
         double h0, h1;
         const det_t k0 = ldk(keys_of(d) + i0), k1 = ldk(keys_of(d) + i1);
-#if FQ_DET_WORDS == 1
-        hdiag_lds2(d.e_core, k0, k1, d.N, hpp, jk, d.n_so, h0, h1);
-#else
         if (jk)
             hdiag_lds2(d.e_core, k0, k1, d.N, hpp, jk, d.n_so, h0, h1);
         else
             hdiag_glb2(d.e_core, k0, k1, hpp, d.jk, h0, h1);
-#endif
-        *gp(d.hdiag + i0) = fn_diag_from(d, k0, h0);
-        if (two) *gp(d.hdiag + i1) = fn_diag_from(d, k1, h1);
+        *gp(d.hdiag + i0) = diag_from<PLAIN>(d, k0, h0);
+        if (two) *gp(d.hdiag + i1) = diag_from<PLAIN>(d, k1, h1);
     }
 }
+
+// The same for a queue too short to fill the workgroup, where one lane per determinant is a
+// chain of hundreds of dependent steps behind the staging of the tables: the whole workgroup
+// gathers the terms
+// of up to `cap` determinants from the tables in memory into LDS, then one lane per
+// determinant adds them up in their order. A determinant takes `stride` bytes of LDS: itself,
+// the numbers of its occupied spin orbitals, and its terms (h_pp of its N electrons, then
+// the pairs in ascending (p, q) order), an odd number of places in all so that the adding
+// lanes meet different banks. Whole workgroup; the queue is complete and `lds` free.
+struct FewDets {
+    int terms, stride, cap;   // per determinant: terms, bytes of LDS; determinants at once
+    __device__ __forceinline__ FewDets(int nel, int bytes) {
+        terms = nel * (nel + 1) / 2;
+        // (in units of a determinant, an odd number of them)
+        constexpr int U = (int)sizeof(det_t);
+        stride = ((terms * 8 + NSO_MAX + 2 * U - 1) / U | 1) * U;
+        cap = bytes / stride < 256 ? bytes / stride : 256;
+    }
+};
+template <bool PLAIN>
+__device__ __forceinline__ void flush_few(const SysDesc &d, const uint32_t *queue, int n,
+                                          const FewDets &f, char *lds) {
+    const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
+    const int N = d.N;
+    const int per_it = 256 / f.terms, rest = 256 % f.terms;
+    const auto key_at = [&](int j) { return (det_t *)(lds + j * f.stride); };
+    const auto orb_at = [&](int j) { return (uint8_t *)(lds + j * f.stride + sizeof(det_t)); };
+    const auto sum_at = [&](int j) { return (double *)(lds + j * f.stride + sizeof(det_t) + NSO_MAX); };
+    for (int j0 = 0; j0 < n; j0 += f.cap) {
+        const int m = n - j0 < f.cap ? n - j0 : f.cap;
+        uint32_t at = 0u;
+        if (t < m) {
+            at = queue[j0 + t];
+            *key_at(t) = ldk(keys_of(d) + at);
+        }
+        __syncthreads();
+        for (int j = wid; j < m; j += 4) {
+            const det_t D = *key_at(j);
+            uint8_t *const o = orb_at(j);
+            for (int p = lane; p < 64 * FQ_DET_WORDS; p += 64)
+                if ((bool)(D & DBIT(p))) o[dpopc(D & (DBIT(p) - 1ull))] = (uint8_t)p;
+        }
+        __syncthreads();
+        // term k of determinant j; the next one of this thread is 256 terms on
+        int j = t / f.terms, k = t % f.terms;
+        while (j < m) {
+            double x[8];
+            double *to[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                to[u] = nullptr;
+                if (j < m) {
+                    const uint8_t *const o = orb_at(j);
+                    to[u] = sum_at(j) + k;
+                    if (k < N) {
+                        x[u] = h_so(d, o[k], o[k]);
+                    } else {
+                        // the pair: row i begins at term i (2 N - i - 1) / 2 of the pairs
+                        const int v = k - N, b = 2 * N - 1;
+                        int i = (int)(((float)b - sqrtf((float)(b * b - 8 * v))) * 0.5f);
+                        i = i * (b - i) / 2 > v ? i - 1 : i;
+                        i = (i + 1) * (b - i - 1) / 2 <= v ? i + 1 : i;
+                        x[u] = gptr(d.jk)[o[i] * NSO_MAX + o[i + 1 + v - i * (b - i) / 2]];
+                    }
+                }
+                j += per_it;
+                k += rest;
+                if (k >= f.terms) {
+                    k -= f.terms;
+                    ++j;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (to[u]) *to[u] = x[u];
+        }
+        __syncthreads();
+        if (t < m) {
+            const double *const v = sum_at(t);
+            double x = d.e_core;
+            int i = 0;
+            for (; i + 8 <= f.terms; i += 8) {
+                double y[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) y[u] = v[i + u];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) x = x + y[u];
+            }
+            for (; i < f.terms; ++i) x = x + v[i];
+            *gp(d.hdiag + at) = diag_from<PLAIN>(d, *key_at(t), x);
+        }
+        __syncthreads();
+    }
+}
+#endif
 
 // Adding up statistics: by their owner, and (any order) into a system's share in memory.
 __device__ __forceinline__ void add_stat(IterStat &x, const IterStat &y) {
@@ -1982,6 +2163,7 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
     // Each wavefront's working set, and (between chunks only) the pair table from
     // which the diagonal elements of new determinants are computed.
     struct PairTable {
+        double before;            // (read as entry -1, never used)
         double jk[64 * 63 / 2];   // (up to 64 spin orbitals)
         double hpp[NSO_MAX];
     };
@@ -2008,7 +2190,9 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
     __shared__ uint32_t s_nr[POST_WIN * BPC];        // records per bucket
     __shared__ unsigned long long s_bnw[POST_WIN * BPC];   // walkers per bucket that spawn next
     __shared__ int s_qn, s_qsys;
+#if FQ_DET_WORDS == 1
     __shared__ int s_tabsys;                         // system whose pair table is staged (-1: none)
+#endif
     __shared__ int s_ncl[POST_WAVES];
     __shared__ int64_t s_win;                        // first chunk of the window taken
     __shared__ unsigned int s_len[NLIST];            // windows per list
@@ -2035,26 +2219,59 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
     if (t == 0) {
         s_qn = 0;
         s_qsys = -1;
+#if FQ_DET_WORDS == 1
         s_tabsys = -1;
+#endif
         s_accsys = -1;
         for (int w = 0; w < POST_WAVES; ++w) s_acc[w] = IterStat{};
     }
     auto flush = [&]() {   // (uniform) H_DD of the queued new determinants
-        const SysDesc &dq = desc[s_qsys];
-        const bool in_lds = dq.n_so <= 64;   // the pair table's upper triangle fits in LDS
-        if (FQ_DET_WORDS == 2 || s_tabsys != s_qsys) {   // (uniform) stage the system's tables
-            if (in_lds)
-                for (int i = t; i < dq.n_so * 64; i += 256) {
-                    const int p = i >> 6, q = i & 63;
-                    if (q > p && q < dq.n_so)
-                        L.tab.jk[pair_row(p, dq.n_so) + q] = gptr(dq.jk)[p * NSO_MAX + q];
+        const int sq = (int)uni((uint32_t)s_qsys);
+        const int qn = (int)uni((uint32_t)s_qn), nq = qn < POST_QUEUE ? qn : POST_QUEUE;
+        const SysDesc &dq = desc[sq];
+#if FQ_DET_WORDS == 1
+        if (s_tabsys != sq) {   // (uniform)
+            const int n = dq.n_so, q = t & 63;
+#pragma unroll
+            for (int v = 0; v < 64; v += 32) {
+                if (v >= n) break;
+                double x[8];   // (eight loads under way at a time)
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int p = v + 4 * u + wid;
+                    x[u] = q > p && q < n ? gptr(dq.jk)[p * NSO_MAX + q] : 0.0;
                 }
-            for (int i = t; i < dq.n_so; i += 256) L.tab.hpp[i] = h_so(dq, i, i);
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int p = v + 4 * u + wid;
+                    if (q > p && q < n) L.tab.jk[pair_row(p, n) + q] = x[u];
+                }
+            }
+            if (t < n) L.tab.hpp[t] = h_so(dq, t, t);
             __syncthreads();
-            if (t == 0) s_tabsys = s_qsys;   // (read again only after the barrier below)
+            if (t == 0) s_tabsys = sq;   // (read again only after the barrier below)
         }
-        flush_new_dets(dq, s_queue, s_qn < POST_QUEUE ? s_qn : POST_QUEUE, L.tab.hpp,
-                       in_lds ? L.tab.jk : nullptr);
+        flush_new_dets<PLAIN>(dq, s_queue, nq, L.tab.hpp, L.tab.jk);
+#else
+        // Few of them, up to four of flush_few's batches (a batch takes 3 to 5 us; staging the
+        // tables, which two words have no room to keep, 7, and a sum from them 10 to 20: k_post
+        // with 10 electrons in 36 orbitals 73 -> 61 us at 2.2e6 walkers).
+        const FewDets few(dq.N, (int)sizeof L);
+        if (nq <= 4 * few.cap) {
+            flush_few<PLAIN>(dq, s_queue, nq, few, (char *)&L);
+            return;
+        }
+        const bool in_lds = dq.n_so <= 64;   // the pair table's upper triangle fits in LDS
+        if (in_lds)
+            for (int i = t; i < dq.n_so * 64; i += 256) {
+                const int p = i >> 6, q = i & 63;
+                if (q > p && q < dq.n_so)
+                    L.tab.jk[pair_row(p, dq.n_so) + q] = gptr(dq.jk)[p * NSO_MAX + q];
+            }
+        for (int i = t; i < dq.n_so; i += 256) L.tab.hpp[i] = h_so(dq, i, i);
+        __syncthreads();
+        flush_new_dets<PLAIN>(dq, s_queue, nq, L.tab.hpp, in_lds ? L.tab.jk : nullptr);
+#endif
         __syncthreads();
     };
     auto flush_stat = [&]() {   // (thread f < 7 hands over the f-th number)
@@ -2529,7 +2746,7 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                     if ((todo >> 5) & 1u) {
                         double *const to = diag >= DIAG_SPILL ? a.sp_hd + (diag - DIAG_SPILL)
                                                               : d.hdiag + base + diag;
-                        *gp(to) = fn_diag(d, rd);
+                        *gp(to) = diag_from<PLAIN>(d, rd, hdiag_of(d, rd));
                     }
                 }
             }

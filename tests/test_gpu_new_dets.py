@@ -52,3 +52,23 @@ def test_systems_alternate():
         assert np.array_equal(d, do) and np.array_equal(p, po), slot
         ref.close()
     F.fciqmc_free(h)
+
+
+@pytest.mark.parametrize("m,na,nb", [(32, 31, 1), (32, 16, 17), (20, 1, 0), (33, 2, 1), (40, 20, 21),
+                                     (64, 64, 63)])
+def test_table_edges(m, na, nb):
+    """Electron counts at the ends of the words of four in which the sums run, up to all
+    spin orbitals but one, in tables of up to 64 spin orbitals and of more; and where no
+    determinant's terms fit the workgroup's memory at once (127 electrons)."""
+    ham = S.synthetic_molecule(m, na, nb, 11)
+    prm = S.Params(tau=4e-3, initiator_threshold=0, target_walkers=10**9, initial_walkers=6000,
+                   initial_shift=1.0, seed=3 * m + na)
+    print(f"[gpu] new determinants: {na}+{nb} electrons in {m} orbitals", flush=True)
+    gpu, ref = F.Solver(ham, prm, F.current_stream()), O.Oracle(ham, prm)
+    gpu.iterate(5)
+    ref.iterate(5)
+    (dg, pg, _), (do, po, _) = gpu.walkers(), ref.walkers()
+    assert len(pg) > (5 if na + nb == 1 else 40)
+    assert np.array_equal(dg, do) and np.array_equal(pg, po)
+    gpu.close()
+    ref.close()
