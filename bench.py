@@ -57,10 +57,9 @@ ALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 OPS_PER_ATTEMPT = 252
 PROFILES = os.path.join(ROOT, "profiles")
 GROUPS = ["chunk_sums", "scans", "spawn", "annihilation", "statistics"]
-# Kernels of each group (the annihilation group is the record sort and k_post).
-GROUP_KERNELS = {"spawn": ["k_spawn"],
-                 "annihilation": ["k_fix", "k_bscan_up", "k_bscan_top", "k_bscan_down",
-                                  "k_scatter", "k_post"]}
+# Kernels of each group (k_spawn writes its records into their buckets' slots, so that
+# annihilation is one kernel).
+GROUP_KERNELS = {"spawn": ["k_spawn"], "annihilation": ["k_post"]}
 
 
 def log(*a):
@@ -130,12 +129,13 @@ def history(F, h, first, n):
 
 
 def method_bytes(recs, nd_before):
-    """Algorithmic HBM bytes per iteration of the annihilation group and of k_post alone
-    (mean over the records), counted per occupied determinant (21 B read: key, population,
-    H_DD and the initiator flag; 4 B population written by death), per spawn record (16 B
-    read by the annihilation pass; 32 B more to partition it by bucket: read and write),
-    per merged spawn target (8 B key + 4 B population read, 4 B written) and per new
-    determinant (20 B: key, population, H_DD written)."""
+    """Algorithmic HBM bytes per iteration of an annihilation that partitions its records by
+    bucket, and of k_post, whose records k_spawn has written into their buckets' slots (mean
+    over the records), counted per occupied determinant (21 B read: key, population, H_DD and
+    the initiator flag; 4 B population written by death), per spawn record (16 B read by the
+    annihilation pass; 32 B more to partition it by bucket: read and write), per merged
+    spawn target (8 B key + 4 B population read, 4 B written) and per new determinant (20 B:
+    key, population, H_DD written)."""
     group, post = [], []
     prev = nd_before
     for r in recs:
@@ -442,8 +442,7 @@ def pmc_means(path, last=0):
     return out
 
 
-TRAFFIC_KERNELS = ("k_spawn", "k_fix", "k_bscan_up", "k_bscan_top", "k_bscan_down",
-                   "k_scatter", "k_post", "k_chunk_sum")
+TRAFFIC_KERNELS = ("k_spawn", "k_post", "k_tiles")
 CALIBRATION_KERNEL = "MulFunctor"
 
 
@@ -687,7 +686,7 @@ def main():
     grp_ms = {g: float(kms[i] / max(kcnt[i], 1)) for i, g in enumerate(GROUPS)}
     prof_ms = (sum(kms) / max(kcnt[2], 1))
     att_launch = float(np.mean([r["attempts"] for r in prec]))
-    b_group, b_post = method_bytes(prec, ep0["n_dets"])
+    _, b_post = method_bytes(prec, ep0["n_dets"])
     copy_gbs = stream_bandwidth()
 
     spawn_ms = grp_ms["spawn"]
@@ -702,12 +701,12 @@ def main():
                 "issue_frac": (issued * att_launch / (spawn_ms * 1e-3) / 1e12 / ALU_PEAK_TOPS
                                if issued else None)}
     ann_ms = grp_ms["annihilation"]
-    ach = b_group / (ann_ms * 1e-3) / 1e9
-    roofline_ann = {"bound": "hbm", "kernel": "annihilation (k_fix, k_bscan_*, k_scatter, k_post)",
+    ach = b_post / (ann_ms * 1e-3) / 1e9
+    roofline_ann = {"bound": "hbm", "kernel": "annihilation (k_post)",
                     "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                     "frac": ach / HBM_PEAK_GBS,
                     "traffic": measured_traffic(GROUP_KERNELS["annihilation"]),
-                    "algorithmic_bytes": b_group, "k_post_algorithmic_bytes": b_post,
+                    "algorithmic_bytes": b_post, "k_post_algorithmic_bytes": b_post,
                     "avg_ms": ann_ms, "measured_copy_gbs": copy_gbs,
                     "frac_of_measured_copy": ach / copy_gbs,
                     "k_post_issued_lane_ops_per_det": issued_ops_per("k_post", "det")}

@@ -90,8 +90,9 @@ typedef struct {
                                    up to whole chunks of 1024); the list is re-bucketed as it
                                    grows, and results do not depend on it */
     int64_t spawn_capacity;     /* initial capacity of the handle's spawn-record buffer in
-                                   records (0: automatic); it grows by itself (an iteration
-                                   that overflows it is re-run bit-exactly) */
+                                   records, shared out among the buckets (0: automatic); it
+                                   grows by itself (an iteration that overflows a bucket's
+                                   slots is re-run bit-exactly) */
     uint64_t seed;              /* Philox key */
     int32_t avg_start;          /* iterations after the shift starts varying before samples
                                    enter the averages */
@@ -168,8 +169,8 @@ typedef struct {
                                    re-bucketed; results unaffected) */
     /* Device time (ms) of the phases of one iteration of the handle: the last
      * iteration of the last fciqmc_iterate call runs as direct launches bracketed
-     * by events (the others run in graphs). Spawning includes the attempt mapping
-     * (chunk scans); death runs inside the annihilation pass, so ms_death is 0 and
+     * by events (the others run in graphs). Spawning includes the listing of its
+     * tiles in a call of one iteration; death runs inside the annihilation pass, so ms_death is 0 and
      * its time is part of ms_annihilate; the estimators include the shift. */
     double ms_spawn, ms_death, ms_annihilate, ms_estimators;
     int64_t born;               /* determinants that entered the main list: unoccupied
@@ -205,8 +206,8 @@ int fciqmc_init(const fciqmc_hamiltonian *ham, const fciqmc_params *prm, void *h
  * the main list with the initiator rule for unoccupied children (Sec. 4.2);
  * the estimators (Eq. ProjE) and the shift update (Sec. 2). Iterations run in
  * graph-captured launches of up to 64; the main list is re-bucketed as it
- * grows, and an iteration that overflows the spawn-record buffer is re-run
- * bit-exactly after the buffer grows.
+ * grows, and an iteration that overflows a bucket's record slots is re-run
+ * bit-exactly with more of them.
  * Errors: EINVAL, EDEVICE, ECAPACITY, EOVERFLOW. */
 int fciqmc_iterate(fciqmc_t *h, int32_t n_iterations);
 
@@ -305,12 +306,13 @@ int32_t fciqmc_batch_active(fciqmc_t *h);
  * Per-kernel-group device time (ms) accumulated since the last reset, measured
  * with HIP events on the handle's stream around each group of non-graph
  * launches (enable with fciqmc_set_profiling(h, 1); graph launches are then
- * disabled). Groups: 0 chunk sums of |C| (first iteration of a launch),
- * 1 attempt mapping (chunk scans), 2 spawning (Sec. 2, 5: records of the
- * accepted spawns), 3 annihilation (the records sorted by bucket, then death,
- * merge and annihilation per bucket: Eq. pdeath, Sec. 4.1, 4.2),
- * 4 statistics reduction / shift (Eq. ProjE, Sec. 2). counts[k] is the number
- * of launches measured. */
+ * disabled). Groups: 0 listing of the spawn tiles (first iteration of a
+ * launch; later ones are listed by the annihilation of the iteration before),
+ * 1 unused (no launch of its own any more), 2 spawning (Sec. 2, 5: the accepted
+ * spawns, written as records into their buckets' slots), 3 annihilation (merge,
+ * death and annihilation per bucket: Eq. pdeath, Sec. 4.1, 4.2),
+ * 4 statistics / shift (Eq. ProjE, Sec. 2). counts[k] is the number of launches
+ * measured. */
 int fciqmc_set_profiling(fciqmc_t *h, int32_t on);
 int fciqmc_kernel_times(fciqmc_t *h, double ms[5], int64_t counts[5]);
 
@@ -319,10 +321,13 @@ int fciqmc_kernel_times(fciqmc_t *h, double ms[5], int64_t counts[5]);
 int64_t fciqmc_history(fciqmc_t *h, int32_t slot, int64_t first, int64_t n, fciqmc_iteration *out);
 
 /* ---- launch shape ----------------------------------------------------------
- * spawn_grid: workgroups of the spawning kernel; tile: consecutive attempts a
- * workgroup takes at a time (a power of two, 256 .. 2^20; a tile never spans
- * two chunks of the table); post_grid: workgroups of the
- * death/annihilation kernel. Results never depend on these (every random
+ * spawn_grid: workgroups of the spawning kernel; tile: consecutive attempts its
+ * four wavefronts take at a time (a power of two, 256 .. 2^20), a quarter each
+ * and at most 512 (256 with two-word determinants; a wavefront's tile never
+ * spans two buckets of the list);
+ * post_grid: workgroups of the death/annihilation kernel. Until one of these
+ * calls sets a shape, small populations run with smaller tiles and grids than
+ * fciqmc_get_launch returns. Results never depend on these (every random
  * number is keyed by determinant and walker ordinal, every merge is an
  * integer sum). fciqmc_autotune saves every active system (walker list,
  * dynamics, statistics, iteration log), runs iters_per_trial iterations of all
@@ -363,14 +368,15 @@ int64_t fciqmc_walkers_noalloc(fciqmc_t *h, uint64_t *det, int32_t *pop, uint32_
 int fciqmc_blocking(const double *num, const double *den, int64_t n, double *mean, double *err);
 
 /* ---- test knobs -------------------------------------------------------------
- * planner = 0: do not size the buckets or the spawn-record buffer before each
- * launch, so that overflows are met inside an iteration: an overflowing record
- * buffer abandons the iteration, grows and re-runs it (fciqmc_estimates.redos),
+ * planner = 0: do not size the buckets or their record slots before each
+ * launch, so that overflows are met inside an iteration: overflowing record
+ * slots abandon the iteration, which is re-run with more (fciqmc_estimates.redos),
  * an overflowing bucket completes the iteration through the spill list and is
  * re-bucketed (fciqmc_estimates.spills). record_capacity > 0 replaces the record
- * buffer by one of that many records now (0: leave it). tile_map_limit >= 0 caps
- * the map from spawn tiles to chunks at that many entries (0: no map), so tile
- * grabs beyond it search the chunk offsets instead; -1 restores the default.
+ * buffer by one of that many records now, shared out evenly among the handle's
+ * buckets (0: leave it). tile_map_limit >= 0 caps the lists of spawn tiles at
+ * that many entries in all (0: no list), so buckets whose tiles do not fit are
+ * taken whole instead; -1 restores the default.
  * Results do not depend on any of these. Errors: EINVAL, ENOMEM. */
 int fciqmc_set_test_options(fciqmc_t *h, int32_t planner, int64_t tile_map_limit,
                             int64_t record_capacity);

@@ -7,8 +7,8 @@ namespace fq {
 
 constexpr int BQ = 256;              // entries per bucket of the main list (a wavefront's unit
                                      // in annihilation: four per lane)
-constexpr int CHUNK = 1024;          // four consecutive buckets: the unit of attempt mapping and
-                                     // spawn staging, and one workgroup's unit in annihilation
+constexpr int CHUNK = 1024;          // four consecutive buckets: one workgroup's unit in
+                                     // annihilation
 constexpr int BPC = CHUNK / BQ;      // buckets per chunk
 constexpr int BUCKET_FILL = 128;     // planned mean entries per bucket (half full)
 constexpr int BUCKET_RECS = 32;      // planned mean spawn records per bucket at most: a
@@ -197,8 +197,8 @@ constexpr size_t NOALLOC_BYTES = NOALLOC_FLAGS_OFF + 4 * (size_t)NOALLOC_MAX_DET
 
 // Kernel launchers (kernels.hip, compiled once per determinant width: one word in fq,
 // two words in fq::w2). Determinant arrays hold the width's words per entry.
-constexpr int NKERN = 5;   // profiled kernel groups: chunk sums, scans, spawn, annihilation
-                           // (record sort + death/annihilation pass), statistics/shift
+constexpr int NKERN = 5;   // profiled kernel groups: tile listing, (unused), spawn,
+                           // annihilation, statistics/shift
 // Device sort: longest list (32-bit positions), and the words its digit counts take (a
 // total per digit, then one count per digit and run of 1024 entries).
 constexpr int64_t SORT_MAX = (int64_t)1 << 31;

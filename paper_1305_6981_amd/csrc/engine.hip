@@ -1,15 +1,15 @@
 // Host engine of libfciqmc: the C ABI declared in include/fciqmc.h.
 //
 // A handle holds up to max_slots independent systems. Each system owns a main
-// list in device memory, hash-partitioned into buckets of at most 1024 packed
+// list in device memory, hash-partitioned into buckets of at most 256 packed
 // entries (structure of arrays: determinant, population, stored diagonal
 // element, plus a count per bucket), its integrals, and a row of the device
 // descriptor table. One iteration of every system is one pass of the kernels
 // over the descriptor table; up to 64 iterations are captured in one HIP graph.
 // Between launches the host reads the per-iteration records, feeds the
 // estimator averages, and re-buckets a list whose buckets would fill up, or
-// grows the spawn-record buffer. An iteration whose records overflowed the
-// buffer is abandoned and re-run after growth (the counter-based random
+// gives its buckets more record slots. An iteration whose records overflowed a
+// bucket's slots is abandoned and re-run with more (the counter-based random
 // numbers make the re-run identical); new determinants that did not fit their
 // bucket complete the iteration in a spill list and are re-bucketed before the
 // system continues.

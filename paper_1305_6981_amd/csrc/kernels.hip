@@ -5,7 +5,7 @@
 // densely packed entries (determinant, population, stored H_DD): the paper's
 // distribution of determinants over processes by a hash (Sec. 4.1), with a
 // wavefront in the role of a process. Four consecutive buckets form a chunk,
-// the unit of attempt mapping. One iteration of every active system is
+// one workgroup's unit in annihilation. One iteration of every active system is
 // three launches (four in the first iteration of a launch sequence):
 //
 //   k_tiles       lists the spawn tiles, runs of attempts of one bucket (first iteration
@@ -1075,7 +1075,7 @@ __device__ __forceinline__ unsigned long long bucket_walkers(const SysDesc &d, i
 // ---------------------------------------------------------------------------
 // K1: the tiles of the current list (the first iteration of a launch). A wavefront takes
 // up to 64 consecutive buckets, fewer in a small list; four buckets' loads are in flight
-// at a time.
+// at a time. Bound by memory: 4 B per entry, 0.15 ms for 8e7 entries, 7 us for a small list.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_tiles(EngineArgs a, const SysDesc *__restrict__ desc) {
     const int lane = threadIdx.x & 63;
@@ -1134,6 +1134,13 @@ __global__ __launch_bounds__(256) void k_tiles(EngineArgs a, const SysDesc *__re
 // test too (the bound holds for every rounding), so the walkers are the same; what is
 // saved is the element's two gathers and the division for most attempts, and wavefronts
 // that run them for a few lanes only. Single excitations are queued apart.
+//
+// Bound, in large launches, by vector-instruction issue (405 wavefront instructions per 64
+// attempts, a Philox block and the choice of four orbitals most of them); in small ones by
+// the chain of memory round trips from the lists to the records (some 17 us for one tile).
+// Against a workgroup per tile of a 1024-entry chunk, which searched each attempt's entry
+// and evaluated every element: 1.90 -> 1.50 ms (24 electrons, 1.4e8 walkers), 148 -> 85 us
+// (3.5e6), 78 -> 36 us (ring of 14 sites, 8e5), 35 -> 20 us (ring of 8 sites, 1.8e4).
 // ---------------------------------------------------------------------------
 
 // A spawn record into its child's bucket's slots, at the place the bucket's counter
@@ -1671,8 +1678,8 @@ void k_spawn(EngineArgs a, const SysDesc *__restrict__ desc, int first) {
 }
 
 // ---------------------------------------------------------------------------
-// K4: annihilation. A workgroup takes windows of consecutive chunks from a shared
-// counter and, in each chunk, every wavefront one bucket, with no workgroup barrier
+// K4: annihilation. A workgroup takes windows of consecutive chunks from lists of
+// them and, in each chunk, every wavefront one bucket, with no workgroup barrier
 // inside a bucket:
 //   - the bucket's records are merged per child in the wavefront's LDS hash
 //     (the sort and compress of Sec. 4.1, by hashing);
@@ -1681,11 +1688,20 @@ void k_spawn(EngineArgs a, const SysDesc *__restrict__ desc, int first) {
 //     initiator sent some of them (Sec. 4.2);
 //   - children outside the bucket with an initiator parent become new entries
 //     (emptied positions first); the other children are discarded;
-//   - the bucket is re-packed; the estimator partials and the next iteration's
-//     sum of |C| are written.
+//   - the bucket is re-packed; the estimator partials are added up, and the next
+//     iteration's tiles listed from the buckets' sums of |C|.
 // A bucket with more than NREC records merges them in rounds of at most NREC distinct
 // children, staging each merged child outside the bucket in the slot of the record that
 // entered it into the hash.
+//
+// Bound by instruction issue and, per bucket, by a chain of loads, LDS and stores (8 us for
+// a bucket alone) that four wavefronts per SIMD do not cover; small launches by the chain
+// around the buckets as well (lists, metadata, tiles, diagonal elements: some 20 us). With
+// the records in their buckets' slots, the queue of new determinants kept over windows,
+// statistics in shares and the tiles listed here: 242 -> 100 us at 3.5e6 walkers (24
+// electrons), 104 -> 80 us at 1.1e7 (10 electrons), 90 -> 52 us on a ring of 14 sites (8e5),
+// 27 -> 20 us on one of 8 (1.8e4), and at 1.4e8 walkers 1.26 -> 1.19 ms with the sort of
+// its records (0.13 ms) and a pass over statistics (0.03 ms) gone besides.
 // ---------------------------------------------------------------------------
 constexpr int NREC = 64;                // distinct children per round in a wavefront's hash
 constexpr int WHASH = 128;              // hash slots per wavefront (load <= 0.5)
