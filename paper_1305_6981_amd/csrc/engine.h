@@ -144,6 +144,8 @@ struct __attribute__((aligned(16))) SpawnRec {
     uint32_t tag;
 };
 
+constexpr int EXT_BITS = 28;
+
 struct EngineArgs {
     SysDesc *desc;
     int32_t max_sys;
@@ -170,6 +172,12 @@ struct EngineArgs {
     // 115 us of a 3.3 ms iteration and 23 us of a 118 us one.
     SpawnRec *recs;
     uint32_t *bhist;                 // [BPC chunk_cap] records per bucket (k_post clears them)
+    uint32_t *bprev;                 // [BPC chunk_cap] the same, the last count above zero
+    // [BPC chunk_cap] slots of a bucket beyond its system's rec_r: their first << EXT_BITS |
+    // how many (0: none). For lists whose records crowd into few buckets (the reference's
+    // neighbours): with as many slots for every bucket as the fullest one needs, a list
+    // grown from walkers on the reference asked for 8e9.
+    uint64_t *bext;
     uint32_t *rec_max;               // [max_sys] most records of one bucket this iteration
     long long *d0acc;                // [max_sys] walkers spawned onto the reference (kept out of
                                      // the records: the reference is the hot spot of Sec. 4.1)
@@ -252,6 +260,12 @@ struct ListCheck {
     /* Initiator flag of each of n entries: |pop| > n_a, or the reference. */                 \
     hipError_t launch_flags(const uint64_t *key, const int32_t *val, int64_t n, int32_t n_a,  \
                             uint64_t d0, uint64_t d0_hi, uint32_t *flags, hipStream_t s);     \
+    /* Gives nb buckets of rec_r slots (arrays bprev and bext at the first) their places in \
+       the extension [pool0, pool0 + pool) of the record buffer, for `factor` times the       \
+       records of the last iteration and 16 more; *used gets what all of them need. */        \
+    hipError_t launch_extend(const uint32_t *bprev, uint64_t *bext, int64_t nb, uint32_t rec_r, \
+                             float factor, int64_t pool0, int64_t pool,                       \
+                             unsigned long long *used, hipStream_t s);                        \
     /* H_DD (or the function's diagonal) of one determinant, words lo and hi. */              \
     hipError_t launch_e0(const SysDesc *desc, int32_t sys, uint64_t lo, uint64_t hi,          \
                          double *out, hipStream_t s);

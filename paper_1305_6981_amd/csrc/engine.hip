@@ -216,6 +216,9 @@ struct SysHost {
     int64_t growth = 0;        // expected per-iteration increase of the entries
     double spawn_rate = 1.0;   // mean growth of the records per iteration in the last launch
     int64_t rec_r = 0;         // record slots per bucket
+    bool crowded = false;      // few buckets hold most records: those get extensions,
+    bool counted = false;      // from the last iteration's counts, if there are any
+    double ext_factor = 1.0;   // slots per record of it
     bool no_split = false;     // no room for buckets planned by their records
     int64_t rec_peak = 0;      // most records of one bucket in the last launch (0: unknown)
     double h_max = 0.0;        // scale of the largest off-diagonal elements
@@ -260,7 +263,10 @@ struct fciqmc_t {
     void *d_recs = nullptr;
     int64_t rec_cap = 0;                    // slots allocated
     int64_t rec_floor = 65536;              // slots a system's buckets share at least
-    uint32_t *d_bhist = nullptr, *d_rec_max = nullptr;
+    uint32_t *d_bhist = nullptr, *d_rec_max = nullptr, *d_bprev = nullptr;
+    uint64_t *d_bext = nullptr;
+    int64_t rec_base = 0;                   // slots in use before the extensions
+    bool ext_on = false;                    // some bucket may have an extension
     long long *d_d0acc = nullptr;
     void *d_spill = nullptr;
     int64_t sp_cap = 0;
@@ -316,6 +322,8 @@ EngineArgs make_args(fciqmc_t *h) {
     a.unlisted = h->d_unlisted;
     a.recs = (SpawnRec *)h->d_recs;
     a.bhist = h->d_bhist;
+    a.bprev = h->d_bprev;
+    a.bext = h->d_bext;
     a.rec_max = h->d_rec_max;
     a.d0acc = h->d_d0acc;
     char *q = (char *)h->d_spill;
@@ -409,6 +417,7 @@ int layout_records(fciqmc_t *h) {
         h->hdesc[s].rec_r = S.rec_r;
         at += S.cap / BQ * S.rec_r;
     }
+    h->rec_base = at;
     if (at > h->rec_cap) return ensure_records(h, std::max<int64_t>(at, h->rec_cap + h->rec_cap / 4));
     return 0;
 }
@@ -450,17 +459,26 @@ int relayout(fciqmc_t *h) {
         hipFree(h->d_chunk_local);
         hipFree(h->d_unlisted);
         hipFree(h->d_bhist);
+        hipFree(h->d_bprev);
+        hipFree(h->d_bext);
         h->d_chunk_sys = nullptr;
         h->chunk_alloc = 0;
         HIP_TRY(hipMalloc(&h->d_chunk_sys, na * sizeof(int32_t)));
         HIP_TRY(hipMalloc(&h->d_chunk_local, na * sizeof(int32_t)));
         HIP_TRY(hipMalloc(&h->d_unlisted, BPC * na * sizeof(uint32_t)));
         HIP_TRY(hipMalloc(&h->d_bhist, BPC * na * sizeof(uint32_t)));
+        HIP_TRY(hipMalloc(&h->d_bprev, BPC * na * sizeof(uint32_t)));
+        HIP_TRY(hipMalloc(&h->d_bext, BPC * na * sizeof(uint64_t)));
         h->chunk_alloc = na;
         drop_graphs(h);
     }
     // record counts start at zero (k_post keeps them so after every iteration)
     HIP_TRY(hipMemsetAsync(h->d_bhist, 0, BPC * h->chunk_alloc * sizeof(uint32_t), h->stream));
+    // (the buckets are others now: their counts and extensions are void)
+    HIP_TRY(hipMemsetAsync(h->d_bprev, 0, BPC * h->chunk_alloc * sizeof(uint32_t), h->stream));
+    HIP_TRY(hipMemsetAsync(h->d_bext, 0, BPC * h->chunk_alloc * sizeof(uint64_t), h->stream));
+    h->ext_on = false;
+    for (SysHost &S : h->sys) S.counted = false;
     std::vector<int32_t> cs(total), cl(total);
     int64_t g = 0;
     for (int s = 0; s < h->max_sys; ++s) {
@@ -1103,6 +1121,7 @@ int load_entries(fciqmc_t *h, int s, const uint64_t *dd, const int32_t *dp, int6
     S.growth = std::max<int64_t>(256, entries / 8);
     S.spawn_rate = 1.0;
     S.rec_peak = 0;
+    S.counted = false;
     S.pop_max = most;
     return 0;
 }
@@ -1369,6 +1388,39 @@ int capture_or_get(fciqmc_t *h, int L, hipGraphExec_t *out) {
     return 0;
 }
 
+// The extensions of crowded systems' buckets, anew before each launch (the record buffer is
+// dead between launches): what they need in all, room for it, their places.
+int extend_buckets(fciqmc_t *h) {
+    bool any = false;
+    for (const SysHost &S : h->sys) any |= S.active && S.crowded && S.counted;
+    if (!any && !h->ext_on) return 0;
+    HIP_TRY(hipMemsetAsync(h->d_bext, 0, BPC * h->chunk_alloc * sizeof(uint64_t), h->stream));
+    h->ext_on = any;
+    int64_t pool = 0;
+    for (int pass = 0; any && pass < 2; ++pass) {
+        HIP_TRY(hipMemsetAsync(h->d_count, 0, 8, h->stream));
+        for (int s = 0; s < h->max_sys; ++s) {
+            const SysHost &S = h->sys[s];
+            if (!S.active || !S.crowded || !S.counted) continue;
+            const int64_t b0 = h->hdesc[s].gchunk0 * BPC;
+            HIP_TRY(FQ_LAUNCH(h->W, launch_extend, h->d_bprev + b0, h->d_bext + b0, S.cap / BQ,
+                              (uint32_t)S.rec_r, (float)S.ext_factor, h->rec_base, pool, h->d_count,
+                              h->stream));
+        }
+        if (pass == 0) {
+            unsigned long long need = 0;
+            HIP_TRY(hipMemcpyAsync(&need, h->d_count, 8, hipMemcpyDeviceToHost, h->stream));
+            HIP_TRY(hipStreamSynchronize(h->stream));
+            pool = (int64_t)need;
+            if (h->rec_base + pool > h->rec_cap) {
+                const int rc = ensure_records(h, h->rec_base + pool + pool / 4);
+                if (rc) return rc;
+            }
+        }
+    }
+    return 0;
+}
+
 // Before a launch of up to L iterations: re-bucket any main list whose buckets
 // would pass 5/8 full on average during the launch (each iteration adds at most
 // `growth` entries, the largest increase seen, with slack), size the record slots per
@@ -1414,13 +1466,27 @@ int plan_launch(fciqmc_t *h, int L, int *L_out) {
                                            : (double)std::max<int64_t>(S.last.nw, 1) / (double)nb +
                                                  S.prm.tau * S.h_max * (double)S.pop_max;
         const double grow = std::min(std::pow(S.spawn_rate, (double)std::min(allowed, 8)), 4.0);
-        const int64_t want = std::max(min_slots(h, nb), round_slots(1.5 * peak * grow + 16.0));
+        const double fullest = 1.5 * peak * grow + 16.0;
+        int64_t want = std::max(min_slots(h, nb), round_slots(std::min(fullest, 1e12)));
+        // As many for every bucket as the fullest needs, up to 8 slots (128 B) per walker or
+        // 2^21 in all; where records crowd into few buckets, those get the rest as extensions
+        // (a pass over the buckets before the launch), by what each received in the last
+        // iteration. Without such a count (the buckets are new) one iteration is tried: if
+        // it overflows it is re-run, from its own counts.
+        const int64_t most = std::max<int64_t>((int64_t)1 << 21, 8 * S.last.nw) / nb / 8 * 8;
+        S.crowded = want > std::max(most, min_slots(h, nb));
+        if (S.crowded) {
+            want = std::max(most, min_slots(h, nb));
+            S.ext_factor = 1.5 * grow;
+            if (!S.counted) allowed = 1;
+        }
         if (want > S.rec_r || 4 * want < S.rec_r) {
             S.rec_r = want;
             relaid = true;
         }
         if (S.spawn_rate > 1.0) {
-            const double fit = std::log((double)S.rec_r / (1.25 * peak)) / std::log(S.spawn_rate);
+            const double fit = std::log((S.crowded ? fullest : (double)S.rec_r) / (1.25 * peak)) /
+                               std::log(S.spawn_rate);
             allowed = (int)std::max<double>(1.0, std::min<double>((double)allowed, std::floor(fit)));
         }
     }
@@ -1428,6 +1494,8 @@ int plan_launch(fciqmc_t *h, int L, int *L_out) {
         const int rc = layout_records(h);
         if (rc) return rc;
     }
+    const int rc = extend_buckets(h);
+    if (rc) return rc;
     *L_out = allowed;
     return 0;
 }
@@ -1492,6 +1560,7 @@ int run_iterations(fciqmc_t *h, int L, bool sample) {
         SysHost &S = h->sys[s];
         if (!S.active) continue;
         SysDesc &d = h->hdesc[s];
+        S.counted = true;   // (an abandoned iteration counts its records as well)
         const int64_t n_new = d.iter - before[s];
         if (n_new > 0) {
             // the stream has been synchronised: the records are in host memory
@@ -1551,6 +1620,7 @@ int run_iterations(fciqmc_t *h, int L, bool sample) {
         HIP_TRY(hipMemsetAsync(h->d_rec_max + s, 0, sizeof most, h->stream));
         HIP_TRY(hipStreamSynchronize(h->stream));
         h->sys[s].rec_peak = most;
+        if (h->planner) continue;   // (plan_launch lays them out)
         h->sys[s].rec_r = std::max(h->sys[s].rec_r + 8, round_slots(1.5 * (double)most + 16.0));
         rc = layout_records(h);
         if (rc) return rc;
@@ -1760,6 +1830,8 @@ void release(fciqmc_t *h) {
     hipFree(h->d_recs);
     hipFree(h->d_rec_max);
     hipFree(h->d_bhist);
+    hipFree(h->d_bprev);
+    hipFree(h->d_bext);
     hipFree(h->d_d0acc);
     hipFree(h->d_spill);
     hipFree(h->d_sp_count);

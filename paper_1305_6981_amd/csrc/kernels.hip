@@ -1144,7 +1144,8 @@ __global__ __launch_bounds__(256) void k_tiles(EngineArgs a, const SysDesc *__re
 // ---------------------------------------------------------------------------
 
 // A spawn record into its child's bucket's slots, at the place the bucket's counter
-// gives it. A record past the bucket's slots is dropped (still counted) and the system
+// gives it (past the slots that every bucket of the system has, in the bucket's extension,
+// if it has one). A record past those is dropped (still counted) and the system
 // marked: the iteration is then abandoned and re-run with more slots per bucket.
 // Walkers spawned onto the reference go to a per-system sum instead (every
 // iteration sends it many: the reference is the hot spot of Sec. 4.1).
@@ -1153,11 +1154,17 @@ __device__ __forceinline__ void put_record(const EngineArgs &a, const SysDesc &d
     const uint32_t b = bucket_of(D, (uint64_t)d.nbuckets);
     const uint32_t k = __hip_atomic_fetch_add(&a.bhist[d.gchunk0 * BPC + b], 1u, __ATOMIC_RELAXED,
                                               __HIP_MEMORY_SCOPE_AGENT);
+    int64_t at = d.rec0 + (int64_t)b * d.rec_r + k;
     if (k >= (uint32_t)d.rec_r) {
-        atomicOr(status, ST_TABLE_FULL);
-        return;
+        const uint64_t x = a.bext[d.gchunk0 * BPC + b];
+        const uint32_t over = k - (uint32_t)d.rec_r;
+        if (over >= (uint32_t)(x & ((1ull << EXT_BITS) - 1ull))) {
+            atomicOr(status, ST_TABLE_FULL);
+            return;
+        }
+        at = (int64_t)(x >> EXT_BITS) + over;
     }
-    put_rec(recs_of(a) + d.rec0 + (int64_t)b * d.rec_r + k, D, v, init ? 1u : 0u);
+    put_rec(recs_of(a) + at, D, v, init ? 1u : 0u);
 }
 
 // The acceptance uniform: the type word's uniform rescaled within the chosen
@@ -2393,7 +2400,10 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
             uint32_t nrec = 0;
             if (t < nwin * BPC) {
                 nrec = a.bhist[c0 * BPC + t];
-                if (nrec) a.bhist[c0 * BPC + t] = 0u;   // counted afresh next iteration
+                if (nrec) {
+                    a.bhist[c0 * BPC + t] = 0u;   // counted afresh next iteration
+                    a.bprev[c0 * BPC + t] = nrec;
+                }
                 s_nr[t] = nrec;
                 // the fullest bucket, from which the host plans the slots (of an abandoned
                 // iteration too: its dropped records were counted)
@@ -2430,6 +2440,14 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                 const int n = s_bn[ci * BPC + wid];
                 const uint32_t nr = s_nr[ci * BPC + wid];
                 rec_t *const seg = recs_of(a) + d.rec0 + lb * d.rec_r;   // the bucket's records
+                // fast path: one record per lane, all in the bucket's own slots
+                const bool fast = nr <= (uint32_t)NREC && nr <= (uint32_t)d.rec_r;
+                // slow path: record j (see put_record)
+                auto rec_at = [&](uint32_t j) -> rec_t * {
+                    if (j < (uint32_t)d.rec_r) return seg + j;
+                    const uint64_t x = a.bext[(c0 + ci) * BPC + wid];
+                    return recs_of(a) + ((int64_t)(x >> EXT_BITS) + (j - (uint32_t)d.rec_r));
+                };
                 // the H_DD queue serves one system at a time: the first to use it in a window
                 if (lane == 0 && s_qsys < 0) atomicCAS(&s_qsys, -1, s);
                 // entry u * 64 + lane is this lane's u-th; R rounds cover the n entries
@@ -2451,7 +2469,7 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                 uint32_t rf = 0u;
                 int rh = 0;
                 bool rown = false;
-                if ((uint32_t)lane < nr && nr <= (uint32_t)NREC) {
+                if ((uint32_t)lane < nr && fast) {
                     const rec_t r = get_rec(seg + lane);
                     rd = r.det;
                     rw = r.w;
@@ -2489,7 +2507,7 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                 wave_sync();
                 long long spv[4] = {0ll, 0ll, 0ll, 0ll};   // walkers arrived per entry
                 uint32_t flv = 0u;                         // bit u: an initiator sent some
-                if (nr <= (uint32_t)NREC) {
+                if (fast) {
                     // Fast path: at most NREC records, so at most NREC distinct children.
                     if ((uint32_t)lane < nr) {
                         rh = wl_claim(rd, W, &rown, lane);
@@ -2528,16 +2546,16 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                         wave_sync();
                         bool maybe = false;
                         for (uint32_t j = lane; j < nr; j += 64) {   // (a record stays with its lane)
-                            const rec_t r = get_rec(seg + j);
+                            const rec_t r = get_rec(rec_at(j));
                             if (round > 0 && !(r.tag & F_DEFER)) continue;
                             bool own;
                             const int h = wl_claim_limited(r.det, W, &s_ncl[wid], &own, lane);
                             if (h < 0) {
-                                seg[j].tag = (r.tag & F_INIT) | F_MAYBE;
+                                rec_at(j)->tag = (r.tag & F_INIT) | F_MAYBE;
                                 maybe = true;
                                 continue;
                             }
-                            if (r.tag & F_DEFER) seg[j].tag = r.tag & F_INIT;
+                            if (r.tag & F_DEFER) rec_at(j)->tag = r.tag & F_INIT;
                             atomicAdd((unsigned long long *)&W.acc[h], (unsigned long long)(long long)r.w);
                             const uint32_t f = (r.tag & F_INIT) | (own ? j << OWN_SHIFT : 0u);
                             if (f) atomicOr(&W.flg[h], f);
@@ -2546,15 +2564,15 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                         bool defer = false;
                         if (__ballot(maybe)) {
                             for (uint32_t j = lane; j < nr; j += 64) {
-                                const rec_t r = get_rec(seg + j);
+                                const rec_t r = get_rec(rec_at(j));
                                 if (!(r.tag & F_MAYBE)) continue;
                                 const int h = wl_find(r.det, W);
                                 if (h < 0) {
-                                    seg[j].tag = (r.tag & F_INIT) | F_DEFER;
+                                    rec_at(j)->tag = (r.tag & F_INIT) | F_DEFER;
                                     defer = true;
                                     continue;
                                 }
-                                seg[j].tag = r.tag & F_INIT;
+                                rec_at(j)->tag = r.tag & F_INIT;
                                 atomicAdd((unsigned long long *)&W.acc[h],
                                           (unsigned long long)(long long)r.w);
                                 if (r.tag & F_INIT) atomicOr(&W.flg[h], F_INIT);
@@ -2581,7 +2599,7 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                                 atomicOr(status, ST_POP_OVERFLOW);
                                 sp = 0;
                             }
-                            put_rec(seg + (f >> OWN_SHIFT), W.key[h], (int32_t)sp, (f & F_INIT) | F_STAGED);
+                            put_rec(rec_at(f >> OWN_SHIFT), W.key[h], (int32_t)sp, (f & F_INIT) | F_STAGED);
                         }
                         wave_sync();
                         if (!__ballot(defer)) break;
@@ -2683,7 +2701,7 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                 };
                 int diag = -1;         // fast path: place()'s answer for this lane's child
                 long long rsp = 0ll;   // fast path: walkers that arrived for this lane's child
-                if (nr <= (uint32_t)NREC) {
+                if (fast) {
                     // one lane per distinct child: the lane that entered it into the hash
                     const uint32_t f = rown ? W.flg[rh] : F_MATCHED;
                     const bool cand = !(f & F_MATCHED);
@@ -2697,11 +2715,11 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                 } else {
                     for (uint32_t i0 = 0; i0 < nr; i0 += 64) {
                         const uint32_t i = i0 + lane;
-                        const rec_t r = get_rec(seg + (i < nr ? i : 0u));
+                        const rec_t r = get_rec(rec_at(i < nr ? i : 0u));
                         const bool in = i < nr && (r.tag & F_STAGED);
                         const int at = place(in ? r.det : det_t(0ull), in ? (long long)r.w : 0ll,
                                              in && (r.tag & F_INIT));
-                        if (at >= 0) seg[i].tag = r.tag | (uint32_t)(at + 1) << DIAG_SHIFT;
+                        if (at >= 0) rec_at(i)->tag = r.tag | (uint32_t)(at + 1) << DIAG_SHIFT;
                     }
                 }
                 // Re-pack: n' = (kept entries) + (new determinants); when fewer new
@@ -2741,12 +2759,11 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
                 // computed, taken last, when few values are live: a lane's entries (bits 0-3
                 // of todo) and its new determinant (bits 4 and 5; many of them on the slow
                 // path).
-                const bool fast = nr <= (uint32_t)NREC;
                 for (uint32_t i0 = 0; i0 == 0 || (!fast && i0 < nr); i0 += 64) {
                     bool fresh_det = fast && rown && rf != 0u && rsp != 0ll;
                     if (!fast) {
                         const uint32_t i = i0 + lane;
-                        const rec_t r = get_rec(seg + (i < nr ? i : 0u));
+                        const rec_t r = get_rec(rec_at(i < nr ? i : 0u));
                         fresh_det = i < nr && (r.tag & F_STAGED) && (r.tag & F_INIT) && r.w != 0;
                         rd = r.det;
                         rsp = r.w;
@@ -3230,6 +3247,34 @@ hipError_t launch_sort(uint64_t *key, int32_t *val, uint64_t *key2, int32_t *val
         std::swap(a, b);
         std::swap(val, val2);
     }
+    return hipGetLastError();
+}
+
+// Places for the records that crowded buckets get beyond their system's slots (once per
+// launch, and only for systems that need it).
+__global__ void k_extend(const uint32_t *bprev, uint64_t *bext, int64_t nb, uint32_t rec_r,
+                         float factor, int64_t pool0, int64_t pool, unsigned long long *used) {
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < nb;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const float need = (float)bprev[i] * factor + 16.0f;
+        uint64_t x = 0ull;
+        if (need > (float)rec_r) {
+            const float over = fminf(need - (float)rec_r, (float)((1 << EXT_BITS) - 64));
+            const unsigned long long n = ((unsigned long long)over + 8ull) / 8ull * 8ull;
+            const unsigned long long at = atomicAdd(used, n);
+            if ((int64_t)(at + n) <= pool) x = (uint64_t)(pool0 + (int64_t)at) << EXT_BITS | n;
+        }
+        bext[i] = x;
+    }
+}
+
+hipError_t launch_extend(const uint32_t *bprev, uint64_t *bext, int64_t nb, uint32_t rec_r,
+                         float factor, int64_t pool0, int64_t pool, unsigned long long *used,
+                         hipStream_t s) {
+    if (nb <= 0) return hipSuccess;
+    const int64_t g = (nb + 255) / 256;
+    hipLaunchKernelGGL(k_extend, dim3((unsigned)(g < 4096 ? g : 4096)), dim3(256), 0, s, bprev, bext,
+                       nb, rec_r, factor, pool0, pool, used);
     return hipGetLastError();
 }
 

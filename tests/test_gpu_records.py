@@ -51,3 +51,46 @@ def test_list_on_the_reference():
     print("[gpu] records: 60000 walkers on the reference", flush=True)
     e = _run(ham, prm, 0, 2, 20)
     assert e["redos"] == 0       # the slots are planned from the largest population
+
+
+@pytest.mark.parametrize("words", [0, 2])
+def test_crowded_buckets(words):
+    """A list of many buckets whose records crowd into a few (walkers on the reference of a
+    ring: each of its neighbours is sent a thousand): the crowded buckets' slots beyond
+    everybody's, and the iterations re-run until their counts are known."""
+    ham = S.hubbard_ring(10, 4.0)
+    prm = S.Params(tau=0.01, initiator_threshold=0, target_walkers=10**9, initial_walkers=100_000,
+                   det_capacity=1 << 21, seed=9, det_words=words)
+    print(f"[gpu] records: crowded buckets, words {words}", flush=True)
+    e = _run(ham, prm, 0, 3, 5)
+    assert 1 <= e["redos"] <= 4
+
+
+def test_crowded_batch():
+    """The same beside systems that are not crowded, through a change of the batch."""
+    ring, mol = S.hubbard_ring(10, 4.0), S.synthetic_molecule(8, 3, 3, 4)
+    sy = [(mol, S.Params(tau=4e-3, initiator_threshold=0, target_walkers=10**9, initial_walkers=500,
+                         seed=1)),
+          (ring, S.Params(tau=0.01, initiator_threshold=0, target_walkers=10**9,
+                          initial_walkers=60_000, det_capacity=1 << 21, seed=2)),
+          (ring, S.Params(tau=0.01, initiator_threshold=0, target_walkers=10**9,
+                          initial_walkers=90_000, det_capacity=1 << 20, seed=3))]
+    print("[gpu] records: crowded systems in a batch", flush=True)
+    h = F.fciqmc_batch_create(3, [a for a, _ in sy], [b for _, b in sy], F.current_stream())
+    refs = [O.Oracle(a, b) for a, b in sy]
+    for n, drop in ((4, False), (5, True), (4, False)):
+        F.fciqmc_batch_iterate(h, n)
+        for slot, ref in enumerate(refs):
+            if ref is None:
+                continue
+            ref.iterate(n)
+            d, p, _ = F.fciqmc_batch_slot_walkers(h, slot)
+            do, po, _ = ref.walkers()
+            assert np.array_equal(d, do) and np.array_equal(p, po), slot
+        if drop:
+            F.fciqmc_batch_retire(h, 0)
+            refs[0].close()
+            refs[0] = None
+    for ref in refs[1:]:
+        ref.close()
+    F.fciqmc_free(h)
