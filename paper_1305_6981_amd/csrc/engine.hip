@@ -405,6 +405,15 @@ int64_t min_slots(const fciqmc_t *h, int64_t nbuckets) {
     return round_slots((double)std::max<int64_t>(24, std::min<int64_t>(share, 1024)));
 }
 
+// A list of more buckets than before (old_nb) keeps its slots in all, not per bucket, until
+// the next launch is planned: the few buckets of a list that starts on the reference have
+// thousands each.
+void share_slots(const fciqmc_t *h, SysHost &S, int64_t old_nb) {
+    const int64_t nb = S.cap / BQ;
+    if (!h->planner || S.rec_r <= 0 || nb <= old_nb) return;
+    S.rec_r = std::max(min_slots(h, nb), round_slots((double)S.rec_r * (double)old_nb / (double)nb));
+}
+
 // Lay the active systems' record slots out one after another, each system's at its own
 // count per bucket; the buffer grows when they need more.
 int layout_records(fciqmc_t *h) {
@@ -658,6 +667,7 @@ int rebucket_system(fciqmc_t *h, int s, int64_t new_cap, int64_t n_spill) {
         if (!err) {
             HIP_TRY(hipFree(S_old.block));
             S.last.used = std::max<int64_t>(S.last.used, S.last.nd + 1);
+            share_slots(h, S, S_old.cap / BQ);
             rc = relayout(h);
             if (rc) return rc;
             return upload_desc(h);
@@ -1095,7 +1105,9 @@ int load_entries(fciqmc_t *h, int s, const uint64_t *dd, const int32_t *dp, int6
             rc = upload_integrals(h, T);
             if (rc) return rc;
             HIP_TRY(hipFree(S.block));
+            const int64_t old_nb = S.cap / BQ;
             carve(S, blk, need);
+            share_slots(h, S, old_nb);
             fill_desc_tables(h, s);
             rc = relayout(h);
             if (rc) return rc;

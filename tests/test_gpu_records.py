@@ -94,3 +94,25 @@ def test_crowded_batch():
     for ref in refs[1:]:
         ref.close()
     F.fciqmc_free(h)
+
+
+def test_slots_when_the_list_grows():
+    """Few buckets with thousands of slots each (a start on the reference) that become
+    thousands of buckets: a list is loaded that needs them, and the solve goes on."""
+    ham = S.synthetic_molecule(20, 4, 4, 12)
+    prm = S.Params(tau=2e-3, initiator_threshold=3, target_walkers=10**9, initial_walkers=200_000,
+                   det_capacity=1024, seed=21)
+    print("[gpu] records: slots of a list that grows", flush=True)
+    gpu, ref = F.Solver(ham, prm, F.current_stream()), O.Oracle(ham, prm)
+    for n in (2, 3):
+        gpu.iterate(n)
+        ref.iterate(n)
+        F.fciqmc_reserve(gpu.h, 1 << (22 if n == 2 else 25))
+        (dg, pg, _), (do, po, _) = gpu.walkers(), ref.walkers()
+        assert np.array_equal(dg, do) and np.array_equal(pg, po)
+    gpu.iterate(2)
+    ref.iterate(2)
+    (dg, pg, _), (do, po, _) = gpu.walkers(), ref.walkers()
+    assert np.array_equal(dg, do) and np.array_equal(pg, po)
+    gpu.close()
+    ref.close()
