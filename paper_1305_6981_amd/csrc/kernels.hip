@@ -653,15 +653,18 @@ __device__ __forceinline__ bool draw_double(const SysDesc &d, const ClassView<fa
     const bool same = ((p ^ x.q) & 1) == 0;
     const det_t A = same ? (emp & ((p & 1) ? odd_bits() : even_bits())) : emp;
     const int gpq = cv.irrep(d, p >> 1) ^ cv.irrep(d, x.q >> 1);
-    // a orbitals whose partner class (Eq. sym1 plus spin) has an empty orbital besides a.
+    // a orbitals whose partner class (Eq. sym1 plus spin) has an empty orbital besides a: an
+    // irrep's two spins together, without a branch on the lanes (which kept the LDS reads of
+    // the partners' masks one behind the other). Like spins take the partner of their own
+    // spin (the other spin's class has no orbital in A).
     det_t allowed = det_t(0ull);
-    for (int c = 0; c < n_class; ++c) {
-        const det_t memb = A & cmask_of(d, c);
-        if (!memb) continue;
-        const int sb = same ? (p & 1) : 1 - (c & 1);
-        const int pc = 2 * (gpq ^ (c >> 1)) + sb;
-        const int nb = dpopc(emp & cv.mask(pc)) - (pc == c ? 1 : 0);
-        if (nb > 0) allowed |= memb;
+    const int self = same && gpq == 0 ? 1 : 0;   // a is in its own partner class
+#pragma unroll 2
+    for (int g = 0; 2 * g < n_class; ++g) {
+        const det_t even = cv.mask(2 * (gpq ^ g)), odd = cv.mask(2 * (gpq ^ g) + 1);
+        const int ne = dpopc(emp & even), no = dpopc(emp & odd);
+        if ((same ? ne : no) > self) allowed |= A & cmask_of(d, 2 * g);
+        if ((same ? no : ne) > self) allowed |= A & cmask_of(d, 2 * g + 1);
     }
     const uint32_t nal = (uint32_t)dpopc(allowed);
     if (nal == 0) return false;
