@@ -369,12 +369,15 @@ Shape launch_shape(const fciqmc_t *h) {
     int64_t walkers = 0;
     for (int s = 0; s < h->max_sys; ++s)
         if (h->sys[s].active && !h->sys[s].fatal) walkers += std::max<int64_t>(h->sys[s].last.nw, 0);
-    // (two tiles for each of the grid's wavefronts: with one, lists whose walkers sit on few
-    // determinants gave some three full tiles and others next to nothing. 8 electrons in 20
-    // orbitals, half of 3e6 walkers on the reference: 219 -> 179 us an iteration; a ring of
-    // 14 sites, even as it is, 97 -> 100.)
-    const int64_t waves = 8 * (int64_t)h->spawn_grid;
+    const int64_t waves = 4 * (int64_t)h->spawn_grid;
     while (o.wsh > 6 && (walkers >> o.wsh) < waves) --o.wsh;
+    // Two tiles for each of the grid's wavefronts, but not more than two for a bucket (each
+    // stages its bucket again): with one, lists whose walkers sit on few determinants gave
+    // some wavefronts three full tiles and others next to nothing (8 electrons in 20 orbitals,
+    // half of 3e6 walkers on the reference: 219 -> 179 us an iteration; a ring of 14 sites, 90
+    // walkers a bucket, would go from 140 to 160).
+    const int64_t per_bucket = walkers / std::max<int64_t>(BPC * h->n_chunks, 1);
+    while (o.wsh > 6 && (walkers >> o.wsh) < 2 * waves && per_bucket >> o.wsh) --o.wsh;
     const int64_t tiles = std::min<int64_t>(BPC * h->n_chunks, walkers) + (walkers >> o.wsh);
     o.spawn_grid = (int)std::min<int64_t>(o.spawn_grid, next_pow2(std::max<int64_t>(1, (tiles + 3) / 4)));
     o.post_grid = (int)std::min<int64_t>(o.post_grid, next_pow2(std::max<int64_t>(1, h->n_chunks)));
