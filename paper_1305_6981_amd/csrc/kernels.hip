@@ -597,9 +597,10 @@ __device__ __forceinline__ uint4 spawn_words(const SpawnSys &h, det_t det, uint3
 
 // The orbitals of a double excitation (Sec. 5.2) from the words of one Philox block: the
 // electrons p < q from w.y, the holes a and b, in the order drawn, from w.z and w.w.
-// Returns false for a null excitation. pgen: with no point group one of the four
-// per-system values, given as its index pc; else computed here. recip[k] = 1.0 / k,
-// filled by IEEE division (same bits as dividing in place).
+// Returns false for a null excitation (p, q, a and b are orbital numbers all the same, below
+// NSO_MAX: the bounds are looked up for every lane that picked a double). pgen: with no point
+// group one of the four per-system values, given as its index pc; else computed here.
+// recip[k] = 1.0 / k, filled by IEEE division (same bits as dividing in place).
 struct DoubleDraw {
     int p, q, a, b, pc;
     double pgen;
@@ -667,7 +668,12 @@ __device__ __forceinline__ bool draw_double(const SysDesc &d, const ClassView<fa
         if ((same ? no : ne) > self) allowed |= A & cmask_of(d, 2 * g + 1);
     }
     const uint32_t nal = (uint32_t)dpopc(allowed);
-    if (nal == 0) return false;
+    if (nal == 0) {
+        // null: any orbitals will do, but the caller looks their bounds up (p and q are set)
+        x.a = x.b = x.pc = 0;
+        x.pgen = 0.0;
+        return false;
+    }
     const int a = select_bit(allowed, pick(w.z, nal), sel8);
     const int ca = cv.cls(d, a);
     const int pca = 2 * (gpq ^ (ca >> 1)) + (same ? (p & 1) : 1 - (ca & 1));
