@@ -2197,9 +2197,18 @@ int fciqmc_autotune(fciqmc_t *h, int32_t iters_per_trial) {
         const int rc = take_snapshot(h, s, snaps.back());
         if (rc) return rc;
     }
-    const bool was = h->profiling;
+    const bool was = h->profiling, shape_was_set = h->shape_set;
+    const int sg0 = h->spawn_grid, tl0 = h->tile, pg0 = h->post_grid;
     h->profiling = true;
     h->shape_set = true;   // (each trial runs at its own shape)
+    auto give_up = [&](int rc) {   // a trial failed: the shape is again what it was
+        h->spawn_grid = sg0;
+        h->tile = tl0;
+        h->post_grid = pg0;
+        h->shape_set = shape_was_set;
+        h->profiling = was;
+        return rc;
+    };
     auto trial = [&](int sg, int tl, int pg, double &spawn_ns, double &post_ns) -> int {
         h->spawn_grid = sg;
         h->tile = tl;
@@ -2227,10 +2236,7 @@ int fciqmc_autotune(fciqmc_t *h, int32_t iters_per_trial) {
         for (int j = 0; j < 3; ++j) {
             double sn, pn;
             int rc = trial(sgs[i] * cus, tls[j], best_pg, sn, pn);
-            if (rc) {
-                h->profiling = was;
-                return rc;
-            }
+            if (rc) return give_up(rc);
             if (sn < best_s) {
                 best_s = sn;
                 best_sg = sgs[i] * cus;
@@ -2240,10 +2246,7 @@ int fciqmc_autotune(fciqmc_t *h, int32_t iters_per_trial) {
     for (int i = 0; i < 5; ++i) {
         double sn, pn;
         int rc = trial(best_sg, best_tl, pgs[i] * cus, sn, pn);
-        if (rc) {
-            h->profiling = was;
-            return rc;
-        }
+        if (rc) return give_up(rc);
         if (pn < best_p) {
             best_p = pn;
             best_pg = pgs[i] * cus;
