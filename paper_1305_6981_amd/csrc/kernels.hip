@@ -566,9 +566,10 @@ __device__ __forceinline__ SpawnSys spawn_sys(const SysDesc &d) {
     h.npairs = uni((uint32_t)(d.N * (d.N - 1) / 2));
     h.n0 = uni((uint32_t)d.n_emp[0]);
     h.n1 = uni((uint32_t)d.n_emp[1]);
-    h.nl0 = h.n0 >= 2u ? h.n0 : 0u;
-    h.nl1 = h.n1 >= 2u ? h.n1 : 0u;
-    h.nu = (h.n1 > 0u ? h.n0 : 0u) + (h.n0 > 0u ? h.n1 : 0u);
+    // (one electron: the type word still picks a double, which has no choice: null)
+    h.nl0 = d.N >= 2 && h.n0 >= 2u ? h.n0 : 0u;
+    h.nl1 = d.N >= 2 && h.n1 >= 2u ? h.n1 : 0u;
+    h.nu = d.N >= 2 ? (h.n1 > 0u ? h.n0 : 0u) + (h.n0 > 0u ? h.n1 : 0u) : 0u;
     h.mu = (h.n1 > 0u ? 0x5555555555555555ull : 0ull) | (h.n0 > 0u ? 0xAAAAAAAAAAAAAAAAull : 0ull);
     h.f0 = uni(d.bound_f[0]);
     h.f1 = uni(d.bound_f[1]);
@@ -577,7 +578,7 @@ __device__ __forceinline__ SpawnSys spawn_sys(const SysDesc &d) {
     h.ft = uni(d.bound_ft);
     h.sg_mul = uni(d.sg_mul);
     h.sg_sub = uni(d.sg_sub);
-    h.has_double = (int32_t)uni(d.has_double && d.N >= 2 ? 1u : 0u);
+    h.has_double = (int32_t)uni((uint32_t)d.has_double);
     h.defer = (int32_t)uni((uint32_t)d.defer);
     h.c1 = (int32_t)uni(d.n_class == 2 ? 1u : 0u);
     h.coupled = (int32_t)uni((uint32_t)d.hphf);
@@ -668,7 +669,7 @@ __device__ __forceinline__ bool draw_double(const SysDesc &d, const ClassView<fa
         if ((same ? no : ne) > self) allowed |= A & cmask_of(d, 2 * g + 1);
     }
     const uint32_t nal = (uint32_t)dpopc(allowed);
-    if (nal == 0) {
+    if (nal == 0 || N < 2) {
         // null: any orbitals will do, but the caller looks their bounds up (p and q are set)
         x.a = x.b = x.pc = 0;
         x.pgen = 0.0;

@@ -16,6 +16,30 @@ def _words0(det):
     return det if det.ndim == 1 else det[:, 0]
 
 
+@pytest.mark.parametrize("form", ["plain", "group", "two_words", "two_words_group"])
+@pytest.mark.parametrize("p_double", [0.3, 0.6, 1.0])
+def test_one_electron(p_double, form):
+    """One electron has no double excitation: with an explicit share of doubles that share
+    of the attempts is null."""
+    irr = np.array([0, 1, 0, 1, 0, 0]) if form.endswith("group") else None
+    ham = S.synthetic_molecule(6, 1, 0, 41, irreps=irr)
+    ham.p_double = p_double
+    prm = S.Params(tau=0.05, target_walkers=10**9, initial_walkers=2000, initial_shift=1.0, seed=7,
+                   det_words=2 if form.startswith("two_words") else 0)
+    print(f"[gpu] one electron, p_double {p_double}, {form}", flush=True)
+    gpu, ref = F.Solver(ham, prm, F.current_stream()), O.Oracle(ham, prm)
+    gpu.iterate(10)
+    ref.iterate(10)
+    (dg, pg, _), (do, po, _) = gpu.walkers(), ref.walkers()
+    assert np.array_equal(_words0(dg), _words0(do)) and np.array_equal(pg, po)
+    eg, eo = gpu.estimates(), ref.estimates()
+    for k in COUNTS:
+        assert eg[k] == eo[k], k
+    assert (eg["total_spawns"] > 0) == (p_double < 1.0)
+    gpu.close()
+    ref.close()
+
+
 def _pairs_without_target(ham):
     """Pairs of the reference's electrons for which no empty orbital has an empty partner."""
     nso, ref = 2 * ham.n_orb, int(ham.ref_det)
