@@ -384,7 +384,9 @@ Shape launch_shape(const fciqmc_t *h) {
     return o;
 }
 
-// The spawn-record buffer for `cap` records (16 W B each).
+// The spawn-record buffer for `cap` records (16 W B each). The old one is given back first
+// (its records are dead, and there is seldom room for both); on failure there is none, until
+// plan_launch, before the next launch, asks again.
 int ensure_records(fciqmc_t *h, int64_t cap) {
     if (cap <= h->rec_cap) return 0;
     HIP_TRY(hipStreamSynchronize(h->stream));
@@ -1509,7 +1511,9 @@ int plan_launch(fciqmc_t *h, int L, int *L_out) {
             allowed = (int)std::max<double>(1.0, std::min<double>((double)allowed, std::floor(fit)));
         }
     }
-    if (relaid) {
+    // (a buffer that an earlier call could not make larger is gone: asked for again, so that
+    // no launch runs without the slots its descriptors name)
+    if (relaid || h->rec_base > h->rec_cap) {
         const int rc = layout_records(h);
         if (rc) return rc;
     }

@@ -116,3 +116,28 @@ def test_slots_when_the_list_grows():
     assert np.array_equal(dg, do) and np.array_equal(pg, po)
     gpu.close()
     ref.close()
+
+
+@pytest.mark.parametrize("words", [0, 2])
+def test_after_a_buffer_that_does_not_fit(words):
+    """A record buffer no device has room for is refused; the solve then goes on with one of
+    its own size."""
+    ham, prm, _ = S.workload("hubbard8")
+    prm.det_words = words
+    print(f"[gpu] records: a buffer that does not fit, words {words}", flush=True)
+    gpu, ref = F.Solver(ham, prm, F.current_stream()), O.Oracle(ham, prm)
+    for n in (20, 20):
+        gpu.iterate(n)
+        ref.iterate(n)
+        (dg, pg, _), (do, po, _) = gpu.walkers(), ref.walkers()
+        assert np.array_equal(dg if dg.ndim == 1 else dg[:, 0], do if do.ndim == 1 else do[:, 0])
+        assert np.array_equal(pg, po)
+        with pytest.raises(F.FciqmcError) as e:
+            F.fciqmc_set_test_options(gpu.h, 1, -1, 1 << 40)
+        assert e.value.code == -2
+    gpu.iterate(5)
+    ref.iterate(5)
+    (dg, pg, _), (do, po, _) = gpu.walkers(), ref.walkers()
+    assert np.array_equal(pg, po) and len(dg) == len(do)
+    gpu.close()
+    ref.close()
