@@ -472,23 +472,29 @@ int relayout(fciqmc_t *h) {
     for (int s = 0; s < h->max_sys; ++s)
         if (h->sys[s].active) total += h->sys[s].cap / CHUNK;
     if (total > h->chunk_alloc) {
-        int64_t na = next_pow2(std::max<int64_t>(total, 64));
-        hipFree(h->d_chunk_sys);
-        hipFree(h->d_chunk_local);
-        hipFree(h->d_unlisted);
-        hipFree(h->d_bhist);
-        hipFree(h->d_bprev);
-        hipFree(h->d_bext);
-        h->d_chunk_sys = nullptr;
-        h->chunk_alloc = 0;
-        HIP_TRY(hipMalloc(&h->d_chunk_sys, na * sizeof(int32_t)));
-        HIP_TRY(hipMalloc(&h->d_chunk_local, na * sizeof(int32_t)));
-        HIP_TRY(hipMalloc(&h->d_unlisted, BPC * na * sizeof(uint32_t)));
-        HIP_TRY(hipMalloc(&h->d_bhist, BPC * na * sizeof(uint32_t)));
-        HIP_TRY(hipMalloc(&h->d_bprev, BPC * na * sizeof(uint32_t)));
-        HIP_TRY(hipMalloc(&h->d_bext, BPC * na * sizeof(uint64_t)));
-        h->chunk_alloc = na;
+        const int64_t na = next_pow2(std::max<int64_t>(total, 64));
+        const struct {
+            void **p;
+            size_t bytes;
+        } arrays[] = {{(void **)&h->d_chunk_sys, na * sizeof(int32_t)},
+                      {(void **)&h->d_chunk_local, na * sizeof(int32_t)},
+                      {(void **)&h->d_unlisted, BPC * na * sizeof(uint32_t)},
+                      {(void **)&h->d_bhist, BPC * na * sizeof(uint32_t)},
+                      {(void **)&h->d_bprev, BPC * na * sizeof(uint32_t)},
+                      {(void **)&h->d_bext, BPC * na * sizeof(uint64_t)}};
         drop_graphs(h);
+        h->chunk_alloc = 0;   // (without them plan_launch lays out again before a launch)
+        for (const auto &x : arrays) {
+            hipFree(*x.p);
+            *x.p = nullptr;
+        }
+        for (const auto &x : arrays)
+            if (hipMalloc(x.p, x.bytes) != hipSuccess) {
+                (void)hipGetLastError();
+                return set_err(FCIQMC_ENOMEM, "the maps of " + std::to_string(total) +
+                                                  " chunks do not fit in device memory");
+            }
+        h->chunk_alloc = na;
     }
     // record counts start at zero (k_post keeps them so after every iteration)
     HIP_TRY(hipMemsetAsync(h->d_bhist, 0, BPC * h->chunk_alloc * sizeof(uint32_t), h->stream));
@@ -1452,6 +1458,10 @@ int extend_buckets(fciqmc_t *h) {
 int plan_launch(fciqmc_t *h, int L, int *L_out) {
     int allowed = L;
     bool relaid = false;
+    if (h->n_chunks > h->chunk_alloc) {   // (an earlier call had no room for the chunks' maps)
+        const int rc = relayout(h);
+        if (rc) return rc;
+    }
     for (int s = 0; s < h->max_sys; ++s) {
         SysHost &S = h->sys[s];
         if (!S.active || S.fatal) continue;

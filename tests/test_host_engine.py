@@ -71,3 +71,25 @@ def test_record_buffer_that_cannot_grow(fake, how):
         assert fake.fake_spawns() == spawns + 5 and fake.fake_faults() == 0
         F.fciqmc_free(h)
     """)
+
+
+def test_chunk_maps_that_do_not_fit(fake):
+    """A list re-bucketed into the last of the memory leaves none for the maps of its chunks:
+    the next call asks for them again and launches nothing without them."""
+    fake_device.run(fake, """
+        ham = S.hubbard_ring(8, 4.0)
+        prm = S.Params(tau=0.01, target_walkers=1 << 23, initial_walkers=1000, det_capacity=4096)
+        fake.fake_iteration(1000, 100, 300, 100, 5, 20)
+        h = F.fciqmc_init(ham, prm)
+        F.fciqmc_iterate(h, 3)
+        fake.fake_capacity(fake.fake_used() + F.fciqmc_footprint_bytes(ham, prm))
+        assert error(F.fciqmc_reserve, h, 1 << 24) != 0
+        for _ in range(2):
+            assert error(F.fciqmc_iterate, h, 1) != 0
+        assert fake.fake_spawns() == 3 and fake.fake_faults() == 0
+        fake.fake_capacity(64 << 30)
+        F.fciqmc_iterate(h, 5)
+        assert fake.fake_spawns() == 8 and fake.fake_faults() == 0
+        F.fciqmc_free(h)
+        assert fake.fake_used() == 0
+    """)
