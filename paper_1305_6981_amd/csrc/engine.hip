@@ -1812,29 +1812,35 @@ int compute_e0(fciqmc_t *h, int s) {
 }
 
 int admit_full(fciqmc_t *h, int s, const fciqmc_hamiltonian *ham, const fciqmc_params *prm) {
+    const int64_t floor0 = h->rec_floor;
     int rc = admit(h, s, ham, prm);
-    if (rc) {
+    if (!rc) rc = compute_e0(h, s);
+    if (!rc && prm->spawn_capacity > 0) {   // the record buffer is shared by the handle's systems
+        h->rec_floor = std::max(h->rec_floor, prm->spawn_capacity);
+        rc = ensure_records(h, prm->spawn_capacity);
+    }
+    if (rc) {   // the slot is free again
+        const std::string keep = g_err;
         SysHost &S = h->sys[s];
-        if (S.block) hipFree(S.block);
+        if (S.block) {
+            (void)hipStreamSynchronize(h->stream);
+            hipFree(S.block);
+        }
         S = SysHost();
+        h->rec_floor = floor0;
         h->hdesc[s] = SysDesc{};
+        h->hstatus[s] = 0;
         relayout(h);
         upload_desc(h);
+        g_err = keep;
         return rc;
     }
-    rc = compute_e0(h, s);
-    if (rc) return rc;
     const int64_t n0 = prm->initial_walkers > 0 ? prm->initial_walkers : 10;
     h->sys[s].last = IterRecord{};
     h->sys[s].last.nw = n0;
     h->sys[s].last.nd = 1;
     h->sys[s].last.c0 = n0;
     h->sys[s].last.shift = prm->initial_shift;
-    if (prm->spawn_capacity > 0) {   // the record buffer is shared by the handle's systems
-        h->rec_floor = std::max(h->rec_floor, prm->spawn_capacity);
-        rc = ensure_records(h, prm->spawn_capacity);
-        if (rc) return rc;
-    }
     return upload_desc(h);
 }
 

@@ -93,3 +93,26 @@ def test_chunk_maps_that_do_not_fit(fake):
         F.fciqmc_free(h)
         assert fake.fake_used() == 0
     """)
+
+
+def test_refused_admission_leaves_its_slot(fake):
+    """An admission refused for its record buffer leaves the slot free, the memory as it was
+    and the other systems' slots at their own count."""
+    fake_device.run(fake, """
+        ham = S.hubbard_ring(8, 4.0)
+        prm = S.Params(tau=0.01, target_walkers=10**6, initial_walkers=1000)
+        fake.fake_iteration(1000, 100, 300, 100, 5, 20)
+        h = F.fciqmc_batch_create(2, [ham], [prm])
+        F.fciqmc_batch_iterate(h, 3)
+        used = fake.fake_used()
+        prm.spawn_capacity = 1 << 40
+        assert error(F.fciqmc_batch_admit, h, ham, prm) == -2
+        assert F.fciqmc_batch_active(h) == 1
+        F.fciqmc_batch_iterate(h, 3)
+        assert fake.fake_used() == used and fake.fake_faults() == 0
+        prm.spawn_capacity = 0
+        assert F.fciqmc_batch_admit(h, ham, prm) == 1
+        F.fciqmc_batch_iterate(h, 3)
+        assert fake.fake_faults() == 0
+        F.fciqmc_free(h)
+    """)
