@@ -283,7 +283,12 @@ struct fciqmc_t {
     int post_grid = 1024;
     int tile = 2048;
     bool shape_set = false;                 // the launch shape was set or tuned: used as it is
-    std::map<std::array<int, 6>, hipGraphExec_t> graphs;   // by iterations, kernel variant, shape
+    struct Graph {
+        hipGraphExec_t exec;
+        int64_t used;                       // when it was last launched
+    };
+    std::map<std::array<int, 6>, Graph> graphs;   // by iterations, kernel variant, shape
+    int64_t graph_clock = 0;
     bool use_graph = true;
     bool profiling = false;
     hipEvent_t ev[NKERN + 1] = {};
@@ -298,7 +303,7 @@ struct fciqmc_t {
 namespace {
 
 void drop_graphs(fciqmc_t *h) {
-    for (auto &kv : h->graphs) (void)hipGraphExecDestroy(kv.second);
+    for (auto &kv : h->graphs) (void)hipGraphExecDestroy(kv.second.exec);
     h->graphs.clear();
 }
 
@@ -1387,8 +1392,10 @@ int fill_estimates(fciqmc_t *h, int s, fciqmc_estimates *o) {
     return 0;
 }
 
-// Statistics of the list as loaded (before any iteration): N_w, N_d, C_0, num.
-int run_iterations(fciqmc_t *h, int L, bool sample);
+// Captured graphs a handle keeps (up to 64 iterations of three kernels each): a list that
+// grows, or calls of changing lengths, would otherwise leave one for every combination of
+// length and launch shape it has met.
+constexpr size_t MAX_GRAPHS = 64;
 
 int capture_or_get(fciqmc_t *h, int L, hipGraphExec_t *out) {
     // one graph per length, spawning variant and launch shape
@@ -1399,8 +1406,16 @@ int capture_or_get(fciqmc_t *h, int L, hipGraphExec_t *out) {
     const std::array<int, 6> key = {L, a.plain, sh.wsh, sh.spawn_grid, sh.post_grid, sh.post_seg};
     auto it = h->graphs.find(key);
     if (it != h->graphs.end()) {
-        *out = it->second;
+        it->second.used = ++h->graph_clock;
+        *out = it->second.exec;
         return 0;
+    }
+    if (h->graphs.size() >= MAX_GRAPHS) {   // the one not launched for longest (none is running)
+        auto old = h->graphs.begin();
+        for (auto k = h->graphs.begin(); k != h->graphs.end(); ++k)
+            if (k->second.used < old->second.used) old = k;
+        (void)hipGraphExecDestroy(old->second.exec);
+        h->graphs.erase(old);
     }
     hipGraph_t g = nullptr;
     HIP_TRY(hipStreamBeginCapture(h->stream, hipStreamCaptureModeRelaxed));
@@ -1410,7 +1425,7 @@ int capture_or_get(fciqmc_t *h, int L, hipGraphExec_t *out) {
     hipGraphExec_t ex = nullptr;
     HIP_TRY(hipGraphInstantiate(&ex, g, nullptr, nullptr, 0));
     HIP_TRY(hipGraphDestroy(g));
-    h->graphs[key] = ex;
+    h->graphs[key] = {ex, ++h->graph_clock};
     *out = ex;
     return 0;
 }

@@ -116,3 +116,23 @@ def test_refused_admission_leaves_its_slot(fake):
         assert fake.fake_faults() == 0
         F.fciqmc_free(h)
     """)
+
+
+def test_captured_graphs_are_bounded(fake):
+    """A solve whose population, births and call lengths keep changing meets hundreds of
+    combinations of length and launch shape; the handle keeps the 64 used last."""
+    fake_device.run(fake, """
+        ham = S.hubbard_ring(8, 4.0)
+        prm = S.Params(tau=0.01, target_walkers=10**9, initial_walkers=1000, det_capacity=1 << 23)
+        h = F.fciqmc_init(ham, prm)
+        most = 0
+        for step in range(400):
+            nw = 1000 << (step * 7 % 17)
+            fake.fake_iteration(nw, 100, 300, 100, (step * 5 % 11) ** 6, 20)
+            F.fciqmc_iterate(h, 2 + step * 13 % 40)
+            most = max(most, fake.fake_graphs())
+        assert most == 64, most
+        assert fake.fake_faults() == 0
+        F.fciqmc_free(h)
+        assert fake.fake_graphs() == 0
+    """)
