@@ -1463,6 +1463,19 @@ int extend_buckets(fciqmc_t *h) {
     return 0;
 }
 
+// Whether list S may have nc entries' worth of buckets for its records' sake: they save time
+// only, so the table and the slots that BUCKET_RECS records a bucket come to (120, with the
+// planner's slack over the fullest of many) may take half of the free memory, the old ones
+// still in place. The rest is for what lists cannot do without.
+int split_fits(const fciqmc_t *h, const SysHost &S, int64_t nc, bool *fits) {
+    size_t fr = 0, tot = 0;
+    HIP_TRY(hipMemGetInfo(&fr, &tot));
+    const int64_t need = table_bytes(nc, S.W) + integral_bytes(S.M, S.W) +
+                         nc / BQ * (int64_t)(128 * 16 * h->W);
+    *fits = need <= (int64_t)(fr / 2);
+    return 0;
+}
+
 // Before a launch of up to L iterations: re-bucket any main list whose buckets
 // would pass 5/8 full on average during the launch (each iteration adds at most
 // `growth` entries, the largest increase seen, with slack), size the record slots per
@@ -1495,8 +1508,12 @@ int plan_launch(fciqmc_t *h, int L, int *L_out) {
         // by their entries merge in several rounds, from memory: more buckets then, unless
         // the device has no room for them.
         if (S.last.spawns > S.cap / BQ * (BUCKET_RECS + BUCKET_RECS / 2) && !S.no_split) {
-            const int rc = rebucket_system(h, s, round_cap(S.last.spawns / BUCKET_RECS * BQ), 0);
-            if (rc == FCIQMC_ECAPACITY) S.no_split = true;
+            const int64_t nc = round_cap(S.last.spawns / BUCKET_RECS * BQ);
+            bool fits = false;
+            int rc = split_fits(h, S, nc, &fits);
+            if (rc) return rc;
+            if (fits) rc = rebucket_system(h, s, nc, 0);
+            if (!fits || rc == FCIQMC_ECAPACITY) S.no_split = true;
             else if (rc) return rc;
         }
         const int64_t room = (S.cap * 5 / 8 - used) / g;

@@ -136,3 +136,27 @@ def test_captured_graphs_are_bounded(fake):
         F.fciqmc_free(h)
         assert fake.fake_graphs() == 0
     """)
+
+
+def test_more_buckets_only_where_there_is_room(fake):
+    """More buckets for a list of many records save time only: they are not made where their
+    table fits into the device but would leave no room for their record slots."""
+    fake_device.run(fake, """
+        ham = S.hubbard_ring(8, 4.0)
+        prm = S.Params(tau=0.01, target_walkers=10**6, initial_walkers=1000, det_capacity=1 << 20)
+        fake.fake_iteration(1000000, 100000, 4000000, 100000, 5, 20)
+        h = F.fciqmc_init(ham, prm)
+        F.fciqmc_iterate(h, 1)
+        split = 4000000 // 32 * 256 * 20 + 4000000 // 32 * 4
+        fake.fake_capacity(fake.fake_used() + split + (12 << 20))
+        F.fciqmc_iterate(h, 5)
+        assert F.fciqmc_estimators(h)["table_slots"] == 1 << 20
+        fake.fake_capacity(64 << 30)
+        F.fciqmc_free(h)
+        h = F.fciqmc_init(ham, prm)
+        F.fciqmc_iterate(h, 1)
+        F.fciqmc_iterate(h, 5)
+        assert F.fciqmc_estimators(h)["table_slots"] >= 4000000 // 32 * 256
+        assert fake.fake_faults() == 0
+        F.fciqmc_free(h)
+    """)
