@@ -257,7 +257,7 @@ struct fciqmc_t {
     unsigned long long *d_total = nullptr;  // lengths of the tile lists
     uint32_t *d_unlisted = nullptr;         // buckets whose tiles did not fit
     int32_t *d_tiles = nullptr;             // the spawn tiles, 16 B each
-    bool tile_map_off = false;              // its allocation failed once: search instead
+    bool tile_map_off = false;              // its allocation failed once: whole buckets instead
     void *d_stage = nullptr;                // this device's staging area (not owned)
     // spawn records (see EngineArgs) and the spill list
     void *d_recs = nullptr;

@@ -148,17 +148,6 @@ __device__ __forceinline__ double u01(uint64_t x) {
     return (double)(x >> 11) * (1.0 / 9007199254740992.0);
 }
 
-// The four words of one Philox block of a spawning attempt: word 0 picks the
-// type and, rescaled within the chosen type's interval, is the acceptance
-// uniform; words 1-3 pick the orbitals.
-__device__ __forceinline__ uint4 draw_words(uint64_t seed, det_t det, uint32_t k, int64_t iter,
-                                            uint32_t block) {
-    const uint64_t lo = lo64(det), key = seed ^ hi64(det);
-    const uint4 ctr = make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), k,
-                                 ((uint32_t)((uint64_t)iter & 0xFFFFFFu) << 8) | block);
-    return philox10(ctr, (uint32_t)key, (uint32_t)(key >> 32));
-}
-
 // w / 2^32, exact in double.
 __device__ __forceinline__ double u01_32(uint32_t w) {
     return (double)w * (1.0 / 4294967296.0);
@@ -254,7 +243,6 @@ __device__ __forceinline__ T ld_uniform(const T *p) {
 // 16-byte global loads and stores through plain vector types.
 typedef int v4i32 __attribute__((ext_vector_type(4)));
 typedef unsigned long long v2u64 __attribute__((ext_vector_type(2)));
-typedef double v2f64 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ int4 gload_i4(const int32_t *p) {
     const v4i32 v = *gp(reinterpret_cast<const v4i32 *>(p));
     return make_int4(v.x, v.y, v.z, v.w);
@@ -262,10 +250,6 @@ __device__ __forceinline__ int4 gload_i4(const int32_t *p) {
 __device__ __forceinline__ ulonglong2 gload_u2(const uint64_t *p) {
     const v2u64 v = *gp(reinterpret_cast<const v2u64 *>(p));
     return make_ulonglong2(v.x, v.y);
-}
-__device__ __forceinline__ double2 gload_d2(const double *p) {
-    const v2f64 v = *gp(reinterpret_cast<const v2f64 *>(p));
-    return make_double2(v.x, v.y);
 }
 __device__ __forceinline__ void gstore_i4(void *p, int x, int y, int z, int w) {
     v4i32 v;
@@ -590,6 +574,9 @@ template <typename T>
 __device__ __forceinline__ T pick_if(bool c, T a, T b) {
     return c ? a : b;
 }
+// The four words of one Philox block of a spawning attempt: word 0 picks the
+// type and, rescaled within the chosen type's interval, is the acceptance
+// uniform; words 1-3 pick the orbitals.
 __device__ __forceinline__ uint4 spawn_words(const SpawnSys &h, det_t det, uint32_t k) {
     const uint64_t lo = lo64(det), key = h.seed ^ hi64(det);
     return philox10(make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), k, h.iterw), (uint32_t)key,
@@ -847,23 +834,6 @@ __device__ double shift_log(double x) {
 
 __device__ __forceinline__ bool participating(const SysDesc &d, uint32_t status) {
     return d.active && status == 0 && d.iter < d.stop_at;
-}
-
-// ---------------------------------------------------------------------------
-// Block reductions (256 threads, fixed order -> deterministic).
-// ---------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ T block_sum(T v, T *sh) {
-    const int t = threadIdx.x;
-    sh[t] = v;
-    __syncthreads();
-    for (int s = (int)blockDim.x / 2; s > 0; s >>= 1) {
-        if (t < s) sh[t] = sh[t] + sh[t + s];
-        __syncthreads();
-    }
-    const T r = sh[0];
-    __syncthreads();
-    return r;
 }
 
 // Sum over the 64 lanes of a wavefront with a fixed butterfly (deterministic).
@@ -1145,7 +1115,7 @@ __global__ __launch_bounds__(256) void k_tiles(EngineArgs a, const SysDesc *__re
 // saved is the element's two gathers and the division for most attempts, and wavefronts
 // that run them for a few lanes only. Single excitations are queued apart.
 //
-// Bound, in large launches, by vector-instruction issue (405 wavefront instructions per 64
+// Bound, in large launches, by vector-instruction issue (420 wavefront instructions per 64
 // attempts, a Philox block and the choice of four orbitals most of them); in small ones by
 // the chain of memory round trips from the lists to the records (some 17 us for one tile).
 // Against a workgroup per tile of a 1024-entry chunk, which searched each attempt's entry
@@ -2234,8 +2204,8 @@ void k_post(EngineArgs a, const SysDesc *__restrict__ desc) {
     __shared__ int s_accsys;
     const int64_t nch = *a.nchunks;
     // (The wavefront's number, a segment's system and a bucket's sizes are left to vector
-    // registers: as scalars they cost 135 spilled scalar registers and scalar loads at each
-    // use, 1.44 instead of 1.23 ms at 1.4e8 walkers.)
+    // registers: as scalars they were loaded again at each use, 1.44 instead of 1.23 ms at
+    // 1.4e8 walkers. The kernel spills 143 scalar and 68 vector registers as it is.)
     const int t = threadIdx.x, lane = t & 63, wid = t >> 6;
     WaveLds &W = L.w[wid];
     if (blockIdx.x == 0 && t < NLIST) {   // k_spawn's counters, for the next iteration
